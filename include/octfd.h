@@ -192,21 +192,20 @@ int rk_step(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *params, 
 int rk_step_static(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *params, double dt,
                    double *u_zipped_dev, void *hip_stream);
 
-/* Variant of the ghost rule with centred interpolation stencils (level-ordered).  Identical to
+/* Variant of the ghost rule with centred interpolation stencils.  Identical to
  * unzip except for padded points whose containing leaf L is one level coarser: there every odd
  * fine coordinate f = P - 16a' uses the centred six-point stencil on the coarse lattice, nodes
  * c0-2 .. c0+3 with c0 = (f-1)/2 and weights (3, -25, 150, 150, -25, 3)/256, instead of the stencil
  * clamped to L's own eight nodes.  Nodes outside 0..7 are ghost points of L and are taken from L's
- * padded block (local index c+3), so blocks are filled coarsest level first (one launch per
- * level) and the result depends on more than one source leaf.  Same axis order and fma chain.
+ * padded block (local index c+3), so the result depends on more than one source leaf; the 2:1 balance
+ * keeps those ghost points out of leaves that are coarser than L.  Same axis order and fma chain.
  * The interpolation error at a level jump is much smaller (no half-cell extrapolation) and level
  * jumps stay stable for wave propagation over long times.
  *
  * rk_step_centred is rk_step with F = zip(rhs_eval(unzip_centred(.))), bit-identical to that
  * composition.  It differs from rk_step only in how the virtual blocks (see rhs_eval_zipped) are
- * filled before each stage: with the centred stencils, level by level, each from the part of its
- * source leaf's padded block that it needs (gathered from the zipped vector and from the virtual
- * blocks of the level before).  Same stage kernels, same workspace (rk_centred_workspace_bytes
+ * filled before each stage: with the centred stencils, each from the part of its source leaf's
+ * padded block that it needs (gathered from the zipped vector).  Same stage kernels, same workspace (rk_centred_workspace_bytes
  * equals rk_workspace_bytes), and within a few per cent of rk_step's time. */
 int unzip_centred(const ot_tree *tree, int nvar, const double *zipped_dev, double *padded_dev, void *hip_stream);
 int rk_centred_workspace_bytes(const ot_tree *tree, ot_rhs_kind kind, size_t *bytes);

@@ -88,10 +88,10 @@ int ensure_device(const ot_tree* t)
     if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e);
     // one allocation for all tables, each part 256-byte aligned
     const HostTree& h = t->host;
-    constexpr int kParts = 6;
+    constexpr int kParts = 5;
     auto ibytes = [](const std::vector<int32_t>& v) { return v.size() * sizeof(int32_t); };
-    const void* part[kParts] = {h.leaves.data(), h.ghost_v.data(), h.vblk.data(), h.vlist.data(), h.units.data(), h.vneed.data()};
-    const size_t bytes[kParts] = {h.leaves.size() * sizeof(ot_leaf), ibytes(h.ghost_v), ibytes(h.vblk), ibytes(h.vlist), ibytes(h.units), ibytes(h.vneed)};
+    const void* part[kParts] = {h.leaves.data(), h.ghost_v.data(), h.vblk.data(), h.units.data(), h.vneed.data()};
+    const size_t bytes[kParts] = {h.leaves.size() * sizeof(ot_leaf), ibytes(h.ghost_v), ibytes(h.vblk), ibytes(h.units), ibytes(h.vneed)};
     size_t off[kParts + 1] = {0};
     for (int i = 0; i < kParts; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
     char* base = nullptr;
@@ -105,7 +105,7 @@ int ensure_device(const ot_tree* t)
     auto ints = [&](int i) { return reinterpret_cast<const int32_t*>(base + off[i]); };
     t->d_base = base;
     t->dev = DeviceTree{reinterpret_cast<const ot_leaf*>(base + off[0]), static_cast<int64_t>(h.leaves.size()),
-                        ints(1), ints(2), ints(3), h.n_virt, ints(4), static_cast<int64_t>(h.units.size()), ints(5)};
+                        ints(1), ints(2), h.n_virt, ints(3), static_cast<int64_t>(h.units.size()), ints(4)};
     t->device = dev;
     return resolve_static_workspace(dev);
 }
@@ -271,7 +271,7 @@ static int unzip_any(const ot_tree* tree, bool centred, int nvar, const double* 
     if (int rc = ensure_virtual_scratch(tree, vbytes)) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
     const DeviceTree dv = dev_view(tree);
-    hipError_t e = centred ? launch_virtual_centred(dv, tree->host.vlevel_start, nvar, zipped_dev, tree->d_virt, s)
+    hipError_t e = centred ? launch_virtual_centred(dv, nvar, zipped_dev, tree->d_virt, s)
                            : launch_virtual(dv, nvar, zipped_dev, tree->d_virt, s);
     if (e == hipSuccess) e = launch_unzip(dv, nvar, zipped_dev, tree->d_virt, padded_dev, s);
     return e == hipSuccess ? OT_OK : hip_fail(e);
@@ -370,7 +370,7 @@ static int rk_step_launch(const ot_tree* tree, ot_rhs_kind kind, const ot_rhs_pa
         // the virtual blocks of this stage's input first; the stream orders them before the stage kernel and
         // after the previous stage's reads of the same array
         hipError_t e = hipSuccess;
-        if (vbytes && centred) e = launch_virtual_centred(dv, tree->host.vlevel_start, ot_rhs_nvar_in(kind), st[i].in, virt, s);
+        if (vbytes && centred) e = launch_virtual_centred(dv, ot_rhs_nvar_in(kind), st[i].in, virt, s);
         else if (vbytes) e = launch_virtual(dv, ot_rhs_nvar_in(kind), st[i].in, virt, s);
         if (e == hipSuccess) e = launch_rhs(dv, kind, true, ep[i], st[i], s);
         if (e != hipSuccess) return hip_fail(e);

@@ -375,12 +375,21 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual(DeviceTree tr, int nvar, c
 // Virtual blocks with the centred ghost rule.  The value at a fine position inside a leaf L that is one level coarser
 // is the centred six-point stencil on the coarse lattice around it, nodes c0 - 2 .. c0 + 3 with c0 = f / 2, and nodes
 // outside L are ghost points of L.  A child octant o of L therefore needs, per axis, the nine coarse nodes
-// 4 o - 2 .. 4 o + 6: a 9^3 part of L's padded block, which is gathered here straight from the zipped array and from
-// the virtual blocks of L's own level (a plan of 729 sources, made once per workgroup from L's table row and shared
-// by all variables), so launches go level by level, coarsest first.  Then the same three passes as in k_virtual,
-// with nine nodes per line (81, 72 and 64 lines: a lane takes a second line where there are more than 64).
+// 4 o - 2 .. 4 o + 6: a 9^3 part of L's padded block, which is gathered here straight from the zipped array (729
+// sources).  None of them lies in another virtual block, so one launch fills them all: a virtual block is needed because
+// some block touches the octant, that block's parent P is a same-level neighbour of L, and the seven neighbours of L on
+// the octant's side are 26-neighbours of P too (per axis they step back towards P where L is off P, and one to either
+// side where it is not); P is subdivided, so the 2:1 balance leaves none of them coarser than L.
+// Then the same three passes as in k_virtual, with nine nodes per line.  A lane gathers the nine nodes of its x lines
+// (81 of them: the first 17 lanes take a second one) into registers, so that the staging array is first written by the x
+// pass: where a line lies is worked out once per virtual block, as two sources (the part inside L's x range and the part
+// beyond it), and shared by all variables of the wavefront.  As in k_virtual, a wavefront owns one variable of one virtual
+// block at a time, with fewer than eight variables a workgroup takes several virtual blocks, and nothing needs a
+// workgroup barrier.
+// (47,783 blocks, 18,256 virtual blocks, two variables: 85 us per call; with one virtual block per workgroup, six of its
+// eight wavefronts idle, and one launch per level it was 154 us.)
 constexpr int CN = 9;                                // coarse nodes per axis
-constexpr int CRS = CN, CPS = CN * CN + 7;           // row and plane stride of a wavefront's staging array: 88 = 24 (mod 32)
+constexpr int CPS = CN * NPT;                        // plane stride of a wavefront's staging array (lines of 8 after the x pass): 72 = 8 (mod 32)
 constexpr int CSTAGE = CN * CPS;
 
 // the eight fine values of a line with nine nodes v (node n is coarse node 4 o - 2 + n): even f passes node c0 through,
@@ -397,75 +406,93 @@ __device__ __forceinline__ void fine_line_centred(const double (&v)[CN], double 
     }
 }
 
-__global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, const int32_t* __restrict__ list, int64_t nlist, int nvar,
-                                                              const double* __restrict__ zipped, double* virt)
+// Where the nine nodes of an x line come from, as byte offsets into one variable's zipped array: nodes 0..3, 4..7 of the
+// octant of L's size that holds the line (`lo`, `hi`: of nodes 0 and 4; they are two leaves where that octant is
+// subdivided) and the nodes beyond it on the side of the child octant (`out`: of the first one); distance of two nodes in bytes.
+struct LineSource { uint32_t lo, hi, out; int in_step, out_step; };
+
+__device__ __forceinline__ LineSource line_source(const int32_t* row, int ox, int jj, int kk)
+{
+    const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2), rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
+    const int ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
+    const int rx = ox ? 2 : 0;
+    const int32_t* e = &row[(rz * 9 + ry * 3 + 1) * 5];          // the centre entry is L itself
+    const int32_t* g = &row[(rz * 9 + ry * 3 + rx) * 5];
+    LineSource s;
+    s.lo = ghost_source(e, 1, ry, rz, 0, ly, lz);
+    s.hi = ghost_source(e, 1, ry, rz, 4, ly, lz);
+    s.out = ghost_source(g, rx, ry, rz, ox ? 0 : 6, ly, lz);
+    s.in_step = e[0] == K_SAME ? 8 : 16;
+    s.out_step = g[0] == K_SAME ? 8 : 16;
+    return s;
+}
+// the nine nodes of a line of a child octant in the lower (O = 0: nodes -2..6) or upper (O = 1: nodes 2..10) half of L's x range
+template <int O>
+__device__ __forceinline__ void load_line(double (&v)[CN], const double* base, const LineSource& s)
+{
+#pragma unroll
+    for (int m = 0; m < CN; ++m) {
+        const int n = 4 * O - 2 + m;                 // node
+        v[m] = n < 0 ? ldg(base, s.out + (n + 2) * s.out_step)
+               : n < 4 ? ldg(base, s.lo + n * s.in_step)
+               : n < 8 ? ldg(base, s.hi + (n - 4) * s.in_step)
+                       : ldg(base, s.out + (n - 8) * s.out_step);
+    }
+}
+
+__global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int nvar, const double* __restrict__ zipped,
+                                                              double* __restrict__ virt)
 {
     __shared__ double staging[8][CSTAGE];
-    __shared__ uint32_t plan[CN * CN * CN];          // byte offsets of the 729 sources, bit 0: virtual block
-    __shared__ int32_t gt[27 * 5];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int64_t w = block_of_workgroup(blockIdx.x), nb = tr.nb;
-    if (w >= nlist) return;                          // uniform
-    const int64_t q = list[w];
+    __shared__ int32_t rows[8][27 * 5];              // L's table row, a copy for each wavefront
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int nv = nvar < 8 ? nvar : 8, per = 8 / nv;
+    const int sub = wave / nv, v0 = wave - sub * nv;
+    const int64_t q = block_of_workgroup(blockIdx.x) * per + sub, nb = tr.nb;
+    if (sub >= per || q >= tr.n_virt) return;        // uniform over the wavefront; the kernel has no workgroup barrier
     const int64_t leaf = tr.vblk[2 * q];
     const int oct = tr.vblk[2 * q + 1];
     const int need = tr.vneed[q];                    // y rows and z planes that any block reads
-    if (tid < 27 * 5) gt[tid] = tr.ghost_v[leaf * (27 * 5) + tid];
-    __syncthreads();
-    for (int p = tid; p < CN * CN * CN; p += NTHREADS) {
-        const int nz = p / (CN * CN), r = p - nz * CN * CN, ny = r / CN, nx = r - ny * CN;
-        // position in L's padded block: coarse node 4 o - 2 + n, shifted by the three ghost layers
-        const int ii = 4 * (oct & 1) + 1 + nx, jj = 4 * ((oct >> 1) & 1) + 1 + ny, kk = 4 * (oct >> 2) + 1 + nz;
-        const int rx = ii < PAD ? 0 : (ii < PAD + NPT ? 1 : 2);
-        const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2);
-        const int rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
-        const int lx = ii - PAD + (1 - rx) * NPT, ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
-        plan[p] = ghost_source(&gt[(rz * 9 + ry * 3 + rx) * 5], rx, ry, rz, lx, ly, lz);   // the centre entry is L itself
-    }
-    __syncthreads();
+    const int ox = oct & 1, oy = (oct >> 1) & 1, oz = oct >> 2;
+    int32_t* row = rows[wave];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+        if (lane + 64 * m < 27 * 5) row[lane + 64 * m] = tr.ghost_v[leaf * (27 * 5) + lane + 64 * m];
+    __builtin_amdgcn_wave_barrier();
+    // this lane's x lines: (cz, cy) = (line / 9, line % 9), in L's padded block shifted by the three ghost layers
+    const int line0 = lane, line1 = min(lane + 64, CN * CN - 1);
+    const bool second = lane + 64 < CN * CN;
+    const LineSource s0 = line_source(row, ox, 4 * oy + 1 + line0 % CN, 4 * oz + 1 + line0 / CN);
+    const LineSource s1 = line_source(row, ox, 4 * oy + 1 + line1 % CN, 4 * oz + 1 + line1 / CN);
     double* A = staging[wave];
     const int hi = lane >> 3, lo = lane & 7;
     const int64_t in_stride = nb * BLK, out_stride = tr.n_virt * BLK;
     double* out = virt + q * BLK + lane;
-    // this lane's share of the gather: elements lane, lane + 64, ... of the 729
-    constexpr int NG = (CN * CN * CN + 63) / 64;     // 12
-    uint32_t off[NG];
-    int dst[NG];
-#pragma unroll
-    for (int m = 0; m < NG; ++m) {
-        const int p = min(lane + 64 * m, CN * CN * CN - 1);
-        const int nz = p / (CN * CN), r = p - nz * CN * CN, ny = r / CN;
-        off[m] = plan[p];
-        dst[m] = nz * CPS + ny * CRS + (r - ny * CN);
-    }
-    auto gather = [&](double (&g)[NG], int v) {
+    double n0[CN], n1[CN];
+    auto gather = [&](int v) {
         const double* base = zipped + v * in_stride;
-        const double* vbase = virt + v * out_stride;
-#pragma unroll
-        for (int m = 0; m < NG; ++m) g[m] = ldg((off[m] & 1u) ? vbase : base, off[m] & ~1u);
-    };
-    double nxt[NG];
-    if (wave < nvar) gather(nxt, wave);
-#pragma unroll 1
-    for (int v = wave; v < nvar; v += 8) {
-#pragma unroll
-        for (int m = 0; m < NG; ++m) A[dst[m]] = nxt[m];         // the last element is stored twice by the lanes past 729
-        if (v + 8 < nvar) gather(nxt, v + 8);
-        __builtin_amdgcn_wave_barrier();
-        double c[CN], r[8];
-        // x pass: lines (cz, cy), 81 of them; in place (a lane writes the first eight positions of the row it has read)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int line = lane + 64 * h;
-            if (line < CN * CN) {
-                double* row = A + (line / CN) * CPS + (line % CN) * CRS;
-#pragma unroll
-                for (int m = 0; m < CN; ++m) c[m] = row[m];
-                fine_line_centred(c, r);
-#pragma unroll
-                for (int m = 0; m < 8; ++m) row[m] = r[m];
-            }
+        if (ox) {                                    // uniform
+            load_line<1>(n0, base, s0);
+            if (second) load_line<1>(n1, base, s1);
+        } else {
+            load_line<0>(n0, base, s0);
+            if (second) load_line<0>(n1, base, s1);
         }
+    };
+    gather(v0);
+#pragma unroll 1
+    for (int v = v0; v < nvar; v += nv) {
+        double c[CN], r[8];
+        // x pass: lines (cz, cy), from registers
+        fine_line_centred(n0, r);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) A[line0 * NPT + m] = r[m];
+        if (second) {
+            fine_line_centred(n1, r);
+#pragma unroll
+            for (int m = 0; m < 8; ++m) A[line1 * NPT + m] = r[m];
+        }
+        if (v + nv < nvar) gather(v + nv);
         __builtin_amdgcn_wave_barrier();
         // y pass: lines (cz, tx), 72 of them; in place
 #pragma unroll
@@ -474,21 +501,21 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, con
             if (line < CN * 8) {
                 double* col = A + (line >> 3) * CPS + (line & 7);
 #pragma unroll
-                for (int m = 0; m < CN; ++m) c[m] = col[m * CRS];
+                for (int m = 0; m < CN; ++m) c[m] = col[m * NPT];
                 fine_line_centred(c, r);
 #pragma unroll
-                for (int m = 0; m < 8; ++m) col[m * CRS] = r[m];
+                for (int m = 0; m < 8; ++m) col[m * NPT] = r[m];
             }
         }
         __builtin_amdgcn_wave_barrier();
         // z pass: lines (ty, tx) = (hi, lo)
 #pragma unroll
-        for (int m = 0; m < CN; ++m) c[m] = A[m * CPS + hi * CRS + lo];
+        for (int m = 0; m < CN; ++m) c[m] = A[m * CPS + lane];
         fine_line_centred(c, r);
 #pragma unroll
         for (int m = 0; m < 8; ++m)
             if (((need >> hi) & 1) && ((need >> (8 + m)) & 1)) out[v * out_stride + m * (NPT * NPT)] = r[m];
-        __builtin_amdgcn_wave_barrier();                         // the next variable's gather overwrites the array
+        __builtin_amdgcn_wave_barrier();                         // the next variable's x pass overwrites the array
     }
 }
 
@@ -554,19 +581,12 @@ hipError_t launch_virtual(const DeviceTree& t, int nvar, const double* zipped, d
     return hipGetLastError();
 }
 
-hipError_t launch_virtual_centred(const DeviceTree& t, const int64_t* vlevel_start, int nvar, const double* zipped, double* virt,
-                                   hipStream_t s)
+hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* zipped, double* virt, hipStream_t s)
 {
     if (t.n_virt <= 0 || nvar <= 0) return hipSuccess;
-    for (int l = 0; l < 20; ++l) {                   // coarsest level first: a level's virtual blocks read those of the level before
-        const int64_t n = vlevel_start[l + 1] - vlevel_start[l];
-        if (n <= 0) continue;
-        hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks(n)), dim3(NTHREADS), 0, s, t, t.vlist + vlevel_start[l], n, nvar,
-                           zipped, virt);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    const int per = 8 / (nvar < 8 ? nvar : 8);       // virtual blocks per workgroup, as in the kernel
+    hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+    return hipGetLastError();
 }
 
 hipError_t launch_zip(const DeviceTree& t, int nvar, const double* padded, double* zipped, hipStream_t s)

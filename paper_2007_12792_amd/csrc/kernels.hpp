@@ -11,10 +11,9 @@ namespace octfd {
 struct DeviceTree {
     const ot_leaf* leaves;   // [nb]
     int64_t nb;
-    // virtual blocks (see HostTree): the ghost table that names them, what each is, and their order by level
+    // virtual blocks (see HostTree): the ghost table that names them and what each is
     const int32_t* ghost_v;  // [nb][27][5]
     const int32_t* vblk;     // [n_virt][2] {source leaf, child octant} of every virtual block
-    const int32_t* vlist;    // [n_virt] virtual blocks sorted by level
     int64_t n_virt;
     // the 24-field system on zipped input: the work units of the two-block kernel (see HostTree::units)
     const int32_t* units;
@@ -56,9 +55,8 @@ hipError_t launch_unzip(const DeviceTree& t, int nvar, const double* zipped, con
 // fills the virtual blocks of a zipped array: virt [nvar][n_virt][512], each the child octant of its source leaf,
 // every point interpolated inside that leaf exactly as a ghost point is in unzip ...
 hipError_t launch_virtual(const DeviceTree& t, int nvar, const double* zipped, double* virt, hipStream_t s);
-// ... or in unzip_centred (level by level; vlevel_start[21] as in HostTree)
-hipError_t launch_virtual_centred(const DeviceTree& t, const int64_t* vlevel_start, int nvar, const double* zipped, double* virt,
-                                   hipStream_t s);
+// ... or in unzip_centred
+hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* zipped, double* virt, hipStream_t s);
 hipError_t launch_zip(const DeviceTree& t, int nvar, const double* padded, double* zipped, hipStream_t s);
 // the 24-field right-hand side over the units of the tree (pair.hip): zipped input with its virtual blocks,
 // epilogue kOutZipped or one of the Runge-Kutta stages

@@ -25,8 +25,7 @@ struct HostTree {
     //   ghost_v [nb][27][5]        the ghost table with every coarser entry replaced by {kVirtual, virtual block}
     //   n_virt                     number of virtual blocks
     //   vlist   [n_virt]           virtual blocks sorted by level (the level of a virtual block is its source leaf's
-    //                              plus one): level l occupies vlist[vlevel_start[l] .. vlevel_start[l+1]).  With the
-    //                              centred ghost rule a level's virtual blocks read those of the level before.
+    //                              plus one): level l occupies vlist[vlevel_start[l] .. vlevel_start[l+1])
     //   vneed   [n_virt]           which y rows (bits 0..7) and z planes (bits 8..15) of a virtual block any block reads: the
     //                              union, per axis, over the blocks that have it as a neighbour.  The fill writes only
     //                              those (whole x rows of them); the rest of a virtual block is never read.
