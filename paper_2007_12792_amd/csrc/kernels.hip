@@ -1,12 +1,10 @@
 // gfx950 kernels of liboctfd.
 //
-// One workgroup of 512 threads (8 wavefronts) owns one block and one thread owns one of its 8^3
-// points.  A ghost-padded 14^3 tile of ONE variable lives in LDS; variables are streamed through it.
-// The tile is filled either from a padded array (plain copy) or straight from zipped storage
-// through the ghost-source table (copy, injection, separable Lagrange interpolation staged in
-// LDS): `unzip` writes that tile out, the fused right-hand-side kernels consume it in place and
-// never materialise the padded array.  Where each of a thread's tile entries comes from is worked
-// out once per block (the "fill plan") and reused for every variable.
+// A workgroup owns one block.  The kinds with one or two variables read it in slabs of two planes, one per wavefront
+// (slab.hpp); the 24-field system has one thread per point and a ghost-padded 14^3 tile of ONE variable in LDS through
+// which the variables are streamed (here from a padded array; on zipped input see pair.hip).  The fused kernels take ghost
+// values straight from zipped storage through the ghost-source table and never materialise the padded array; where each
+// value comes from is worked out once per block and reused for every variable.
 //
 // Mixed second derivatives D1_a(D1_b u) are not evaluated as 36-tap stencils: every thread
 // publishes its own D1_y u and D1_z u in LDS, the 3-deep ghost positions are filled in
@@ -15,6 +13,7 @@
 // Arithmetic follows one fixed IEEE sequence per formula (see octfd.h); the file is compiled with
 // -ffp-contract=off, so a fused multiply-add happens exactly where fma() is written.
 #include "fill.hpp"
+#include "slab.hpp"
 #include "stencils.hpp"
 #include "syn24.hpp"
 #include "tile.hpp"
@@ -26,197 +25,158 @@ namespace {
 
 // ---------------------------------------------------------------- right-hand-side kernel
 
-// LDS of the right-hand-side kernels (in doubles / words)
-template <int KIND>
-struct RhsLds {
-    static constexpr int NBUF = KIND == OT_RHS_SYN24 ? 2 : 1;
-    // the 24-field system keeps D1_z u and D1_y u of the variable in hand here (mixed derivatives)
-    static constexpr int NW = KIND == OT_RHS_SYN24 ? WZ + WY : 1;
-    // second derivatives (SYN24 only) read the edge slabs of the tile too
-    static constexpr int NPLAN = KIND == OT_RHS_SYN24 ? PLAN_EDGE : PLAN_FACE;
-    static constexpr int NPOINTS = KIND == OT_RHS_SYN24 ? NEDGE : NFACE;
-    static constexpr bool PLAN_IN_REGS = KIND != OT_RHS_SYN24;
-    static constexpr int NPLAN_SRC = PLAN_IN_REGS ? 1 : NPLAN * NTHREADS;
+// The 24-field system on padded input: one block per workgroup of 512 threads, one thread per point, the variables
+// streamed through a double-buffered tile.  (On zipped input it runs k_rhs_pair instead.)
+struct Syn24Lds {
+    double tiles[2 * TILE];
+    double wyz[WZ + WY];                             // D1_z u and D1_y u of the variable in hand (mixed derivatives)
+    uint32_t plan_src[PLAN_EDGE * NTHREADS];
 };
-
-// The right-hand side (and Runge-Kutta stage update) of whole blocks, one block per workgroup, all its variables.
-// Zipped input (ZIN): the tile is filled through the ghost table in which coarser neighbours appear as virtual
-// blocks, which k_virtual or k_virtual_centred has filled before the launch, so every tile entry is a copy or an
-// injection and no interpolation happens here; the two ghost rules differ only in which of the two kernels ran.
-// (The 24-field system on zipped input runs k_rhs_pair instead.)
-template <int KIND, bool ZIN, int EPI>
-__global__ __launch_bounds__(NTHREADS, waves_per_simd(KIND)) void k_rhs(DeviceTree tr, RhsArgs a)
+template <int EPI>
+__device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const RhsArgs& a, Syn24Lds& lds, int64_t b, int tid)
 {
-    using L = RhsLds<KIND>;
-    __shared__ double tiles[L::NBUF * TILE];
-    __shared__ double wyz[L::NW];
-    __shared__ BlockInfo bi;
-    __shared__ uint32_t plan_src[L::NPLAN_SRC];
-    constexpr int NPLAN = L::NPLAN, NPOINTS = L::NPOINTS;
-    constexpr bool PLAN_IN_REGS = L::PLAN_IN_REGS;
-
-    const int64_t b = block_of_workgroup(blockIdx.x);
-    if (b >= tr.nb) return;                          // uniform over the workgroup, like everything below
-
-    const int tid = threadIdx.x;
     const int64_t nb = tr.nb;
-    load_block_info(bi, tr, b, tid);
-    __syncthreads();
-
+    double* const tiles = lds.tiles;
+    double* const wyz = lds.wyz;
     int i, j, k;
     point_of(tid, i, j, k);
     const int c = tidx(k + PAD, j + PAD, i + PAD);
     // byte offsets of this thread's point inside one variable's zipped array / inside a padded block
     const uint32_t o8 = ((uint32_t)b * BLK + (k * NPT + j) * NPT + i) * 8u;
     const uint32_t p8 = (((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)) * 8u;
-    // 1/h = 2^(l+3) and 1/h^2, built from the level as bit patterns in scalar registers (the level is the same
-    // for the whole workgroup, which the compiler cannot see through the LDS copy)
-    const int lvl = __builtin_amdgcn_readfirstlane((int)bi.level);
+    // 1/h = 2^(l+3) and 1/h^2, built from the level as bit patterns in scalar registers
+    const int lvl = tr.leaves[b].level;
     const double ih = __longlong_as_double((long long)(1026 + lvl) << 52), ih2 = __longlong_as_double((long long)(1029 + 2 * lvl) << 52);
     const double sigma = a.sigma;
 
-    FillPlan<NPLAN, PLAN_IN_REGS> fp;
-    fp.src = plan_src;
-    if (ZIN) make_plan_zipped<NPLAN, NPOINTS>(fp, bi, tid);
-    else make_plan_padded<NPLAN, NPOINTS>(fp, tid);
-    double pv[NPLAN];
+    FillPlan<PLAN_EDGE> fp;
+    fp.src = lds.plan_src;
+    make_plan_padded<PLAN_EDGE, NEDGE>(fp, tid);
+    double pv[PLAN_EDGE];
 
-    auto var_base = [&](int v) -> const double* {
-        return ZIN ? a.in + (int64_t)v * nb * BLK : a.in + ((int64_t)v * nb + b) * PBLK;
+    auto var_base = [&](int v) -> const double* { return a.in + ((int64_t)v * nb + b) * PBLK; };
+    auto centre = [&](int v) -> double { return ldg(var_base(v), p8); };   // this thread's own value of variable v
+
+    // SYN24.  The variables are streamed in descending cyclic order (see syn24_stream).  The
+    // first ten real passes (variables 9..0) evaluate the second-derivative combinations Lap_s;
+    // each thread parks them at its own point in variables 10+s of the `stash` array, from where
+    // the later passes (variables 23..10, which need Lap_{a mod 10}) read them back before those
+    // slots receive their final values.  Per-thread state thus shrinks to one gradient.
+    //
+    // The tile is double-buffered and global memory is requested ahead of its use: tile data
+    // of the next variable is loaded into registers at the top of a pass and stored to the
+    // other LDS buffer at its end (one barrier per pass, plus the one inside mixed_derivs); the
+    // pointwise operands of the next pass (RK accumulator and state, u_{a+11}, Lap) likewise.
+    double* wz = wyz;
+    double* wy = wyz + WZ;
+    const double halpha = 0.5 * centre(0), bx = centre(1), by = centre(2), bz = centre(3);
+    const double Gxx = 1.0 - 0.125 * centre(4), Gxy = -(0.125 * centre(5)), Gxz = -(0.125 * centre(6));
+    const double Gyy = 1.0 - 0.125 * centre(7), Gyz = -(0.125 * centre(8)), Gzz = 1.0 - 0.125 * centre(9);
+    double nx = 0, ny = 0, nz = 0;
+    const int ownz = k * PS + (j + PAD) * RS + (i + PAD), owny = k * YPS + j * RS + (i + PAD);
+    struct Look { double unext, lap; EpiOperands eo; };
+
+    auto stash_base = [&](int v) -> double* {   // where Lap_{v-10} is parked (v = 10..19)
+        return EPI == kOutPadded ? a.stash + ((int64_t)v * nb + b) * PBLK : a.stash + (int64_t)v * nb * BLK;
     };
-    auto virt_base = [&](int v) -> const double* {  // variable v's virtual blocks
-        return ZIN ? a.virt + (int64_t)v * tr.n_virt * BLK : nullptr;
+    const uint32_t s8 = EPI == kOutPadded ? p8 : o8;
+
+    // top of pass t: request the tile data of pass t+1 and this pass's own pointwise operands.
+    // NEXT_USE says how much of the tile pass t+1 reads (edges only if it takes second derivatives).
+    auto issue = [&](int t, int f, Look& l, int& f1, auto next_use) {
+        constexpr int NEXT_USE = decltype(next_use)::value;
+        if (t + 1 < NSTREAM) {
+            f1 = syn24_stream(t + 1);
+            prefetch<PLAN_EDGE, NEXT_USE>(pv, fp, var_base(f1), tid);
+        }
+        l.unext = centre((f + 11) % 24);
+        l.eo = epi_prefetch<EPI>(a, nb, f, o8);
+        if (t > 10) l.lap = ldg(stash_base(10 + f % 10), s8);
     };
-    auto stage = [&](int v) {   // bring variable v into tile buffer 0 (barrier before and after)
-        __syncthreads();
-        prefetch<NPLAN, PLAN_FACE, ZIN>(pv, fp, var_base(v), tid, virt_base(v));
-        store_tile<NPLAN, PLAN_FACE>(tiles, fp, pv, tid);
+    using UseEdge = std::integral_constant<int, PLAN_EDGE>;
+    using UseFace = std::integral_constant<int, PLAN_FACE>;
+    // pass over a variable with second derivatives (9..0)
+    auto pass_d2 = [&](int t, auto next_use) {
+        constexpr int NEXT_USE = decltype(next_use)::value;
+        const double* T = tiles + (t & 1) * TILE;
+        const int f = syn24_stream(t);
+        int f1 = 0;
+        Look l{0.0, 0.0, {0.0, 0.0}};
+        issue(t, f, l, f1, next_use);
+        const Syn24Part p = syn24_axes<true>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
+        const Mixed mx = mixed_derivs(T, wy, wz, tid, owny, ownz, ih);
+        double off = Gxy * mx.dxy;
+        off = fma(Gxz, mx.dxz, off);
+        off = fma(Gyz, mx.dyz, off);
+        const double lap = fma(2.0, off, p.diag);
+        stg(stash_base(10 + f), s8, lap);
+        emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, lap, halpha, l.unext), l.eo);
+        store_tile<PLAN_EDGE, NEXT_USE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
         __syncthreads();
     };
-    auto centre = [&](int v) -> double {   // this thread's own value of variable v
-        return ZIN ? ldg(a.in + (int64_t)v * nb * BLK, o8) : ldg(a.in + ((int64_t)v * nb + b) * PBLK, p8);
-    };
-
-    if (KIND == OT_RHS_DERIVS) {
-        stage(0);
-        const EpiOperands e0 = epi_prefetch<EPI>(a, nb, 0, o8), e1 = epi_prefetch<EPI>(a, nb, 1, o8);
-        const EpiOperands e2 = epi_prefetch<EPI>(a, nb, 2, o8), e3 = epi_prefetch<EPI>(a, nb, 3, o8);
-        const PointOps p = point_ops<true>(tiles, c, 0.0, ih, ih2);
-        emit<EPI>(a, nb, 0, b, o8, p8, p.dx, e0);
-        emit<EPI>(a, nb, 1, b, o8, p8, p.dy, e1);
-        emit<EPI>(a, nb, 2, b, o8, p8, p.dz, e2);
-        emit<EPI>(a, nb, 3, b, o8, p8, p.lap, e3);
-    } else if (KIND == OT_RHS_WAVE) {
-        stage(0);
-        prefetch<NPLAN, PLAN_FACE, ZIN>(pv, fp, var_base(1), tid, virt_base(1));   // pi is on its way while u is differentiated
-        const PointOps pu = point_ops<true>(tiles, c, sigma, ih, ih2);
-        // the operands of the stage update are requested only now: four more values live during the stencils
-        // above push the kernel over the 64 registers that let four workgroups share a compute unit, and a
-        // kernel that spills there loses a quarter of its speed (the fence keeps the scheduler from moving the
-        // loads back up)
-        __syncthreads();
-        store_tile<NPLAN, PLAN_FACE>(tiles, fp, pv, tid);
-        __builtin_amdgcn_sched_barrier(0);
-        const EpiOperands e0 = epi_prefetch<EPI, ZIN>(a, nb, 0, o8), e1 = epi_prefetch<EPI, ZIN>(a, nb, 1, o8);
-        __syncthreads();
-        const PointOps pp = point_ops<false>(tiles, c, sigma, ih, ih2);
-        emit<EPI>(a, nb, 0, b, o8, p8, pp.u0 + pu.ko, ZIN ? with_u<EPI>(e0, pu.u0) : e0);
-        emit<EPI>(a, nb, 1, b, o8, p8, pu.lap + pp.ko, ZIN ? with_u<EPI>(e1, pp.u0) : e1);
-    } else if (KIND == OT_RHS_BURGERS) {
-        stage(0);
-        const EpiOperands e0 = epi_prefetch<EPI, ZIN>(a, nb, 0, o8);
-        const PointOps p = point_ops<false>(tiles, c, sigma, ih, ih2);
-        const double flux = p.u0 * p.dx;
-        emit<EPI>(a, nb, 0, b, o8, p8, p.ko - flux, ZIN ? with_u<EPI>(e0, p.u0) : e0);
-    } else {
-        // SYN24.  The variables are streamed in descending cyclic order (see syn24_stream).  The
-        // first ten real passes (variables 9..0) evaluate the second-derivative combinations Lap_s;
-        // each thread parks them at its own point in variables 10+s of the `stash` array, from where
-        // the later passes (variables 23..10, which need Lap_{a mod 10}) read them back before those
-        // slots receive their final values.  Per-thread state thus shrinks to one gradient.
-        //
-        // The tile is double-buffered and global memory is requested ahead of its use: tile data
-        // of the next variable is loaded into registers at the top of a pass and stored to the
-        // other LDS buffer at its end (one barrier per pass, plus the one inside mixed_derivs); the
-        // pointwise operands of the next pass (RK accumulator and state, u_{a+11}, Lap) likewise.
-        double* wz = wyz;
-        double* wy = wyz + WZ;
-        const double halpha = 0.5 * centre(0), bx = centre(1), by = centre(2), bz = centre(3);
-        const double Gxx = 1.0 - 0.125 * centre(4), Gxy = -(0.125 * centre(5)), Gxz = -(0.125 * centre(6));
-        const double Gyy = 1.0 - 0.125 * centre(7), Gyz = -(0.125 * centre(8)), Gzz = 1.0 - 0.125 * centre(9);
-        double nx = 0, ny = 0, nz = 0;
-        const int ownz = k * PS + (j + PAD) * RS + (i + PAD), owny = k * YPS + j * RS + (i + PAD);
-        struct Look { double unext, lap; EpiOperands eo; };
-
-        auto stash_base = [&](int v) -> double* {   // where Lap_{v-10} is parked (v = 10..19)
-            return EPI == kOutPadded ? a.stash + ((int64_t)v * nb + b) * PBLK : a.stash + (int64_t)v * nb * BLK;
-        };
-        const uint32_t s8 = EPI == kOutPadded ? p8 : o8;
-
-        // top of pass t: request the tile data of pass t+1 and this pass's own pointwise operands.
-        // NEXT_USE says how much of the tile pass t+1 reads (edges only if it takes second derivatives).
-        auto issue = [&](int t, int f, Look& l, int& f1, auto next_use) {
-            constexpr int NEXT_USE = decltype(next_use)::value;
-            if (t + 1 < NSTREAM) {
-                f1 = syn24_stream(t + 1);
-                prefetch<NPLAN, NEXT_USE, ZIN>(pv, fp, var_base(f1), tid, virt_base(f1));
-            }
-            l.unext = centre((f + 11) % 24);
-            l.eo = epi_prefetch<EPI>(a, nb, f, o8);
-            if (t > 10) l.lap = ldg(stash_base(10 + f % 10), s8);
-        };
-        using UseEdge = std::integral_constant<int, PLAN_EDGE>;
-        using UseFace = std::integral_constant<int, PLAN_FACE>;
-        // pass over a variable with second derivatives (9..0)
-        auto pass_d2 = [&](int t, auto next_use) {
-            constexpr int NEXT_USE = decltype(next_use)::value;
-            const double* T = tiles + (t & 1) * TILE;
-            const int f = syn24_stream(t);
-            int f1 = 0;
-            Look l{0.0, 0.0, {0.0, 0.0}};
-            issue(t, f, l, f1, next_use);
-            const Syn24Part p = syn24_axes<true>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
-            const Mixed mx = mixed_derivs(T, wy, wz, tid, owny, ownz, ih);
-            double off = Gxy * mx.dxy;
-            off = fma(Gxz, mx.dxz, off);
-            off = fma(Gyz, mx.dyz, off);
-            const double lap = fma(2.0, off, p.diag);
-            stg(stash_base(10 + f), s8, lap);
-            emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, lap, halpha, l.unext), l.eo);
-            store_tile<NPLAN, NEXT_USE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
-            __syncthreads();
-        };
-        // pass over a variable without second derivatives (23..10)
-        auto pass_light = [&](int t) {
-            const double* T = tiles + (t & 1) * TILE;
-            const int f = syn24_stream(t);
-            int f1 = 0;
-            Look l{0.0, 0.0, {0.0, 0.0}};
-            issue(t, f, l, f1, UseFace{});
-            const Syn24Part p = syn24_axes<false>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
-            emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, l.lap, halpha, l.unext), l.eo);
-            if (t + 1 < NSTREAM) {
-                store_tile<NPLAN, PLAN_FACE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
-                __syncthreads();
-            }
-        };
-
-        {   // pass 0: gradient of variable 10 only
-            const int f = syn24_stream(0), f1 = syn24_stream(1);
-            prefetch<NPLAN, PLAN_FACE, ZIN>(pv, fp, var_base(f), tid, virt_base(f));
-            store_tile<NPLAN, PLAN_FACE>(tiles, fp, pv, tid);
-            __syncthreads();
-            prefetch<NPLAN, PLAN_EDGE, ZIN>(pv, fp, var_base(f1), tid, virt_base(f1));
-            nx = d1_at(tiles, c, 1, ih); ny = d1_at(tiles, c, RS, ih); nz = d1_at(tiles, c, PS, ih);
-            store_tile<NPLAN, PLAN_EDGE>(tiles + TILE, fp, pv, tid);
+    // pass over a variable without second derivatives (23..10)
+    auto pass_light = [&](int t) {
+        const double* T = tiles + (t & 1) * TILE;
+        const int f = syn24_stream(t);
+        int f1 = 0;
+        Look l{0.0, 0.0, {0.0, 0.0}};
+        issue(t, f, l, f1, UseFace{});
+        const Syn24Part p = syn24_axes<false>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
+        emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, l.lap, halpha, l.unext), l.eo);
+        if (t + 1 < NSTREAM) {
+            store_tile<PLAN_EDGE, PLAN_FACE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
             __syncthreads();
         }
-#pragma unroll 1
-        for (int t = 1; t < 10; ++t) pass_d2(t, UseEdge{});
-        pass_d2(10, UseFace{});
-#pragma unroll 1
-        for (int t = 11; t < NSTREAM; ++t) pass_light(t);
+    };
+
+    {   // pass 0: gradient of variable 10 only
+        const int f = syn24_stream(0), f1 = syn24_stream(1);
+        prefetch<PLAN_EDGE, PLAN_FACE>(pv, fp, var_base(f), tid);
+        store_tile<PLAN_EDGE, PLAN_FACE>(tiles, fp, pv, tid);
+        __syncthreads();
+        prefetch<PLAN_EDGE, PLAN_EDGE>(pv, fp, var_base(f1), tid);
+        nx = d1_at(tiles, c, 1, ih); ny = d1_at(tiles, c, RS, ih); nz = d1_at(tiles, c, PS, ih);
+        store_tile<PLAN_EDGE, PLAN_EDGE>(tiles + TILE, fp, pv, tid);
+        __syncthreads();
     }
+#pragma unroll 1
+    for (int t = 1; t < 10; ++t) pass_d2(t, UseEdge{});
+    pass_d2(10, UseFace{});
+#pragma unroll 1
+    for (int t = 11; t < NSTREAM; ++t) pass_light(t);
+}
+
+// The right-hand side (and Runge-Kutta stage update) of whole blocks, one block per workgroup, all its variables.
+// Zipped input (ZIN): the block's surroundings are read through the ghost table in which coarser neighbours appear as
+// virtual blocks, which k_virtual or k_virtual_centred has filled before the launch, so every value is a copy or an
+// injection and no interpolation happens here; the two ghost rules differ only in which of the two kernels ran.
+constexpr int rhs_threads(int kind) { return kind == OT_RHS_SYN24 ? NTHREADS : slab_wavefronts(kind) * 64; }
+template <int KIND, bool ZIN, int EPI>
+__global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs(DeviceTree tr, RhsArgs a)
+{
+    const int64_t b = block_of_workgroup(blockIdx.x);
+    if (b >= tr.nb) return;                          // uniform over the workgroup
+    if constexpr (KIND == OT_RHS_SYN24) {
+        __shared__ Syn24Lds lds;
+        rhs_syn24_padded<EPI>(tr, a, lds, b, threadIdx.x);
+    } else {
+        __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
+        __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
+        rhs_slab<KIND, ZIN, EPI, false>(tr, a, lds, lapS, b, threadIdx.x);
+    }
+}
+// The same on zipped input with non-temporal accesses to everything but the input (see streams()): what passes through once
+// does not push the input, whose ghost rows are read by several blocks, out of the L2 and the memory-side cache.
+constexpr int kStreamChunk = 64;   // blocks dealt to an XCD at a time: 1541 / 1521 / 1515 / 1509 / 1535 us for 8 / 16 / 32 / 64 / 128
+                                   // (step of the wave system on 47,783 blocks)
+template <int KIND, int EPI>
+__global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs_stream(DeviceTree tr, RhsArgs a)
+{
+    const int64_t b = block_of_workgroup<kStreamChunk>(blockIdx.x);
+    if (b >= tr.nb) return;
+    __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
+    __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
+    rhs_slab<KIND, true, EPI, true>(tr, a, lds, lapS, b, threadIdx.x);
 }
 
 // ---------------------------------------------------------------- unzip / zip kernels
@@ -528,13 +488,34 @@ __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double*
     zipped[q * BLK + tid] = padded[q * PBLK + ((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)];
 }
 
+// Non-temporal accesses pay where a step's four vectors (or an evaluation's input and output) do not stay in the 256 MB
+// memory-side cache from one launch to the next, and cost where they would have.  Measured, us without / with: steps of
+// the wave system 239 / 261 on 7,134 blocks (234 MB), 360 / 346 on 9,920 (325 MB), 1645 / 1501 on 47,783; steps of Burgers
+// 219 / 238 on 13,700 blocks (224 MB), 302 / 300 on 18,278 (299 MB), 403 / 374 on 23,801; evaluations of DERIVS 36 / 36 on
+// 7,134 blocks (146 MB), 76 / 62 on 13,700 (281 MB), of Burgers 61 / 59 on 23,801 (195 MB).
+constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 180ll << 20;
+template <int KIND, int EPI>
+bool streams(int64_t nb)
+{
+    const int64_t vector = nb * BLK * (int64_t)sizeof(double);
+    const ot_rhs_kind kind = static_cast<ot_rhs_kind>(KIND);
+    return EPI == kOutZipped ? (ot_rhs_nvar_in(kind) + ot_rhs_nvar_out(kind)) * vector > kStreamEvalBytes
+                             : 4 * ot_rhs_nvar_in(kind) * vector > kStreamStepBytes;
+}
+
 template <int KIND, bool ZIN, int EPI>
 hipError_t launch_one(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
     if constexpr (KIND == OT_RHS_SYN24 && ZIN) {
         return launch_rhs_pairs(t, static_cast<Epilogue>(EPI), a, s);
     } else {
-        hipLaunchKernelGGL((k_rhs<KIND, ZIN, EPI>), dim3(grid_for_blocks(t.nb)), dim3(NTHREADS), 0, s, t, a);
+        if constexpr (ZIN) {
+            if (streams<KIND, EPI>(t.nb)) {
+                hipLaunchKernelGGL((k_rhs_stream<KIND, EPI>), dim3(grid_for_blocks<kStreamChunk>(t.nb)), dim3(rhs_threads(KIND)), 0, s, t, a);
+                return hipGetLastError();
+            }
+        }
+        hipLaunchKernelGGL((k_rhs<KIND, ZIN, EPI>), dim3(grid_for_blocks(t.nb)), dim3(rhs_threads(KIND)), 0, s, t, a);
         return hipGetLastError();
     }
 }

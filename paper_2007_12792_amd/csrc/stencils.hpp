@@ -32,10 +32,8 @@ __device__ __forceinline__ double d1_at(const double* t, int c, int st, double i
 struct AxisOps { double d1, d2, ko; };
 
 template <bool WITH_D2>
-__device__ __forceinline__ AxisOps axis_ops(const double* t, int c, int st, double u0, double ih, double ih2)
+__device__ __forceinline__ AxisOps axis_ops_taps(double m3, double m2, double m1, double p1, double p2, double p3, double u0, double ih, double ih2)
 {
-    const double m3 = t[c - 3 * st], m2 = t[c - 2 * st], m1 = t[c - st];
-    const double p1 = t[c + st], p2 = t[c + 2 * st], p3 = t[c + 3 * st];
     AxisOps r;
     r.d1 = d1_taps(m3, m2, m1, p1, p2, p3, ih);
     const double s1 = p1 + m1, s2 = p2 + m2, s3 = p3 + m3;
@@ -53,31 +51,13 @@ __device__ __forceinline__ AxisOps axis_ops(const double* t, int c, int st, doub
     }
     return r;
 }
-
-struct PointOps { double u0, dx, dy, dz, lap, ko, dxx, dyy, dzz; };
-
-// The three axes are evaluated one after the other (the scheduling fences keep the compiler from
-// fetching all 19 taps up front): fewer values are live at once, which is what lets two workgroups
-// share a compute unit.
 template <bool WITH_D2>
-__device__ __forceinline__ PointOps point_ops(const double* t, int c, double sigma, double ih, double ih2)
+__device__ __forceinline__ AxisOps axis_ops(const double* t, int c, int st, double u0, double ih, double ih2)
 {
-    PointOps r;
-    r.u0 = t[c];
-    const AxisOps x = axis_ops<WITH_D2>(t, c, 1, r.u0, ih, ih2);
-    r.dx = x.d1; r.dxx = x.d2;
-    __builtin_amdgcn_sched_barrier(0);
-    const AxisOps y = axis_ops<WITH_D2>(t, c, RS, r.u0, ih, ih2);
-    r.dy = y.d1; r.dyy = y.d2;
-    const double kxy = x.ko + y.ko, lxy = x.d2 + y.d2;
-    __builtin_amdgcn_sched_barrier(0);
-    const AxisOps z = axis_ops<WITH_D2>(t, c, PS, r.u0, ih, ih2);
-    r.dz = z.d1; r.dzz = z.d2;
-    r.lap = lxy + z.d2;
-    r.ko = sigma * ((kxy + z.ko) * over64(ih));
-    __builtin_amdgcn_sched_barrier(0);
-    return r;
+    return axis_ops_taps<WITH_D2>(t[c - 3 * st], t[c - 2 * st], t[c - st], t[c + st], t[c + 2 * st], t[c + 3 * st], u0, ih, ih2);
 }
+
+struct PointOps { double u0, dx, dy, dz, lap, ko; };   // all operators at a point
 
 struct Mixed { double dxy, dxz, dyz; };
 
@@ -125,13 +105,13 @@ struct EpiOperands { double acc, u; };
 // U_FROM_TILE: in the first stage the input of the right-hand side is the state itself (the launcher checks it), so
 // the state at the thread's point is the centre of the variable's tile and is not loaded again: the kernel hands it
 // over with with_u() once it has it.
-template <int EPI, bool U_FROM_TILE = false>
+template <int EPI, bool U_FROM_TILE = false, bool NT = false>
 __device__ __forceinline__ EpiOperands epi_prefetch(const RhsArgs& a, int64_t nb, int w, uint32_t o8)
 {
     EpiOperands e{0.0, 0.0};
     const int64_t f = (int64_t)w * nb * BLK;
-    if ((EPI == kRkFirst && !U_FROM_TILE) || EPI == kRkMiddle || EPI == kRkLast) e.u = ldg(a.u + f, o8);
-    if (EPI == kRkMiddle || EPI == kRkLast) e.acc = ldg(a.acc + f, o8);
+    if ((EPI == kRkFirst && !U_FROM_TILE) || EPI == kRkMiddle || EPI == kRkLast) e.u = ldg<NT>(a.u + f, o8);
+    if (EPI == kRkMiddle || EPI == kRkLast) e.acc = ldg<NT>(a.acc + f, o8);
     return e;
 }
 template <int EPI>
@@ -141,25 +121,25 @@ __device__ __forceinline__ EpiOperands with_u(EpiOperands e, double centre)
     return e;
 }
 
-template <int EPI>
+template <int EPI, bool NT = false>
 __device__ __forceinline__ void emit(const RhsArgs& a, int64_t nb, int w, int64_t b, uint32_t o8, uint32_t p8, double k,
                                      const EpiOperands& e)
 {
     if (EPI == kOutPadded) {
-        stg(a.out + ((int64_t)w * nb + b) * PBLK, p8, k);
+        stg<NT>(a.out + ((int64_t)w * nb + b) * PBLK, p8, k);
         return;
     }
     const int64_t f = (int64_t)w * nb * BLK;
     if (EPI == kOutZipped) {
-        stg(a.out + f, o8, k);
+        stg<NT>(a.out + f, o8, k);
     } else if (EPI == kRkFirst) {
-        stg(a.acc + f, o8, k);
-        stg(a.out + f, o8, fma(a.c, k, e.u));
+        stg<NT>(a.acc + f, o8, k);
+        stg<NT>(a.out + f, o8, fma(a.c, k, e.u));
     } else if (EPI == kRkMiddle) {
-        stg(a.acc + f, o8, e.acc + 2.0 * k);
-        stg(a.out + f, o8, fma(a.c, k, e.u));
+        stg<NT>(a.acc + f, o8, e.acc + 2.0 * k);
+        stg<NT>(a.out + f, o8, fma(a.c, k, e.u));
     } else {
-        stg(a.u + f, o8, fma(a.c, e.acc + k, e.u));
+        stg<NT>(a.u + f, o8, fma(a.c, e.acc + k, e.u));
     }
 }
 

@@ -10,7 +10,7 @@ namespace {
 
 constexpr int NPT = 8, PAD = 3, NP = 14, BLK = 512, PBLK = 2744;
 constexpr int NTHREADS = 512;
-constexpr int K_SAME = 0, K_VIRT = 3;   // kinds of a ghost-table entry that are plain copies (1: finer, injection)
+constexpr int K_SAME = 0, K_FINER = 1, K_VIRT = 3;   // kinds of a ghost-table entry: copy, injection, copy from a virtual block
 
 // LDS geometry (in doubles).  Rows are stored compactly (stride 14) and planes are padded to a
 // stride of 200 = 8 (mod 32).  A wavefront holds one j row of the block, its lanes run over
@@ -25,10 +25,6 @@ constexpr int TILE = NP * PS;            // 14 planes
 constexpr int WZ = NPT * PS;             // D1_z u on [8 k][14 jj][14 ii]
 constexpr int YPS = NPT * RS + 8;        // plane stride of the D1_y array, 120 = 24 (mod 32)
 constexpr int WY = NPT * YPS;            // D1_y u on [8 k][8 j][14 ii]
-struct BlockInfo {       // per-workgroup copy of the block's table row
-    int32_t gt[27 * 5];  // ghost table in which coarser neighbours appear as virtual blocks
-    uint32_t level;
-};
 
 __device__ __forceinline__ int tidx(int kk, int jj, int ii) { return kk * PS + jj * RS + ii; }
 
@@ -57,28 +53,40 @@ __device__ __forceinline__ void stg(double* base, uint32_t byte_off, double v)
     *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + byte_off) = v;
 }
 
+// NT: as non-temporal accesses, for data that would leave the caches before it is read again.
+template <bool NT>
+__device__ __forceinline__ double ldg(const double* base, uint32_t byte_off)
+{
+    if (!NT) return ldg(base, byte_off);
+    asm volatile("" : "+v"(byte_off));
+    return __builtin_nontemporal_load(reinterpret_cast<const double*>(reinterpret_cast<const char*>(base) + byte_off));
+}
+template <bool NT>
+__device__ __forceinline__ void stg(double* base, uint32_t byte_off, double v)
+{
+    if (!NT) { stg(base, byte_off, v); return; }
+    asm volatile("" : "+v"(byte_off));
+    __builtin_nontemporal_store(v, reinterpret_cast<double*>(reinterpret_cast<char*>(base) + byte_off));
+}
+
 // Workgroups are handed to the eight XCDs (each with its own L2) round-robin by workgroup id.
 // Chunks of 16 Morton-consecutive blocks (two sibling octets) are dealt to the XCDs in turn: blocks
 // that run at the same time on one XCD are then close neighbours, which read each other's rows
 // through the same L2, while every XCD still sees the same mix of cheap and expensive blocks.
 // (Measured on the 102,075-block tree: 78.0 ms per step against 83.5 ms with one contiguous eighth
 // of the Morton order per XCD and 78.4 ms with no remapping.)
-constexpr int NXCD = kSchedXcds, XCD_CHUNK = kSchedChunk;
+constexpr int NXCD = kSchedXcds;
+template <int XCD_CHUNK = kSchedChunk>
 __device__ __forceinline__ int64_t block_of_workgroup(int64_t wg)
 {
     const int64_t x = wg % NXCD, q = wg / NXCD;
     return (q / XCD_CHUNK) * (XCD_CHUNK * NXCD) + x * XCD_CHUNK + (q % XCD_CHUNK);   // may be >= nb: caller checks
 }
+template <int XCD_CHUNK = kSchedChunk>
 inline unsigned grid_for_blocks(int64_t nb)
 {
     const int64_t span = XCD_CHUNK * NXCD;
     return (unsigned)((nb + span - 1) / span * span);
-}
-
-__device__ __forceinline__ void load_block_info(BlockInfo& bi, const DeviceTree& tr, int64_t b, int tid)
-{
-    if (tid < 27 * 5) bi.gt[tid] = tr.ghost_v[b * (27 * 5) + tid];
-    if (tid == 320) bi.level = tr.leaves[b].level;
 }
 
 // ---------------------------------------------------------------- fill plan
@@ -129,17 +137,12 @@ __device__ __forceinline__ void tile_point(int p, int& ii, int& jj, int& kk)
 // Entries with nothing to copy (beyond the range in use, or interpolated later) read element 0 and
 // write to DUMMY, a padding slot of the tile that no stencil reads; the copy loop is branch-free.
 constexpr int DUMMY = NP * RS;   // first padding slot behind plane 0
-// src: byte offset in the source array.  It is needed once per variable: the 24-field kernel, short of
-// registers, keeps it in LDS as src[m * NTHREADS + tid]; with REG the entries are registers (the other
-// kinds: 8 KB less LDS, which lets a fourth workgroup onto the compute unit).
+// src: byte offset in the source array, needed once per variable and kept in LDS as src[m * NTHREADS + tid];
 // dst: tile index, two 16-bit values per register.
-template <int NPLAN, bool REG = false>
+template <int NPLAN>
 struct FillPlan {
     uint32_t* src;
-    uint32_t srcr[REG ? NPLAN : 1];
     uint32_t dstp[(NPLAN + 1) / 2];
-    __device__ __forceinline__ uint32_t get_src(int m, int tid) const { return REG ? srcr[m] : src[m * NTHREADS + tid]; }
-    __device__ __forceinline__ void set_src(int m, int tid, uint32_t v) { if (REG) srcr[m] = v; else src[m * NTHREADS + tid] = v; }
     __device__ __forceinline__ int dst(int m) const { return (dstp[m >> 1] >> (16 * (m & 1))) & 0xffff; }
     __device__ __forceinline__ void set_dst(int m, int v) { dstp[m >> 1] = (m & 1) ? (dstp[m >> 1] | ((uint32_t)v << 16)) : (uint32_t)v; }
 };
@@ -168,37 +171,10 @@ __device__ __forceinline__ uint32_t ghost_source(const int32_t* e, int rx, int r
     return elem * 8u | (kind == K_VIRT ? 1u : 0u);
 }
 
-// Source of every padded point this thread fills, as a byte offset into one variable's zipped
-// array (same-level copy or injection from a finer leaf) or, for a point inside a virtual block, into
-// one variable's part of the array of virtual blocks, marked by bit 0 (offsets are multiples of 8).
+// Source of every padded point this thread fills, as a byte offset into the block's padded data.
 // NPOINTS = how long a prefix of the enumeration is planned.
-template <int NPLAN, int NPOINTS, bool REG>
-__device__ __forceinline__ void make_plan_zipped(FillPlan<NPLAN, REG>& fp, const BlockInfo& bi, int tid)
-{
-#pragma unroll
-    for (int m = 0; m < NPLAN; ++m) {
-        const int p = tid + m * NTHREADS;
-        uint32_t src = 0;
-        int dst = DUMMY;
-        if (p < NPOINTS) {
-            int ii, jj, kk;
-            tile_point(p, ii, jj, kk);
-            const int rx = ii < PAD ? 0 : (ii < PAD + NPT ? 1 : 2);
-            const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2);
-            const int rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
-            // coordinates inside the neighbouring octant of the same level, 0..7
-            const int lx = ii - PAD + (1 - rx) * NPT, ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
-            dst = tidx(kk, jj, ii);
-            src = ghost_source(&bi.gt[(rz * 9 + ry * 3 + rx) * 5], rx, ry, rz, lx, ly, lz);
-        }
-        fp.set_src(m, tid, src);
-        fp.set_dst(m, dst);
-    }
-}
-
-// same for a padded source block (plain copy)
-template <int NPLAN, int NPOINTS, bool REG>
-__device__ __forceinline__ void make_plan_padded(FillPlan<NPLAN, REG>& fp, int tid)
+template <int NPLAN, int NPOINTS>
+__device__ __forceinline__ void make_plan_padded(FillPlan<NPLAN>& fp, int tid)
 {
 #pragma unroll
     for (int m = 0; m < NPLAN; ++m) {
@@ -206,7 +182,7 @@ __device__ __forceinline__ void make_plan_padded(FillPlan<NPLAN, REG>& fp, int t
         const bool ok = p < NPOINTS;
         int ii, jj, kk;
         tile_point(ok ? p : 0, ii, jj, kk);
-        fp.set_src(m, tid, ok ? (uint32_t)((kk * NP + jj) * NP + ii) * 8u : 0u);
+        fp.src[m * NTHREADS + tid] = ok ? (uint32_t)((kk * NP + jj) * NP + ii) * 8u : 0u;
         fp.set_dst(m, ok ? tidx(kk, jj, ii) : DUMMY);
     }
 }
