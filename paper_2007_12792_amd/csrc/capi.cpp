@@ -89,7 +89,7 @@ int ensure_device(const ot_tree* t)
     // one allocation for all tables, each part 256-byte aligned
     const HostTree& h = t->host;
     constexpr int kParts = 5;
-    auto ibytes = [](const std::vector<int32_t>& v) { return v.size() * sizeof(int32_t); };
+    auto ibytes = [](const auto& v) { return v.size() * sizeof(int32_t); };
     const void* part[kParts] = {h.leaves.data(), h.ghost_v.data(), h.vblk.data(), h.units.data(), h.vneed.data()};
     const size_t bytes[kParts] = {h.leaves.size() * sizeof(ot_leaf), ibytes(h.ghost_v), ibytes(h.vblk), ibytes(h.units), ibytes(h.vneed)};
     size_t off[kParts + 1] = {0};

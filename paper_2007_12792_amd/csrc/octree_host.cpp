@@ -1,8 +1,14 @@
 // Host octree engine: refinement, 26-neighbour periodic 2:1 balance, Morton ordering and the
 // ghost-source table (see octfd.h, octree_build).  The tree is an explicit pointer octree; the
 // eight children of a node are stored contiguously in Morton child order c = (cz<<2)|(cy<<1)|cx,
-// so a depth-first walk visits the leaves in storage order and neighbours are found by descending
-// from the root.
+// so a depth-first walk visits the leaves in storage order.
+//
+// Both the balance and the tables rest on one property: the leaves are 2:1 balanced exactly if all 26 neighbour octants of
+// every node that has children exist as nodes.  (A leaf with a neighbour two levels coarser has a parent with a neighbour
+// octant inside that leaf; the other way round, follow the children on the side of the missing octant down to a leaf.)  So
+// only the nodes with children, an eighth of all, are looked at, and the neighbours of a child are children of its
+// parent's neighbours, found without a descent from the root.  (Tree of 27,756 blocks with its tables, these in huge
+// pages: 23 -> 4.8 ms; 26 descents from the root per leaf for the balance and 27 for its table row took most of it.)
 #include "octree_host.hpp"
 
 #include "kernels.hpp"
@@ -80,30 +86,22 @@ bool near_seed(const Node& o, const ot_build_params& p)
     return false;
 }
 
-// Every leaf on the queue makes sure that none of its 26 neighbours is more than one level
-// coarser.  Splitting a leaf can only create new obligations for its own children, so they are
-// queued; leaves that were already checked stay valid because neighbours only ever get finer.
-void balance(Octree& t, std::deque<int32_t>& queue)
+// Splits leaves until every node with children has its 26 neighbour octants, finest level first: what a node at level l
+// asks for is split at coarser levels only.  inner[l]: the nodes of level l that have children.
+void balance(Octree& t, std::vector<int32_t> (&inner)[21])
 {
-    while (!queue.empty()) {
-        const int32_t n = queue.front();
-        queue.pop_front();
-        if (t.nodes[n].first_child != kLeaf) continue;
-        const Node o = t.nodes[n];
-        if (o.level < 2) continue;
-        const uint32_t mask = (1u << o.level) - 1;
-        for (int dz = -1; dz <= 1; ++dz)
-            for (int dy = -1; dy <= 1; ++dy)
-                for (int dx = -1; dx <= 1; ++dx) {
-                    if (!dx && !dy && !dz) continue;
-                    const uint32_t x = (o.ix + dx) & mask, y = (o.iy + dy) & mask, z = (o.iz + dz) & mask;
-                    for (;;) {
-                        const int32_t m = t.descend(o.level, x, y, z);
-                        if (t.nodes[m].first_child != kLeaf || t.nodes[m].level + 1 >= o.level) break;
-                        const int32_t first = t.split(m);
-                        for (int c = 0; c < 8; ++c) queue.push_back(first + c);
-                    }
+    for (int l = 20; l >= 1; --l) {
+        const uint32_t mask = (1u << l) - 1;
+        for (size_t q = 0; q < inner[l].size(); ++q) {
+            const Node o = t.nodes[inner[l][q]];
+            for (int dir = 0; dir < kDirs; ++dir) {
+                const uint32_t x = (o.ix + (dir % 3 - 1)) & mask, y = (o.iy + ((dir / 3) % 3 - 1)) & mask, z = (o.iz + (dir / 9 - 1)) & mask;
+                for (int32_t m = t.descend(o.level, x, y, z); t.nodes[m].level < o.level; m = t.descend(o.level, x, y, z)) {
+                    t.split(m);
+                    inner[t.nodes[m].level].push_back(m);
                 }
+            }
+        }
     }
 }
 
@@ -119,101 +117,149 @@ void emit_leaves(Octree& t, int32_t n, std::vector<ot_leaf>& out)
     for (int c = 0; c < 8; ++c) emit_leaves(t, first + c, out);
 }
 
-// Ghost-source table.  Returns OT_OK or OT_E_UNBALANCED.
-int make_ghost_table(const Octree& t, const std::vector<ot_leaf>& leaves, std::vector<int32_t>& ghost)
-{
-    const size_t nb = leaves.size();
-    ghost.assign(nb * kDirs * kEntry, -1);
-    for (size_t b = 0; b < nb; ++b) {
-        const ot_leaf& o = leaves[b];
-        const uint32_t mask = (1u << o.level) - 1;
+// For child c = (cz<<2)|(cy<<1)|cx of a node and direction dir: which neighbour of the node holds the child's neighbour
+// octant, and as which of its children.
+struct ChildStep { int8_t parent_dir, slot; };
+struct ChildSteps {
+    ChildStep at[8][kDirs];
+    ChildSteps()
+    {
+        for (int c = 0; c < 8; ++c)
+            for (int dir = 0; dir < kDirs; ++dir) {
+                const int x = (c & 1) + dir % 3 - 1, y = ((c >> 1) & 1) + (dir / 3) % 3 - 1, z = (c >> 2) + dir / 9 - 1;   // -1 .. 2
+                auto up = [](int p) { return p < 0 ? 0 : (p < 2 ? 1 : 2); };
+                at[c][dir] = {static_cast<int8_t>(up(z) * 9 + up(y) * 3 + up(x)), static_cast<int8_t>(((z & 1) << 2) | ((y & 1) << 1) | (x & 1))};
+            }
+    }
+};
+
+// The children of an octant that touch the block on its side -dir: along an axis with d = -1 they are the upper
+// children, with d = +1 the lower ones; axes with d = 0 are free and enumerated x, then y, then z (ascending Morton order).
+struct TouchingChildren {
+    int8_t count[kDirs], slot[kDirs][8];
+    TouchingChildren()
+    {
         for (int dir = 0; dir < kDirs; ++dir) {
             const int d[3] = {dir % 3 - 1, (dir / 3) % 3 - 1, dir / 9 - 1};
-            int32_t* e = &ghost[(b * kDirs + dir) * kEntry];
-            const uint32_t x = (o.ix + d[0]) & mask, y = (o.iy + d[1]) & mask, z = (o.iz + d[2]) & mask;
-            const int32_t m = t.descend(o.level, x, y, z);
-            const Node& nd = t.nodes[m];
-            if (nd.first_child == kLeaf) {
-                if (nd.level == o.level) e[0] = kSame;
-                else if (nd.level + 1 == o.level) e[0] = kCoarser;
-                else return OT_E_UNBALANCED;
-                e[1] = nd.leaf_id;
+            int n = 0;
+            for (int c = 0; c < 8; ++c) {
+                bool touches = true;
+                for (int ax = 0; ax < 3; ++ax)
+                    if (d[ax] && ((c >> ax) & 1) != (d[ax] < 0 ? 1 : 0)) touches = false;
+                if (touches) slot[dir][n++] = static_cast<int8_t>(c);
+            }
+            count[dir] = static_cast<int8_t>(n);
+        }
+    }
+};
+
+// The ghost table and what is derived from it: virtual blocks, by level, and which parts of them are read.  The leaves have
+// their ids.  Returns OT_OK or OT_E_UNBALANCED.
+int make_tables(const Octree& t, HostTree& out)
+{
+    static const ChildSteps steps;
+    static const TouchingChildren touching;
+    const size_t nb = out.leaves.size();
+    // neighbours of every node with children (the node itself in the middle), in the order of the nodes: parents come first
+    std::vector<int32_t> rank(t.nodes.size(), -1), nbr;
+    int32_t n_inner = 0;
+    for (size_t n = 0; n < t.nodes.size(); ++n)
+        if (t.nodes[n].first_child >= 0) rank[n] = n_inner++;
+    nbr.assign(static_cast<size_t>(n_inner) * kDirs, 0);             // the root's neighbours are the root
+    std::vector<int32_t> parent_of_leaf(nb, 0);                      // 8 * node + child
+    for (size_t n = 0; n < t.nodes.size(); ++n) {
+        if (t.nodes[n].first_child < 0) continue;
+        const int32_t* at = &nbr[static_cast<size_t>(rank[n]) * kDirs];
+        for (int c = 0; c < 8; ++c) {
+            const int32_t ch = t.nodes[n].first_child + c;
+            if (t.nodes[ch].first_child < 0) {
+                parent_of_leaf[t.nodes[ch].leaf_id] = static_cast<int32_t>(8 * rank[n] + c);
                 continue;
             }
-            // the neighbouring octant is subdivided: take the children that touch this block.
-            // Along an axis with d = -1 they are the upper children, with d = +1 the lower ones;
-            // axes with d = 0 are free and enumerated x, then y, then z (ascending Morton order).
-            e[0] = kFiner;
-            int nfree = 0, free_axis[3];
-            for (int ax = 0; ax < 3; ++ax) if (d[ax] == 0) free_axis[nfree++] = ax;
-            for (int q = 0; q < (1 << nfree); ++q) {
-                int bit[3];
-                for (int ax = 0; ax < 3; ++ax) bit[ax] = d[ax] < 0 ? 1 : 0;
-                for (int f = 0; f < nfree; ++f) bit[free_axis[f]] = (q >> f) & 1;
-                const Node& ch = t.nodes[nd.first_child + ((bit[2] << 2) | (bit[1] << 1) | bit[0])];
-                if (ch.first_child != kLeaf) return OT_E_UNBALANCED;
-                e[1 + q] = ch.leaf_id;
+            int32_t* to = &nbr[static_cast<size_t>(rank[ch]) * kDirs];
+            for (int dir = 0; dir < kDirs; ++dir) {
+                const ChildStep s = steps.at[c][dir];
+                const int32_t first = t.nodes[at[s.parent_dir]].first_child;
+                if (first < 0) return OT_E_UNBALANCED;
+                to[dir] = first + s.slot;
             }
         }
     }
-    return OT_OK;
-}
-
-}  // namespace
-
-void make_virtual_blocks(HostTree& t)
-{
-    const size_t nb = t.leaves.size();
-    // which child octant of its parent the neighbour octant in direction dir is: the low bit of its anchor
-    auto octant_of = [&](size_t b, int dir) {
-        const ot_leaf& o = t.leaves[b];
-        const uint32_t x = o.ix + (dir % 3 - 1), y = o.iy + ((dir / 3) % 3 - 1), z = o.iz + (dir / 9 - 1);   // mod 2^l keeps the low bit
-        return static_cast<int>((x & 1) | ((y & 1) << 1) | ((z & 1) << 2));
-    };
-    // per leaf: which of its child octants some block needs
+    // rows of the ghost table.  A neighbour octant under a leaf is that leaf's child octant: noted in `mask` (per leaf, which
+    // of its child octants some block needs) and `coarser` (index of the entry, octant).
     std::vector<uint8_t> mask(nb, 0);
-    for (size_t b = 0; b < nb; ++b)
+    struct Coarser { size_t entry; int32_t octant, dir; };
+    std::vector<Coarser> coarser;
+    out.ghost.clear();
+    out.ghost.reserve(nb * kDirs * kEntry);
+    for (size_t b = 0; b < nb; ++b) {
+        const int c = parent_of_leaf[b] & 7;
+        const int32_t* at = &nbr[static_cast<size_t>(parent_of_leaf[b] >> 3) * kDirs];
+        int32_t row[kDirs * kEntry];
         for (int dir = 0; dir < kDirs; ++dir) {
-            const int32_t* e = &t.ghost[(b * kDirs + dir) * kEntry];
-            if (e[0] == kCoarser) mask[e[1]] |= static_cast<uint8_t>(1 << octant_of(b, dir));
+            const ChildStep s = steps.at[c][dir];
+            const Node& above = t.nodes[at[s.parent_dir]];
+            int32_t* e = row + dir * kEntry;
+            e[1] = e[2] = e[3] = e[4] = -1;
+            if (above.first_child < 0) {
+                e[0] = kCoarser;
+                e[1] = above.leaf_id;
+                mask[above.leaf_id] |= static_cast<uint8_t>(1 << s.slot);
+                coarser.push_back({(b * kDirs + dir) * kEntry, s.slot, dir});
+                continue;
+            }
+            const Node& nd = t.nodes[above.first_child + s.slot];
+            if (nd.first_child < 0) {
+                e[0] = kSame;
+                e[1] = nd.leaf_id;
+                continue;
+            }
+            e[0] = kFiner;
+            for (int q = 0; q < touching.count[dir]; ++q) {
+                const Node& ch = t.nodes[nd.first_child + touching.slot[dir][q]];
+                if (ch.first_child >= 0) return OT_E_UNBALANCED;
+                e[1 + q] = ch.leaf_id;
+            }
         }
-    // numbered by source leaf, then octant
+        out.ghost.insert(out.ghost.end(), row, row + kDirs * kEntry);
+    }
+    // virtual blocks, numbered by source leaf, then octant
     std::vector<int32_t> first(nb, 0);
-    t.vblk.clear();
+    out.vblk.clear();
     int32_t n = 0;
     for (size_t s = 0; s < nb; ++s) {
         first[s] = n;
         for (int c = 0; c < 8; ++c)
             if ((mask[s] >> c) & 1) {
-                t.vblk.push_back(static_cast<int32_t>(s));
-                t.vblk.push_back(c);
+                out.vblk.push_back(static_cast<int32_t>(s));
+                out.vblk.push_back(c);
                 ++n;
             }
     }
-    t.n_virt = n;
+    out.n_virt = n;
     // by level
     int64_t count[21] = {};
-    for (int32_t q = 0; q < n; ++q) ++count[t.leaves[t.vblk[2 * q]].level + 2];      // its own level + 1
+    for (int32_t q = 0; q < n; ++q) ++count[out.leaves[out.vblk[2 * q]].level + 2];  // its own level + 1
     for (int l = 1; l <= 20; ++l) count[l] += count[l - 1];
-    for (int l = 0; l <= 20; ++l) t.vlevel_start[l] = count[l];
-    t.vlist.assign(n, 0);
-    for (int32_t q = 0; q < n; ++q) t.vlist[count[t.leaves[t.vblk[2 * q]].level + 1]++] = q;
-    t.ghost_v = t.ghost;
-    t.vneed.assign(n, 0);
+    for (int l = 0; l <= 20; ++l) out.vlevel_start[l] = count[l];
+    out.vlist.assign(n, 0);
+    for (int32_t q = 0; q < n; ++q) out.vlist[count[out.leaves[out.vblk[2 * q]].level + 1]++] = q;
+    out.ghost_v = out.ghost;
+    out.vneed.assign(n, 0);
     // a block reads, of its neighbour in direction d, the three layers next to itself along every axis with d != 0
     // and all eight along the others
     auto layers = [](int d) { return d > 0 ? 0x07 : (d < 0 ? 0xE0 : 0xFF); };
-    for (size_t b = 0; b < nb; ++b)
-        for (int dir = 0; dir < kDirs; ++dir) {
-            int32_t* e = &t.ghost_v[(b * kDirs + dir) * kEntry];
-            if (e[0] != kCoarser) continue;
-            const int c = octant_of(b, dir);
-            const int32_t src = e[1];
-            e[0] = kVirtual;
-            e[1] = first[src] + __builtin_popcount(static_cast<unsigned>(mask[src]) & ((1u << c) - 1));
-            t.vneed[e[1]] |= layers((dir / 3) % 3 - 1) | layers(dir / 9 - 1) << 8;
-        }
+    for (const Coarser& e : coarser) {
+        int32_t* v = &out.ghost_v[e.entry];
+        const int32_t src = v[1];
+        v[0] = kVirtual;
+        v[1] = first[src] + __builtin_popcount(static_cast<unsigned>(mask[src]) & ((1u << e.octant) - 1));
+        out.vneed[v[1]] |= layers((e.dir / 3) % 3 - 1) | layers(e.dir / 9 - 1) << 8;
+    }
+    return OT_OK;
 }
+
+}  // namespace
 
 void make_units(HostTree& t)
 {
@@ -249,22 +295,23 @@ int build_tree(const ot_build_params& p, HostTree& out)
 
     Octree t;
     std::deque<int32_t> work{0};
-    std::deque<int32_t> leaves_to_balance;
+    std::vector<int32_t> inner[21];
     // uniform refinement to lmin, then seed-driven refinement; each node is visited once
     while (!work.empty()) {
         const int32_t n = work.front();
         work.pop_front();
         const Node o = t.nodes[n];
         const bool grow = o.level < p.lmin || (o.level < p.lmax && near_seed(o, p));
-        if (!grow) { leaves_to_balance.push_back(n); continue; }
+        if (!grow) continue;
+        inner[o.level].push_back(n);
         const int32_t first = t.split(n);
         for (int c = 0; c < 8; ++c) work.push_back(first + c);
     }
-    balance(t, leaves_to_balance);
+    balance(t, inner);
     out.leaves.clear();
     emit_leaves(t, 0, out.leaves);
-    const int rc = make_ghost_table(t, out.leaves, out.ghost);
-    if (rc == OT_OK) { make_virtual_blocks(out); make_units(out); }
+    const int rc = make_tables(t, out);
+    if (rc == OT_OK) make_units(out);
     return rc;
 }
 
@@ -290,8 +337,8 @@ int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
         if (nd.first_child == kUnset) return OT_E_INCOMPLETE;                // a gap
     out.leaves.clear();
     emit_leaves(t, 0, out.leaves);
-    const int rc = make_ghost_table(t, out.leaves, out.ghost);
-    if (rc == OT_OK) { make_virtual_blocks(out); make_units(out); }
+    const int rc = make_tables(t, out);
+    if (rc == OT_OK) make_units(out);
     return rc;
 }
 
