@@ -266,7 +266,7 @@ int ot_rhs_nvar_out(ot_rhs_kind kind)
 static int unzip_any(const ot_tree* tree, bool centred, int nvar, const double* zipped_dev, double* padded_dev, void* hip_stream)
 {
     if (!tree || nvar <= 0 || !zipped_dev || !padded_dev || !aligned8(zipped_dev) || !aligned8(padded_dev)) return OT_E_BADARG;
-    if (int rc = ensure_device(tree)) return rc;   // < 2^20 blocks, and the grid is at most 8 workgroups per block
+    if (int rc = ensure_device(tree)) return rc;
     const size_t vbytes = static_cast<size_t>(nvar) * static_cast<size_t>(tree->host.n_virt) * 512 * sizeof(double);
     if (int rc = ensure_virtual_scratch(tree, vbytes)) return rc;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);

@@ -18,6 +18,7 @@
 #include "syn24.hpp"
 #include "tile.hpp"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace octfd {
@@ -183,63 +184,77 @@ __global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs
 
 // unzip as a gather.  With the virtual blocks of the input filled (by k_virtual for the clamped ghost rule, by
 // k_virtual_centred for the centred one), every one of the 2,744 points of a padded block is a copy: of the block's
-// own data, of a same-level or virtual neighbour, or of the coinciding node of a finer neighbour.  A thread owns up to
-// six consecutive-by-512 output positions of the padded block and keeps their sources in registers for all
-// variables; no LDS, no barrier, loads and stores of different variables overlap freely.  The stores are non-temporal:
-// the padded output (5.4 times the input) is not read again here and would otherwise push the ghost rows out of the L2
-// (23.8 -> 20.5 ms on the 102,075-block tree with 24 fields).
-// Workgroup r + G b takes variables r, r + G, r + 2G, ... of block b, G = min(8, nvar): with the workgroups dealt to
-// the eight XCDs in turn, an XCD sees a fixed subset of the variables for consecutive blocks one after the other, so a
-// ghost row it fetches was, or soon will be, an interior row of a block it handles for the same variable and is
-// served by its L2.
-__global__ __launch_bounds__(NTHREADS) void k_unzip(DeviceTree tr, int nvar, const double* __restrict__ zipped, const double* __restrict__ virt,
-                                                    double* __restrict__ padded)
+// own data, of a same-level or virtual neighbour, or of the coinciding node of a finer neighbour.
+// What bounds it is the output (5.4 times the input) together with the reads of ghost rows, of which an x ghost uses three
+// values of eight.  A wavefront reads the rows of one plane in groups that lie in whole 128-byte lines of their sources:
+// three rows below the block, four and four of it, three above, so that no line is asked for by two wavefronts at a time
+// (the L1 stalls on a request for a line that is still on its way).  The values meet in LDS, from where they leave in
+// whole lines, 16 bytes a lane; the sources are kept in registers for all variables of the workgroup, and the
+// loads of the next variable are in flight while one is written.  The stores are non-temporal: the padded output is not
+// read again here and would otherwise push the ghost rows out of the L2.
+// A workgroup takes every `stride`-th variable of a block.  Normally that is all of them, chunks of 16 consecutive blocks
+// dealt to the XCDs in turn; on small trees the variables are split so that the chip is full (unzip_stride).
+// (21,064 blocks, 24 variables: 4.24 -> 3.68 ms; 47,783 blocks, two variables: 807 -> 664 us; 792 blocks, 24 variables:
+// 160 -> 142 us.  Before, a thread copied six points 512 apart from memory to memory, eight workgroups per block.  Chunks of
+// 8 / 64 / 128 blocks: 3.71 / 3.71 / 3.79 ms; plain stores +8 %; two buffers in LDS with one barrier per variable +1 to 7 %.)
+// Workgroups per block: 1,024 run at a time, and four times as many keep the last wave short; but at least two variables each,
+// for which the sources are worked out once (792 blocks, 24 variables, 1 / 2 / 6 / 12 per block: 167 / 161 / 154 / 157 us; 834
+// blocks, two variables, 1 / 2 per block: 12.4 / 14.2 us).
+inline int unzip_stride(int64_t nb, int nvar) { return (int)std::max<int64_t>(1, std::min<int64_t>(nvar / 2, (4096 + nb - 1) / nb)); }
+constexpr int kUnzipRows = NP * 4 / (NTHREADS / 64);   // row groups per wavefront: 7
+__global__ __launch_bounds__(NTHREADS, 8) void k_unzip(DeviceTree tr, int nvar, int stride, const double* __restrict__ zipped,
+                                                       const double* __restrict__ virt, double* __restrict__ padded)
 {
     __shared__ int32_t gt[27 * 5];
-    const int tid = threadIdx.x;
-    const int stride = nvar < NXCD ? nvar : NXCD;
-    const int64_t b = blockIdx.x / stride, nb = tr.nb;
-    const int v0 = (int)(blockIdx.x - b * stride);
+    __shared__ __attribute__((aligned(16))) double T[PBLK];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t b = block_of_workgroup(blockIdx.x), nb = tr.nb;
+    const int v0 = (int)blockIdx.y;
+    if (b >= nb) return;                             // uniform over the workgroup
     if (tid < 27 * 5) gt[tid] = tr.ghost_v[b * (27 * 5) + tid];
     __syncthreads();
-    uint32_t off[PLAN_FULL];
+    // the wavefront's row group: rows 0..2, 3..6, 7..10 or 11..13 of the planes wave / 4, + 2, + 4, ...
+    const int group = wave & 3, row0 = group * 4 - (group > 0 ? 1 : 0), rows = group == 0 || group == 3 ? PAD : 4;
+    const bool mine = lane < rows * NP;
+    const int row = min(lane / NP, rows - 1), ii = lane % NP, jj = row0 + row;
+    const int rx = ii < PAD ? 0 : (ii < PAD + NPT ? 1 : 2), ry = group == 0 ? 0 : (group == 3 ? 2 : 1);
+    const int lx = ii - PAD + (1 - rx) * NPT, ly = jj - PAD + (1 - ry) * NPT;
+    uint32_t off[kUnzipRows];
 #pragma unroll
-    for (int m = 0; m < PLAN_FULL; ++m) {
-        const int p = min(tid + m * NTHREADS, PBLK - 1);
-        const int ii = p % NP, jj = (p / NP) % NP, kk = p / (NP * NP);
-        const int rx = ii < PAD ? 0 : (ii < PAD + NPT ? 1 : 2);
-        const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2);
-        const int rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
-        const int lx = ii - PAD + (1 - rx) * NPT, ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
+    for (int m = 0; m < kUnzipRows; ++m) {
+        const int kk = (wave >> 2) + 2 * m;
+        const int rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2), lz = kk - PAD + (1 - rz) * NPT;
         off[m] = ghost_source(&gt[(rz * 9 + ry * 3 + rx) * 5], rx, ry, rz, lx, ly, lz);   // the centre entry is the block itself
     }
-    // the loads of two variables are in flight before the first store (22.1 -> 20.3 ms; three gain nothing more)
-    constexpr int FLIGHT = 2;
+    double pv[kUnzipRows];
+    auto load = [&](int v) {
+        const double* base = zipped + (int64_t)v * nb * BLK;
+        const double* vbase = virt + (int64_t)v * tr.n_virt * BLK;
+        if (mine) {
+#pragma unroll
+            for (int m = 0; m < kUnzipRows; ++m) pv[m] = ldg((off[m] & 1u) ? vbase : base, off[m] & ~1u);
+        }
+    };
+    double* const t = T + (wave >> 2) * (NP * NP) + row0 * NP + lane;
+    load(v0);
 #pragma unroll 1
-    for (int v = v0; v < nvar; v += FLIGHT * stride) {
-        double pv[FLIGHT][PLAN_FULL];
+    for (int v = v0; v < nvar; v += stride) {
+        if (mine) {
 #pragma unroll
-        for (int g = 0; g < FLIGHT; ++g) {
-            const int w = v + g * stride;
-            if (w < nvar) {
-                const double* base = zipped + (int64_t)w * nb * BLK;
-                const double* vbase = virt + (int64_t)w * tr.n_virt * BLK;
-#pragma unroll
-                for (int m = 0; m < PLAN_FULL; ++m) pv[g][m] = ldg((off[m] & 1u) ? vbase : base, off[m] & ~1u);
-            }
+            for (int m = 0; m < kUnzipRows; ++m) t[2 * m * (NP * NP)] = pv[m];
         }
+        __syncthreads();
+        if (v + stride < nvar) load(v + stride);
+        // blocks are 171.5 lines long: every second one starts in the middle of a line
+        const int64_t q = (int64_t)v * nb + b;
+        PairAt8* out = reinterpret_cast<PairAt8*>(padded + q * PBLK);
+        const int first = tid - ((q & 1) ? 4 : 0);
 #pragma unroll
-        for (int g = 0; g < FLIGHT; ++g) {
-            const int w = v + g * stride;
-            if (w < nvar) {
-                double* out = padded + ((int64_t)w * nb + b) * PBLK;
-#pragma unroll
-                for (int m = 0; m < PLAN_FULL; ++m) {
-                    const int p = tid + m * NTHREADS;
-                    if (p < PBLK) __builtin_nontemporal_store(pv[g][m], out + p);
-                }
-            }
+        for (int m = 0; m < 3; ++m) {
+            const int n = first + m * NTHREADS;
+            if (n >= 0 && n < PBLK / 2) __builtin_nontemporal_store(reinterpret_cast<const Pair*>(T)[n], out + n);
         }
+        __syncthreads();                                         // the next variable overwrites the array
     }
 }
 
@@ -550,7 +565,8 @@ hipError_t launch_unzip(const DeviceTree& t, int nvar, const double* zipped, con
 {
     if (t.nb <= 0 || nvar <= 0) return hipSuccess;
     if (!virt && t.n_virt > 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_unzip, dim3((unsigned)(t.nb * (nvar < NXCD ? nvar : NXCD))), dim3(NTHREADS), 0, s, t, nvar, zipped, virt, padded);
+    const int stride = unzip_stride(t.nb, nvar);
+    hipLaunchKernelGGL(k_unzip, dim3(grid_for_blocks(t.nb), (unsigned)stride), dim3(NTHREADS), 0, s, t, nvar, stride, zipped, virt, padded);
     return hipGetLastError();
 }
 

@@ -69,6 +69,10 @@ __device__ __forceinline__ void stg(double* base, uint32_t byte_off, double v)
     __builtin_nontemporal_store(v, reinterpret_cast<double*>(reinterpret_cast<char*>(base) + byte_off));
 }
 
+// two neighbouring values; arrays are only known to be aligned to 8 bytes, which 16-byte accesses allow
+typedef double Pair __attribute__((ext_vector_type(2)));
+typedef Pair PairAt8 __attribute__((aligned(8)));
+
 // Workgroups are handed to the eight XCDs (each with its own L2) round-robin by workgroup id.
 // Chunks of 16 Morton-consecutive blocks (two sibling octets) are dealt to the XCDs in turn: blocks
 // that run at the same time on one XCD are then close neighbours, which read each other's rows
@@ -104,7 +108,6 @@ constexpr int NFACE = BLK + 6 * PAD * NPT * NPT;                 // 1664
 constexpr int NEDGE = NFACE + 12 * PAD * PAD * NPT;              // 2528
 constexpr int PLAN_FACE = (NFACE + NTHREADS - 1) / NTHREADS;     // 4 entries per thread
 constexpr int PLAN_EDGE = (NEDGE + NTHREADS - 1) / NTHREADS;     // 5
-constexpr int PLAN_FULL = (PBLK + NTHREADS - 1) / NTHREADS;      // 6
 
 __device__ __forceinline__ int ghost_index(int g) { return g < PAD ? g : g + NPT; }   // 0,1,2,11,12,13
 
