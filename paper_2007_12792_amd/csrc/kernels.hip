@@ -508,7 +508,6 @@ __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double*
 // the wave system 239 / 261 on 7,134 blocks (234 MB), 360 / 346 on 9,920 (325 MB), 1645 / 1501 on 47,783; steps of Burgers
 // 219 / 238 on 13,700 blocks (224 MB), 302 / 300 on 18,278 (299 MB), 403 / 374 on 23,801; evaluations of DERIVS 36 / 36 on
 // 7,134 blocks (146 MB), 76 / 62 on 13,700 (281 MB), of Burgers 61 / 59 on 23,801 (195 MB).
-constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 180ll << 20;
 template <int KIND, int EPI>
 bool streams(int64_t nb)
 {

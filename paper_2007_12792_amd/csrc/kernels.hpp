@@ -23,6 +23,10 @@ struct DeviceTree {
 
 constexpr int32_t kUnitSingle = 1 << 30;   // flag on a unit: one block without a partner
 
+// from which size of a step's four vectors (an evaluation's input and output) kernels write, and where that pays read,
+// non-temporally
+constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 180ll << 20;
+
 // workgroup i runs on XCD i mod kXcds; the kernels deal chunks of kChunk consecutive blocks to the XCDs in turn
 constexpr int kSchedChunk = 16;
 constexpr int kSchedXcds = 8;

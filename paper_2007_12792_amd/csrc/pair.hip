@@ -27,14 +27,14 @@ namespace {
 namespace pr {
 constexpr int NT = 1024;
 constexpr int NX = 2 * NPT + 2 * PAD;    // 22 tile points along x
-constexpr int RS = NX;                   // row stride
-constexpr int PS = NX * NP + 4;          // plane stride 312 = 24 (mod 32): eight x-contiguous values of four k planes
-                                         // fall into 32 different 8-byte banks, as in the one-block tile
+constexpr int RS = 24;                   // row stride, 8 * odd: eight x-contiguous values of four j rows fall into 32 different
+                                         // 8-byte banks
+constexpr int PS = NP * RS + 1;          // plane stride: odd, for the wavefronts whose lanes are points (j, k) in mixed_fill()
 constexpr int TILE = NP * PS;            // 14 planes
 constexpr int WZ = NPT * PS;             // D1_z u on [8 k][14 jj][22 ii], rows and planes strided like the tile
-constexpr int YPS = NPT * RS + 8;        // 184 = 24 (mod 32)
+constexpr int YPS = NPT * RS + 5;
 constexpr int WY = NPT * YPS;            // D1_y u on [8 k][8 j][22 ii]
-constexpr int DUMMY = NX * NP;           // first padding slot behind plane 0: where masked plan entries are stored
+constexpr int DUMMY = NX;                // first padding slot of row 0: where masked plan entries are stored
 // ghost points of the tile in the order they are planned: the faces, then the edges (corners are never read)
 constexpr int NGF = 2 * PAD * NPT * NPT + 4 * PAD * 2 * NPT * NPT;                  // 1920
 constexpr int NGE = NGF + 8 * PAD * PAD * NPT + 4 * PAD * PAD * 2 * NPT;           // 3072 = 3 * NT
@@ -78,11 +78,11 @@ __device__ __forceinline__ void mixed_fill(const double* tile, double* wy, doubl
 {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int la = tid & 7, lb = (tid >> 3) & 7;
-    if (w < 6) {                                     // ghost x index ii, lanes = (j, k)
-        const int ii = gx(w);
-        const int ct = (lb + PAD) * PS + (la + PAD) * RS + ii;
-        wy[lb * YPS + la * RS + ii] = d1_at(tile, ct, RS, ih);
-        wz[lb * PS + (la + PAD) * RS + ii] = d1_at(tile, ct, PS, ih);
+    if (w < 6) {                                     // ghost x index ii; lanes = (j mod 4, k, j / 4): 32 different banks, since planes are odd
+        const int ii = gx(w), j = (tid & 3) | ((tid >> 3) & 4), k = (tid >> 2) & 7;
+        const int ct = (k + PAD) * PS + (j + PAD) * RS + ii;
+        wy[k * YPS + j * RS + ii] = d1_at(tile, ct, RS, ih);
+        wz[k * PS + (j + PAD) * RS + ii] = d1_at(tile, ct, PS, ih);
     }
     if (w >= 4) {                                    // ghost y index jj of one of the two blocks, lanes = (i, k)
         const int g = w - 4, jj = gyz(g >> 1), ix = la + PAD + NPT * (g & 1);
@@ -113,8 +113,14 @@ __device__ __forceinline__ int64_t pair_of_workgroup(int64_t wg)
 // half is a phantom: the first three columns of that half are the block's own ghost points beyond its upper x
 // face (taken through the block's own table row), the rest is filled with any valid value, and the threads of the
 // second half go through all the motions (they must meet the barriers) but write nothing to memory.
-template <int EPI>
-__global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
+//
+// The Runge-Kutta operands pass through once per stage and are read non-temporally, so that the input, whose ghost rows are
+// read by several workgroups, stays in the caches; with NTS the results are written so too.  Both need wavefronts whose
+// accesses are whole lines: with lanes over (i, k), where two wavefronts shared every line, they cost 5 and 2 %.
+// (Step, us, before -> now: 102,075 blocks 52,650 -> 50,800; 2,143: 1376 -> 1294; 1,135: 798 -> 752; 792: 525 -> 503.
+// Evaluation: 21,064 blocks 2226 -> 2174; 1,709: 221 -> 202.  Lanes over (i, j) alone: 52,760; with plain stores: 51,880.)
+template <int EPI, bool NTS>
+__device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 {
     __shared__ double tile[pr::TILE];
     __shared__ double wyz[pr::WZ + pr::WY];          // D1_z u and D1_y u during the second-derivative passes
@@ -137,10 +143,10 @@ __global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
     if (tid == 320) s_level = tr.leaves[b0].level;
     __syncthreads();
 
-    // thread -> point: the upper half of the workgroup takes the second block; inside a block lanes run over (i, k)
-    // and the wavefront number is j, as in the one-block kernel
+    // thread -> point: the upper half of the workgroup takes the second block; inside a block lanes run over (i, j)
+    // and the wavefront number is k, so that what a wavefront reads and writes at its own points is four whole lines
     const int half = tid >> 9, t9 = tid & 511;
-    const int i = t9 & 7, k = (t9 >> 3) & 7, j = t9 >> 6;
+    const int i = t9 & 7, j = (t9 >> 3) & 7, k = t9 >> 6;
     const int xi = i + NPT * half;                   // 0..15 along the brick
     const int c = (k + PAD) * pr::PS + (j + PAD) * pr::RS + (xi + PAD);
     const bool phantom = single && half;             // uniform over a wavefront
@@ -240,7 +246,7 @@ __global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
         const int f = syn24_stream(t), f1 = syn24_stream(t + 1);
         prefetch(nxt, f1, next_use);
         const double unext = centre((f + 11) % 24);
-        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true>(a, nb, f, o8), tile[c]);
+        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true, true>(a, nb, f, o8), tile[c]);
         const Syn24Part p = syn24_axes<true, pr::RS, pr::PS>(tile, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
         pr::mixed_fill(tile, wy, wz, tid, ih);
         __syncthreads();
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
         off = fma(Gyz, mx.dyz, off);
         const double lap = fma(2.0, off, p.diag);
         lapS[f * pr::NT + tid] = lap;
-        if (!phantom) emit<EPI>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lap, 0.5 * u0, unext), eo);
+        if (!phantom) emit<EPI, NTS>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lap, 0.5 * u0, unext), eo);
         commit(nxt, next_use);
         __syncthreads();                             // the tile is complete; D1_y u, D1_z u may be overwritten
     };
@@ -262,10 +268,10 @@ __global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
         const int f = syn24_stream(t);
         const bool more = t + 1 < NSTREAM;
         if (more) prefetch(nxt, syn24_stream(t + 1), UseFace{});
-        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true>(a, nb, f, o8), tile[c]);
+        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true, true>(a, nb, f, o8), tile[c]);
         if (t <= 13) wyz[(t - 11) * pr::NT + tid] = tile[c];     // u_23, u_22, u_21 for the last three passes
         const Syn24Part p = syn24_axes<false, pr::RS, pr::PS>(tile, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
-        if (!phantom) emit<EPI>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lapS[(f % 10) * pr::NT + tid], 0.5 * u0, unext), eo);
+        if (!phantom) emit<EPI, NTS>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lapS[(f % 10) * pr::NT + tid], 0.5 * u0, unext), eo);
         if (more) {
             __syncthreads();                         // everybody is done with the tile
             commit(nxt, UseFace{});
@@ -285,6 +291,18 @@ __global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a)
     for (int t = 22; t < NSTREAM; ++t) pass_light(t, wyz[(t - 22) * pr::NT + tid]);
 }
 
+template <int EPI>
+__global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, false>(tr, a); }
+template <int EPI>
+__global__ __launch_bounds__(pr::NT) void k_pair_stream(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true>(tr, a); }
+
+template <int EPI>
+void launch_pairs(bool stream, dim3 grid, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
+{
+    if (stream) hipLaunchKernelGGL(k_pair_stream<EPI>, grid, dim3(pr::NT), 0, s, t, a);
+    else hipLaunchKernelGGL(k_rhs_pair<EPI>, grid, dim3(pr::NT), 0, s, t, a);
+}
+
 }  // namespace
 
 hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& a, hipStream_t s)
@@ -292,12 +310,16 @@ hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& a, 
     if (t.n_units <= 0) return hipSuccess;
     if (!a.virt && t.n_virt > 0) return hipErrorInvalidValue;
     const int64_t span = pr::PAIR_CHUNK * NXCD;
-    const dim3 grid((unsigned)((t.n_units + span - 1) / span * span)), block(pr::NT);
+    const dim3 grid((unsigned)((t.n_units + span - 1) / span * span));
+    // Written non-temporally from the size at which the vectors do not stay in the memory-side cache, without / with: steps
+    // 481 / 494 us on 708 blocks (278 MB), 505 / 519 on 792 (311 MB), 784 / 755 on 1,135 (446 MB), 51.9 / 50.8 ms on 102,075;
+    // evaluations 102 / 101 on 708 blocks (139 MB), 151 / 148 on 1,093 (215 MB), 225 / 197 on 1,709.
+    const bool stream = t.nb * BLK * (int64_t)sizeof(double) * 24 * (ep == kOutZipped ? 2 : 4) > (ep == kOutZipped ? kStreamEvalBytes : kStreamStepBytes);
     switch (ep) {
-    case kOutZipped: hipLaunchKernelGGL(k_rhs_pair<kOutZipped>, grid, block, 0, s, t, a); break;
-    case kRkFirst: hipLaunchKernelGGL(k_rhs_pair<kRkFirst>, grid, block, 0, s, t, a); break;
-    case kRkMiddle: hipLaunchKernelGGL(k_rhs_pair<kRkMiddle>, grid, block, 0, s, t, a); break;
-    case kRkLast: hipLaunchKernelGGL(k_rhs_pair<kRkLast>, grid, block, 0, s, t, a); break;
+    case kOutZipped: launch_pairs<kOutZipped>(stream, grid, t, a, s); break;
+    case kRkFirst: launch_pairs<kRkFirst>(stream, grid, t, a, s); break;
+    case kRkMiddle: launch_pairs<kRkMiddle>(stream, grid, t, a, s); break;
+    case kRkLast: launch_pairs<kRkLast>(stream, grid, t, a, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
