@@ -8,6 +8,7 @@
 #include "kernels.hpp"
 #include "octfd.h"
 #include "octree_host.hpp"
+#include "source.hpp"
 #include "transfer.hpp"
 
 using namespace octfd;
@@ -78,8 +79,9 @@ int same_device(int device)
 int ensure_device(const ot_tree* t)
 {
     if (t->device >= 0) return same_device(t->device);
-    // kernels address one variable's zipped array with 32-bit byte offsets
-    if (t->host.leaves.size() >= (size_t(1) << 20)) return OT_E_UNSUPPORTED;
+    // kernels address one variable's zipped array with 32-bit byte offsets, and its virtual blocks with two bits more
+    // (most per block known: 3.73, where one octant in eight of a level is split, none next to another)
+    if (t->host.leaves.size() >= static_cast<size_t>(kBlockLimit) || t->host.n_virt > kVirtualLimit) return OT_E_UNSUPPORTED;
     int ndev = 0;
     hipError_t e = hipGetDeviceCount(&ndev);
     if (e != hipSuccess) return hip_fail(e);

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(NTHREADS, 8) void k_unzip(DeviceTree tr, int nvar, 
         const double* vbase = virt + (int64_t)v * tr.n_virt * BLK;
         if (mine) {
 #pragma unroll
-            for (int m = 0; m < kUnzipRows; ++m) pv[m] = ldg((off[m] & 1u) ? vbase : base, off[m] & ~1u);
+            for (int m = 0; m < kUnzipRows; ++m) pv[m] = ldg_source(base, vbase, off[m]);
         }
     };
     double* const t = T + (wave >> 2) * (NP * NP) + row0 * NP + lane;

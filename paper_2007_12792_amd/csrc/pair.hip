@@ -119,7 +119,7 @@ __device__ __forceinline__ int64_t pair_of_workgroup(int64_t wg)
 // accesses are whole lines: with lanes over (i, k), where two wavefronts shared every line, they cost 5 and 2 %.
 // (Step, us, before -> now: 102,075 blocks 52,650 -> 50,800; 2,143: 1376 -> 1294; 1,135: 798 -> 752; 792: 525 -> 503.
 // Evaluation: 21,064 blocks 2226 -> 2174; 1,709: 221 -> 202.  Lanes over (i, j) alone: 52,760; with plain stores: 51,880.)
-template <int EPI, bool NTS>
+template <int EPI, bool NTS, bool WIDE>
 __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 {
     __shared__ double tile[pr::TILE];
@@ -157,7 +157,7 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
     const double ih = __longlong_as_double((long long)(1026 + lvl) << 52), ih2 = __longlong_as_double((long long)(1029 + 2 * lvl) << 52);
     const double sigma = a.sigma;
 
-    // fill plan, in registers: source offset (bit 0: virtual block) and tile index of the thread's ghost points, and the
+    // fill plan, in registers: source and tile index of the thread's ghost points, and the
     // source of its own point
     uint32_t gsrc[pr::USE_EDGE];
     int gdst[pr::USE_EDGE];
@@ -195,12 +195,12 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
         constexpr int USE = decltype(use)::value;
         const double* base = var_base(v);
         const double* vbase = virt_base(v);
-        f.own = ldg((own_src & 1u) ? vbase : base, own_src & ~1u);
+        f.own = ldg_source<WIDE>(base, vbase, own_src);
 #pragma unroll
         for (int m = 0; m < USE; ++m) {
             uint32_t off = gsrc[m];
             if (USE == pr::USE_FACE && m == 1 && face_mask1) off = 0;
-            f.g[m] = ldg((off & 1u) ? vbase : base, off & ~1u);
+            f.g[m] = ldg_source<WIDE>(base, vbase, off);
         }
     };
     auto commit = [&](const Fetch& f, auto use) {
@@ -292,14 +292,19 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 }
 
 template <int EPI>
-__global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, false>(tr, a); }
+__global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, false, false>(tr, a); }
 template <int EPI>
-__global__ __launch_bounds__(pr::NT) void k_pair_stream(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true>(tr, a); }
+__global__ __launch_bounds__(pr::NT) void k_pair_stream(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true, false>(tr, a); }
+// for trees with more virtual blocks than a 32-bit offset reaches.  The wider addresses cost the two kernels above 1.4 %
+// (21,064 blocks, evaluation: 2233 / 2264 us; 102,075 blocks, step: 51.98 / 52.72 ms), k_unzip and the slab kernels nothing.
+template <int EPI>
+__global__ __launch_bounds__(pr::NT) void k_pair_wide(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true, true>(tr, a); }
 
 template <int EPI>
 void launch_pairs(bool stream, dim3 grid, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
-    if (stream) hipLaunchKernelGGL(k_pair_stream<EPI>, grid, dim3(pr::NT), 0, s, t, a);
+    if (t.n_virt > kBlockLimit) hipLaunchKernelGGL(k_pair_wide<EPI>, grid, dim3(pr::NT), 0, s, t, a);
+    else if (stream) hipLaunchKernelGGL(k_pair_stream<EPI>, grid, dim3(pr::NT), 0, s, t, a);
     else hipLaunchKernelGGL(k_rhs_pair<EPI>, grid, dim3(pr::NT), 0, s, t, a);
 }
 

@@ -54,7 +54,8 @@ __device__ __forceinline__ GhostLane ghost_lane(int lane)
 typedef const __attribute__((address_space(4))) int32_t* ScalarInts;
 __device__ __forceinline__ ScalarInts scalar_ints(const void* p) { return (ScalarInts)(uintptr_t)p; }
 
-// the octant beyond a face: base of the array that holds it, and byte offset of the lane's value in it
+// the octant beyond a face: base of the array that holds it (of virtual blocks: of the 4 GiB of it), and byte offset of the
+// lane's value from there, modulo 2^32 like a source
 struct FaceEntry { int kind, id[4]; };
 __device__ __forceinline__ FaceEntry face_entry(ScalarInts row, int dir)
 {
@@ -78,7 +79,7 @@ __device__ __forceinline__ void load_slab_zipped(Slab& s, ScalarInts row, const 
     // the two lower slabs reach below the block, the two upper ones above it
     const FaceEntry ez = face_entry(row, w < 2 ? kDirZm : kDirZp);
     const FaceEntry e0 = face_entry(row, kDirXm), e1 = face_entry(row, kDirXp), e2 = face_entry(row, kDirYm), e3 = face_entry(row, kDirYp);
-    auto base = [&](const FaceEntry& e) -> const double* { return e.kind == K_VIRT ? virt : in; };
+    auto base = [&](const FaceEntry& e) -> const double* { return e.kind == K_VIRT ? virt + bank_start(e.id[0]) : in; };
     const uint32_t o = ((uint32_t)b * BLK + k0 * 64 + lane) * 8u;
 #pragma unroll
     for (int kk = 0; kk < sl::KZ; ++kk) s.own[kk] = ldg(in + kk * 64, o);

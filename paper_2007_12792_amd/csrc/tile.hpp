@@ -4,13 +4,12 @@
 #pragma once
 #include "kernels.hpp"
 #include "lagrange.hpp"
+#include "source.hpp"
 
 namespace octfd {
 namespace {
 
-constexpr int NPT = 8, PAD = 3, NP = 14, BLK = 512, PBLK = 2744;
 constexpr int NTHREADS = 512;
-constexpr int K_SAME = 0, K_FINER = 1, K_VIRT = 3;   // kinds of a ghost-table entry: copy, injection, copy from a virtual block
 
 // LDS geometry (in doubles).  Rows are stored compactly (stride 14) and planes are padded to a
 // stride of 200 = 8 (mod 32).  A wavefront holds one j row of the block, its lanes run over
@@ -38,7 +37,8 @@ __device__ __forceinline__ void point_of(int tid, int& i, int& j, int& k)
 
 // Loads and stores of global arrays use a uniform 64-bit base (one variable's array) plus a 32-bit
 // byte offset held per thread, so that no per-access 64-bit address arithmetic is needed.  The
-// library refuses trees with 2^20 blocks or more, which keeps every offset below 2^32.
+// library refuses trees with 2^20 blocks or more, which keeps every offset into a zipped array below 2^32
+// (for arrays of virtual blocks see source.hpp).
 // The empty asm keeps the 32-bit offset a 32-bit register at the point of use; otherwise the
 // compiler widens the offsets to 64 bits once, outside the variable loop, which doubles their
 // register cost and forces a 64-bit add per access.
@@ -51,6 +51,16 @@ __device__ __forceinline__ void stg(double* base, uint32_t byte_off, double v)
 {
     asm volatile("" : "+v"(byte_off));
     *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + byte_off) = v;
+}
+
+// the value at a source, from the variable's zipped array or its virtual blocks; WIDE = false: of a tree with at most
+// kBlockLimit virtual blocks, whose bits 1 and 2 are 0
+template <bool WIDE = true>
+__device__ __forceinline__ double ldg_source(const double* base, const double* virt, uint32_t src)
+{
+    if (!WIDE) return ldg(source_is_virtual(src) ? virt : base, src & ~1u);
+    asm volatile("" : "+v"(src));
+    return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(source_is_virtual(src) ? virt : base) + source_offset(src));
 }
 
 // NT: as non-temporal accesses, for data that would leave the caches before it is read again.
@@ -150,29 +160,6 @@ struct FillPlan {
     __device__ __forceinline__ void set_dst(int m, int v) { dstp[m >> 1] = (m & 1) ? (dstp[m >> 1] | ((uint32_t)v << 16)) : (uint32_t)v; }
 };
 static_assert(TILE < 65536, "tile indices are packed in pairs");
-
-// Where the point (lx, ly, lz) of the same-level octant in direction (rx, ry, rz) - 1 comes from, given that
-// direction's entry e of the table in which coarser neighbours appear as virtual blocks: byte offset into one variable's zipped array (same level: copy;
-// finer: the coinciding node of the child that holds it) or, marked by bit 0, into its array of virtual blocks.
-__device__ __forceinline__ uint32_t ghost_source(const int32_t* e, int rx, int ry, int rz, int lx, int ly, int lz)
-{
-    const int kind = e[0];
-    uint32_t elem;
-    if (kind == K_SAME || kind == K_VIRT) {
-        elem = (uint32_t)e[1] * BLK + (lz * NPT + ly) * NPT + lx;
-    } else {
-        // which child holds the point: forced by the direction on non-free axes
-        const int bx = rx == 1 ? (lx >> 2) : (rx == 0 ? 1 : 0);
-        const int by = ry == 1 ? (ly >> 2) : (ry == 0 ? 1 : 0);
-        const int bz = rz == 1 ? (lz >> 2) : (rz == 0 ? 1 : 0);
-        int q = 0, sh = 0;
-        if (rx == 1) { q |= bx << sh; ++sh; }
-        if (ry == 1) { q |= by << sh; ++sh; }
-        if (rz == 1) { q |= bz << sh; }
-        elem = (uint32_t)e[1 + q] * BLK + ((2 * lz - NPT * bz) * NPT + (2 * ly - NPT * by)) * NPT + (2 * lx - NPT * bx);
-    }
-    return elem * 8u | (kind == K_VIRT ? 1u : 0u);
-}
 
 // Source of every padded point this thread fills, as a byte offset into the block's padded data.
 // NPOINTS = how long a prefix of the enumeration is planned.
