@@ -40,46 +40,50 @@ def usage():
     return kernels
 
 
-def rhs_kernels(usage):
-    """(kind, zipped input, epilogue) -> resources, from the mangled template arguments"""
+def instances(usage, name):
+    """template arguments -> resources of the instances of a kernel template, from the mangled names"""
     out = {}
-    for name, res in usage.items():
-        m = re.search(r"k_rhsILi(\d)ELb(\d)ELi(\d)EEE", name)
+    for mangled, res in usage.items():
+        m = re.search(r"\d%sI((?:L[bi]\dE)+)E" % name, mangled)
         if m:
-            out[tuple(int(g) for g in m.groups())] = res
+            out[tuple(int(g) for g in re.findall(r"L[bi](\d)E", m.group(1)))] = res
     return out
 
 
+def check(res, what, vgprs, lds):
+    assert res["VGPRs"] + res.get("AGPRs", 0) <= vgprs, (what, res)
+    assert res["LDS Size [bytes/block]"] <= lds, (what, res)
+    assert res["ScratchSize [bytes/lane]"] == 0 and res["VGPRs Spill"] == 0, (what, res)
+
+
 def test_small_kinds_fit_four_workgroups_per_compute_unit_without_spilling(usage):
-    ks = rhs_kernels(usage)
-    checked = 0
-    for (kind, zin, epi), res in ks.items():
-        if kind == 3 or not zin:
-            continue
-        assert res["LDS Size [bytes/block]"] <= 160 * 1024 // 4, (kind, epi)
-        assert res["ScratchSize [bytes/lane]"] == 0 and res["VGPRs Spill"] == 0, (kind, epi, res)
-        assert res["VGPRs"] <= 64, (kind, epi)
-        checked += 1
-    assert checked >= 3 * 4                # three kinds, four epilogues
+    zipped = {k: v for k, v in instances(usage, "k_rhs").items() if k[0] != 3 and k[1]}     # kind, zipped input, epilogue
+    stream = instances(usage, "k_rhs_stream")                                               # kind, epilogue
+    assert len(zipped) == 3 * 4 and len(stream) == 3 * 4       # three kinds, four epilogues
+    for key, res in list(zipped.items()) + list(stream.items()):
+        check(res, key, 64, 160 * 1024 // 4)
 
 
 def test_24_field_kernels_fit_two_workgroups_per_compute_unit(usage):
-    ks = {k: v for k, v in rhs_kernels(usage).items() if k[0] == 3}      # padded input only: zipped input runs k_rhs_pair
+    ks = {k: v for k, v in instances(usage, "k_rhs").items() if k[0] == 3}      # padded input only: zipped input runs k_rhs_pair
     assert len(ks) == 5
     for key, res in ks.items():
-        assert res["VGPRs"] + res.get("AGPRs", 0) <= 128, key
-        assert res["LDS Size [bytes/block]"] <= 160 * 1024 // 2, key
-        assert res["VGPRs Spill"] == 0 and res["ScratchSize [bytes/lane]"] == 0, (key, res)   # no interpolation code left in them
+        check(res, key, 128, 160 * 1024 // 2)                  # no interpolation code left in them
 
 
-def test_two_block_kernel_fits_one_compute_unit(usage):
-    """k_rhs_pair: 1,024 threads, so 128 registers at most, and all its LDS from one compute unit's 160 KB"""
-    names = [n for n in usage if "k_rhs_pair" in n]
-    assert len(names) == 4
-    for n in names:
-        assert usage[n]["VGPRs"] + usage[n].get("AGPRs", 0) <= 128, n
-        assert usage[n]["LDS Size [bytes/block]"] <= 160 * 1024, n
-        assert usage[n]["VGPRs Spill"] == 0 and usage[n]["ScratchSize [bytes/lane]"] == 0, (n, usage[n])
+@pytest.mark.parametrize("name", ["k_rhs_pair", "k_pair_stream", "k_pair_wide"])
+def test_two_block_kernels_fit_one_compute_unit(usage, name):
+    """1,024 threads, so 128 registers at most, and all the LDS from one compute unit's 160 KB; one instance per epilogue"""
+    ks = instances(usage, name)
+    assert sorted(ks) == [(1,), (2,), (3,), (4,)]
+    for key, res in ks.items():
+        check(res, (name, key), 128, 160 * 1024)
+
+
+def test_every_kernel_is_looked_at(usage):
+    names = ["k_rhs", "k_rhs_stream", "k_rhs_pair", "k_pair_stream", "k_pair_wide", "k_unzip", "k_virtual", "k_virtual_centred", "k_zip"]
+    other = [n for n in usage if not any(re.search(r"\d%s[IE]" % k, n) for k in names)]
+    assert not other, other
 
 
 def test_fill_kernels_fit_three_workgroups_per_compute_unit(usage):
