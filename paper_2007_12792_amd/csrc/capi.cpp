@@ -304,7 +304,7 @@ int rhs_eval(const ot_tree* tree, ot_rhs_kind kind, const ot_rhs_params* params,
     if (!tree || !kind_ok(kind) || !params || !padded_dev || !rhs_padded_dev || !aligned8(padded_dev) || !aligned8(rhs_padded_dev))
         return OT_E_BADARG;
     if (int rc = ensure_device(tree)) return rc;
-    RhsArgs a{padded_dev, rhs_padded_dev, nullptr, nullptr, nullptr, rhs_padded_dev, 0.0, params->ko_sigma};
+    RhsArgs a{padded_dev, rhs_padded_dev, nullptr, nullptr, nullptr, 0.0, params->ko_sigma};
     hipError_t e = launch_rhs(dev_view(tree), kind, false, kOutPadded, a, static_cast<hipStream_t>(hip_stream));
     return e == hipSuccess ? OT_OK : hip_fail(e);
 }
@@ -323,7 +323,7 @@ int rhs_eval_zipped(const ot_tree* tree, ot_rhs_kind kind, const ot_rhs_params* 
         hipError_t e = launch_virtual(dv, ot_rhs_nvar_in(kind), zipped_dev, tree->d_virt, s);
         if (e != hipSuccess) return hip_fail(e);
     }
-    RhsArgs a{zipped_dev, rhs_zipped_dev, nullptr, nullptr, vbytes ? tree->d_virt : nullptr, rhs_zipped_dev, 0.0, params->ko_sigma};
+    RhsArgs a{zipped_dev, rhs_zipped_dev, nullptr, nullptr, vbytes ? tree->d_virt : nullptr, 0.0, params->ko_sigma};
     hipError_t e = launch_rhs(dv, kind, true, kOutZipped, a, s);
     return e == hipSuccess ? OT_OK : hip_fail(e);
 }
@@ -363,10 +363,10 @@ static int rk_step_launch(const ot_tree* tree, ot_rhs_kind kind, const ot_rhs_pa
     // stage vectors ping-pong between sa and sb: a stage reads ghosts of the vector it was given
     // while writing the next one, so the two must be different arrays
     const RhsArgs st[4] = {
-        {u, sa, acc, u, virt, sa, 0.5 * dt, sg},    // k1 = F(u):   acc = k1,        sa = u + dt/2 k1
-        {sa, sb, acc, u, virt, sb, 0.5 * dt, sg},   // k2 = F(sa):  acc += 2 k2,     sb = u + dt/2 k2
-        {sb, sa, acc, u, virt, sa, dt, sg},         // k3 = F(sb):  acc += 2 k3,     sa = u + dt k3
-        {sa, nullptr, acc, u, virt, sb, dt / 6.0, sg}};   // k4 = F(sa):  u += dt/6 (acc + k4); sb is free scratch
+        {u, sa, acc, u, virt, 0.5 * dt, sg},    // k1 = F(u):   acc = k1,        sa = u + dt/2 k1
+        {sa, sb, acc, u, virt, 0.5 * dt, sg},   // k2 = F(sa):  acc += 2 k2,     sb = u + dt/2 k2
+        {sb, sa, acc, u, virt, dt, sg},         // k3 = F(sb):  acc += 2 k3,     sa = u + dt k3
+        {sa, nullptr, acc, u, virt, dt / 6.0, sg}};   // k4 = F(sa):  u += dt/6 (acc + k4)
     const Epilogue ep[4] = {kRkFirst, kRkMiddle, kRkMiddle, kRkLast};
     for (int i = 0; i < 4; ++i) {
         // the virtual blocks of this stage's input first; the stream orders them before the stage kernel and

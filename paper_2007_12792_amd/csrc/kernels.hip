@@ -33,7 +33,6 @@ struct Syn24Lds {
     double wyz[WZ + WY];                             // D1_z u and D1_y u of the variable in hand (mixed derivatives)
     uint32_t plan_src[PLAN_EDGE * NTHREADS];
 };
-template <int EPI>
 __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const RhsArgs& a, Syn24Lds& lds, int64_t b, int tid)
 {
     const int64_t nb = tr.nb;
@@ -42,8 +41,7 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
     int i, j, k;
     point_of(tid, i, j, k);
     const int c = tidx(k + PAD, j + PAD, i + PAD);
-    // byte offsets of this thread's point inside one variable's zipped array / inside a padded block
-    const uint32_t o8 = ((uint32_t)b * BLK + (k * NPT + j) * NPT + i) * 8u;
+    // byte offset of this thread's point inside a padded block
     const uint32_t p8 = (((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)) * 8u;
     // 1/h = 2^(l+3) and 1/h^2, built from the level as bit patterns in scalar registers
     const int lvl = tr.leaves[b].level;
@@ -60,14 +58,14 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
 
     // SYN24.  The variables are streamed in descending cyclic order (see syn24_stream).  The
     // first ten real passes (variables 9..0) evaluate the second-derivative combinations Lap_s;
-    // each thread parks them at its own point in variables 10+s of the `stash` array, from where
+    // each thread parks them at its own point in variables 10+s of the output, from where
     // the later passes (variables 23..10, which need Lap_{a mod 10}) read them back before those
     // slots receive their final values.  Per-thread state thus shrinks to one gradient.
     //
     // The tile is double-buffered and global memory is requested ahead of its use: tile data
     // of the next variable is loaded into registers at the top of a pass and stored to the
     // other LDS buffer at its end (one barrier per pass, plus the one inside mixed_derivs); the
-    // pointwise operands of the next pass (RK accumulator and state, u_{a+11}, Lap) likewise.
+    // pointwise operands of the next pass (u_{a+11}, Lap) likewise.
     double* wz = wyz;
     double* wy = wyz + WZ;
     const double halpha = 0.5 * centre(0), bx = centre(1), by = centre(2), bz = centre(3);
@@ -75,12 +73,10 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
     const double Gyy = 1.0 - 0.125 * centre(7), Gyz = -(0.125 * centre(8)), Gzz = 1.0 - 0.125 * centre(9);
     double nx = 0, ny = 0, nz = 0;
     const int ownz = k * PS + (j + PAD) * RS + (i + PAD), owny = k * YPS + j * RS + (i + PAD);
-    struct Look { double unext, lap; EpiOperands eo; };
+    struct Look { double unext, lap; };
 
-    auto stash_base = [&](int v) -> double* {   // where Lap_{v-10} is parked (v = 10..19)
-        return EPI == kOutPadded ? a.stash + ((int64_t)v * nb + b) * PBLK : a.stash + (int64_t)v * nb * BLK;
-    };
-    const uint32_t s8 = EPI == kOutPadded ? p8 : o8;
+    auto out_base = [&](int v) -> double* { return a.out + ((int64_t)v * nb + b) * PBLK; };   // Lap_{v-10} is parked there (v = 10..19)
+    auto put = [&](int f, double rhs) { emit<kOutPadded>(a, nb, f, b, 0u, p8, rhs, EpiOperands{0.0, 0.0}); };
 
     // top of pass t: request the tile data of pass t+1 and this pass's own pointwise operands.
     // NEXT_USE says how much of the tile pass t+1 reads (edges only if it takes second derivatives).
@@ -91,8 +87,7 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
             prefetch<PLAN_EDGE, NEXT_USE>(pv, fp, var_base(f1), tid);
         }
         l.unext = centre((f + 11) % 24);
-        l.eo = epi_prefetch<EPI>(a, nb, f, o8);
-        if (t > 10) l.lap = ldg(stash_base(10 + f % 10), s8);
+        if (t > 10) l.lap = ldg(out_base(10 + f % 10), p8);
     };
     using UseEdge = std::integral_constant<int, PLAN_EDGE>;
     using UseFace = std::integral_constant<int, PLAN_FACE>;
@@ -102,7 +97,7 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
         const double* T = tiles + (t & 1) * TILE;
         const int f = syn24_stream(t);
         int f1 = 0;
-        Look l{0.0, 0.0, {0.0, 0.0}};
+        Look l{0.0, 0.0};
         issue(t, f, l, f1, next_use);
         const Syn24Part p = syn24_axes<true>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
         const Mixed mx = mixed_derivs(T, wy, wz, tid, owny, ownz, ih);
@@ -110,8 +105,8 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
         off = fma(Gxz, mx.dxz, off);
         off = fma(Gyz, mx.dyz, off);
         const double lap = fma(2.0, off, p.diag);
-        stg(stash_base(10 + f), s8, lap);
-        emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, lap, halpha, l.unext), l.eo);
+        stg(out_base(10 + f), p8, lap);
+        put(f, syn24_combine(p, f, lap, halpha, l.unext));
         store_tile<PLAN_EDGE, NEXT_USE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
         __syncthreads();
     };
@@ -120,10 +115,10 @@ __device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const Rhs
         const double* T = tiles + (t & 1) * TILE;
         const int f = syn24_stream(t);
         int f1 = 0;
-        Look l{0.0, 0.0, {0.0, 0.0}};
+        Look l{0.0, 0.0};
         issue(t, f, l, f1, UseFace{});
         const Syn24Part p = syn24_axes<false>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
-        emit<EPI>(a, nb, f, b, o8, p8, syn24_combine(p, f, l.lap, halpha, l.unext), l.eo);
+        put(f, syn24_combine(p, f, l.lap, halpha, l.unext));
         if (t + 1 < NSTREAM) {
             store_tile<PLAN_EDGE, PLAN_FACE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
             __syncthreads();
@@ -155,11 +150,12 @@ constexpr int rhs_threads(int kind) { return kind == OT_RHS_SYN24 ? NTHREADS : s
 template <int KIND, bool ZIN, int EPI>
 __global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs(DeviceTree tr, RhsArgs a)
 {
+    static_assert(ZIN != (EPI == kOutPadded), "padded in, padded out; everything else zipped");
     const int64_t b = block_of_workgroup(blockIdx.x);
     if (b >= tr.nb) return;                          // uniform over the workgroup
     if constexpr (KIND == OT_RHS_SYN24) {
         __shared__ Syn24Lds lds;
-        rhs_syn24_padded<EPI>(tr, a, lds, b, threadIdx.x);
+        rhs_syn24_padded(tr, a, lds, b, threadIdx.x);
     } else {
         __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
         __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
@@ -540,22 +536,18 @@ hipError_t launch_kind(const DeviceTree& t, bool zin, Epilogue ep, const RhsArgs
     if (zin && !a.virt && t.n_virt > 0) return hipErrorInvalidValue;
     if (zin && ep == kRkFirst && a.in != a.u) return hipErrorInvalidValue;   // the first stage takes the state from its input tiles
     if (!zin) {
+        if (ep != kOutPadded) return hipErrorInvalidValue;
+        return launch_one<KIND, false, kOutPadded>(t, a, s);
+    }
+    if constexpr (KIND != OT_RHS_DERIVS) {           // its output is not a rate of change of its input: no stages
         switch (ep) {
-        case kOutPadded: return launch_one<KIND, false, kOutPadded>(t, a, s);
-        case kOutZipped: return launch_one<KIND, false, kOutZipped>(t, a, s);
-        case kRkFirst: return launch_one<KIND, false, kRkFirst>(t, a, s);
-        case kRkMiddle: return launch_one<KIND, false, kRkMiddle>(t, a, s);
-        case kRkLast: return launch_one<KIND, false, kRkLast>(t, a, s);
-        default: return hipErrorInvalidValue;
+        case kRkFirst: return launch_one<KIND, true, kRkFirst>(t, a, s);
+        case kRkMiddle: return launch_one<KIND, true, kRkMiddle>(t, a, s);
+        case kRkLast: return launch_one<KIND, true, kRkLast>(t, a, s);
+        default: break;
         }
     }
-    switch (ep) {
-    case kOutZipped: return launch_one<KIND, true, kOutZipped>(t, a, s);
-    case kRkFirst: return launch_one<KIND, true, kRkFirst>(t, a, s);
-    case kRkMiddle: return launch_one<KIND, true, kRkMiddle>(t, a, s);
-    case kRkLast: return launch_one<KIND, true, kRkLast>(t, a, s);
-    default: return hipErrorInvalidValue;
-    }
+    return ep == kOutZipped ? launch_one<KIND, true, kOutZipped>(t, a, s) : hipErrorInvalidValue;
 }
 
 }  // namespace

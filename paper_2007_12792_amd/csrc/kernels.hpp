@@ -47,8 +47,6 @@ struct RhsArgs {
     double* u;          // state at the start of the step (zipped); written by kRkLast
     const double* virt;      // zipped input: the virtual blocks of `in`, [V][n_virt][512], filled by launch_virtual or
                              // launch_virtual_centred (which of the two decides the ghost rule)
-    double* stash;      // SYN24 only: array shaped like `out` whose variables 10..19 may be used as
-                        // scratch until their final values are written (may be `out` itself)
     double c;           // dt/2, dt or dt/6
     double sigma;       // Kreiss-Oliger strength
 };

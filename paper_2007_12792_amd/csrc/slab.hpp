@@ -212,12 +212,12 @@ __device__ __forceinline__ void rhs_slab(const DeviceTree& tr, const RhsArgs& a,
             const uint32_t o = o8 + kk * OS, q = p8 + kk * PSB;
             const double val[4] = {p.dx, p.dy, p.dz, p.lap};
 #pragma unroll
-            for (int n = 0; n < 4; ++n) emit<EPI, NT>(a, nb, n, b, o, q, val[n], epi_prefetch<EPI, false, NT>(a, nb, n, o));
+            for (int n = 0; n < 4; ++n) emit<EPI, NT>(a, nb, n, b, o, q, val[n], EpiOperands{0.0, 0.0});   // no stages: four outputs of one field
         }
     } else if (KIND == OT_RHS_BURGERS) {
         EpiOperands e[sl::KZ];
 #pragma unroll
-        for (int kk = 0; kk < sl::KZ; ++kk) e[kk] = epi_prefetch<EPI, ZIN, NT>(a, nb, 0, o8 + kk * OS);
+        for (int kk = 0; kk < sl::KZ; ++kk) e[kk] = epi_prefetch<EPI, NT>(a, nb, 0, o8 + kk * OS);
         store_slab(T, s, w, lane, gl);
         __syncthreads();
         load_column(z, T, s, w, lane);
@@ -225,7 +225,7 @@ __device__ __forceinline__ void rhs_slab(const DeviceTree& tr, const RhsArgs& a,
         for (int kk = 0; kk < sl::KZ; ++kk) {
             const PointOps p = slab_ops<false>(P, z, ya, kk, lane, sigma, ih, ih2);
             const double flux = p.u0 * p.dx;
-            emit<EPI, NT>(a, nb, 0, b, o8 + kk * OS, p8 + kk * PSB, p.ko - flux, ZIN ? with_u<EPI>(e[kk], p.u0) : e[kk]);
+            emit<EPI, NT>(a, nb, 0, b, o8 + kk * OS, p8 + kk * PSB, p.ko - flux, with_u<EPI>(e[kk], p.u0));
         }
     } else {
         // wavefronts of u: the Laplacian goes to those of pi through LDS, d_t u = pi + KO(u) needs pi at the own points only
@@ -233,7 +233,7 @@ __device__ __forceinline__ void rhs_slab(const DeviceTree& tr, const RhsArgs& a,
         double other[sl::KZ];
 #pragma unroll
         for (int kk = 0; kk < sl::KZ; ++kk) {
-            e[kk] = epi_prefetch<EPI, ZIN, NT>(a, nb, v, o8 + kk * OS);
+            e[kk] = epi_prefetch<EPI, NT>(a, nb, v, o8 + kk * OS);
             if (v == 0) other[kk] = ZIN ? ldg(a.in + nb * BLK, o8 + kk * OS) : ldg(a.in + (nb + b) * PBLK, p8 + kk * PSB);
         }
         store_slab(T, s, w, lane, gl);
@@ -254,7 +254,7 @@ __device__ __forceinline__ void rhs_slab(const DeviceTree& tr, const RhsArgs& a,
 #pragma unroll
         for (int kk = 0; kk < sl::KZ; ++kk) {
             const double k = v == 0 ? other[kk] + ko[kk] : lapS[(k0 + kk) * 64 + lane] + ko[kk];
-            emit<EPI, NT>(a, nb, v, b, o8 + kk * OS, p8 + kk * PSB, k, ZIN ? with_u<EPI>(e[kk], s.own[kk]) : e[kk]);
+            emit<EPI, NT>(a, nb, v, b, o8 + kk * OS, p8 + kk * PSB, k, with_u<EPI>(e[kk], s.own[kk]));
         }
     }
 }

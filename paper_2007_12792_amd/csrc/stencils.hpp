@@ -102,16 +102,18 @@ __device__ __forceinline__ Mixed mixed_derivs(const double* tile, double* wy, do
 // padded block; w selects the variable and b the block (both uniform).
 struct EpiOperands { double acc, u; };
 
-// U_FROM_TILE: in the first stage the input of the right-hand side is the state itself (the launcher checks it), so
+// In the first stage the input of the right-hand side is the state itself (the launcher checks it), so
 // the state at the thread's point is the centre of the variable's tile and is not loaded again: the kernel hands it
 // over with with_u() once it has it.
-template <int EPI, bool U_FROM_TILE = false, bool NT = false>
+template <int EPI, bool NT>
 __device__ __forceinline__ EpiOperands epi_prefetch(const RhsArgs& a, int64_t nb, int w, uint32_t o8)
 {
     EpiOperands e{0.0, 0.0};
     const int64_t f = (int64_t)w * nb * BLK;
-    if ((EPI == kRkFirst && !U_FROM_TILE) || EPI == kRkMiddle || EPI == kRkLast) e.u = ldg<NT>(a.u + f, o8);
-    if (EPI == kRkMiddle || EPI == kRkLast) e.acc = ldg<NT>(a.acc + f, o8);
+    if (EPI == kRkMiddle || EPI == kRkLast) {
+        e.u = ldg<NT>(a.u + f, o8);
+        e.acc = ldg<NT>(a.acc + f, o8);
+    }
     return e;
 }
 template <int EPI>
