@@ -153,7 +153,7 @@ struct TouchingChildren {
     }
 };
 
-// The ghost table and what is derived from it: virtual blocks, by level, and which parts of them are read.  The leaves have
+// The ghost table and what is derived from it: virtual blocks, and which parts of them are read.  The leaves have
 // their ids.  Returns OT_OK or OT_E_UNBALANCED.
 int make_tables(const Octree& t, HostTree& out)
 {
@@ -237,13 +237,6 @@ int make_tables(const Octree& t, HostTree& out)
             }
     }
     out.n_virt = n;
-    // by level
-    int64_t count[21] = {};
-    for (int32_t q = 0; q < n; ++q) ++count[out.leaves[out.vblk[2 * q]].level + 2];  // its own level + 1
-    for (int l = 1; l <= 20; ++l) count[l] += count[l - 1];
-    for (int l = 0; l <= 20; ++l) out.vlevel_start[l] = count[l];
-    out.vlist.assign(n, 0);
-    for (int32_t q = 0; q < n; ++q) out.vlist[count[out.leaves[out.vblk[2 * q]].level + 1]++] = q;
     out.ghost_v = out.ghost;
     out.vneed.assign(n, 0);
     // a block reads, of its neighbour in direction d, the three layers next to itself along every axis with d != 0

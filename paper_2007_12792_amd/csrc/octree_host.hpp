@@ -54,15 +54,12 @@ struct HostTree {
     //                              source leaf (Morton order), then octant
     //   ghost_v [nb][27][5]        the ghost table with every coarser entry replaced by {kVirtual, virtual block}
     //   n_virt                     number of virtual blocks
-    //   vlist   [n_virt]           virtual blocks sorted by level (the level of a virtual block is its source leaf's
-    //                              plus one): level l occupies vlist[vlevel_start[l] .. vlevel_start[l+1])
     //   vneed   [n_virt]           which y rows (bits 0..7) and z planes (bits 8..15) of a virtual block any block reads: the
     //                              union, per axis, over the blocks that have it as a neighbour.  The fill writes only
     //                              those (whole x rows of them); the rest of a virtual block is never read.
     BigTable ghost_v;
-    std::vector<int32_t> vblk, vlist, vneed;
+    std::vector<int32_t> vblk, vneed;
     int64_t n_virt = 0;
-    int64_t vlevel_start[21] = {};
     // Work units of the two-block kernel of the 24-field system, in Morton order: the first block of every two
     // leaves that are the lower and upper x child of one parent (they follow each other in storage), and, flagged
     // with kUnitSingle, every other block (a leaf whose x sibling is subdivided).  Every block belongs to exactly one unit.

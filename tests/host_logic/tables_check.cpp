@@ -15,9 +15,9 @@ static int check(const HostTree& t)
 {
     const long nb = static_cast<long>(t.leaves.size());
     // virtual blocks: every coarser entry of the ghost table has become a virtual block that is the right child
-    // octant of the right source leaf; every virtual block is used, listed once per level, one level below its source
+    // octant of the right source leaf; every virtual block is used
     const long nv = static_cast<long>(t.n_virt);
-    if (static_cast<long>(t.vblk.size()) != 2 * nv || static_cast<long>(t.vlist.size()) != nv || t.ghost_v.size() != t.ghost.size())
+    if (static_cast<long>(t.vblk.size()) != 2 * nv || t.ghost_v.size() != t.ghost.size())
         return fail("sizes of the virtual-block tables", -1);
     std::vector<int> used(nv, 0);
     for (long b = 0; b < nb; ++b)
@@ -61,19 +61,8 @@ static int check(const HostTree& t)
         written += 8 * __builtin_popcount(seen[v] & 0xFF) * __builtin_popcount(seen[v] >> 8);
     }
     if (nv) std::printf("points of the virtual blocks that are written: %.1f %%\n", 100.0 * written / (512.0 * nv));
-    std::vector<int> listed(nv, 0);
-    for (int l = 0; l < 20; ++l) {
-        if (t.vlevel_start[l] > t.vlevel_start[l + 1]) return fail("level ranges of the virtual blocks", l);
-        for (int64_t q = t.vlevel_start[l]; q < t.vlevel_start[l + 1]; ++q) {
-            const int32_t v = t.vlist[q];
-            if (v < 0 || v >= nv || static_cast<int>(t.leaves[t.vblk[2 * v]].level) + 1 != l) return fail("level of a listed virtual block", v);
-            ++listed[v];
-        }
-    }
-    if (t.vlevel_start[0] != 0 || t.vlevel_start[20] != nv) return fail("level ranges do not cover the virtual blocks", -1);
     for (long v = 0; v < nv; ++v) {
         if (!used[v]) return fail("a virtual block that nobody reads", v);
-        if (listed[v] != 1) return fail("a virtual block is not listed exactly once", v);
         if (v > 0 && (t.vblk[2 * v] < t.vblk[2 * v - 2] || (t.vblk[2 * v] == t.vblk[2 * v - 2] && t.vblk[2 * v + 1] <= t.vblk[2 * v - 1])))
             return fail("order of the virtual blocks", v);
     }
