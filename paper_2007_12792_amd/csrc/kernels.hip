@@ -499,11 +499,13 @@ __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double*
     zipped[q * BLK + tid] = padded[q * PBLK + ((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)];
 }
 
-// Non-temporal accesses pay where a step's four vectors (or an evaluation's input and output) do not stay in the 256 MB
-// memory-side cache from one launch to the next, and cost where they would have.  Measured, us without / with: steps of
-// the wave system 239 / 261 on 7,134 blocks (234 MB), 360 / 346 on 9,920 (325 MB), 1645 / 1501 on 47,783; steps of Burgers
-// 219 / 238 on 13,700 blocks (224 MB), 302 / 300 on 18,278 (299 MB), 403 / 374 on 23,801; evaluations of DERIVS 36 / 36 on
-// 7,134 blocks (146 MB), 76 / 62 on 13,700 (281 MB), of Burgers 61 / 59 on 23,801 (195 MB).
+// Non-temporal accesses cost where what a launch writes would have been in the memory-side cache for the next one: in a step,
+// whose stages read each other's vectors, below about the size of that cache; after an evaluation, if its result is read
+// next.  They pay everywhere else, and for the launch itself at every size.  Measured, us without / with (kernels.hpp has the
+// sizes at which both are the same): steps of the wave system 231 / 252 on 6,791 blocks (223 MB), 306 / 304 on 8,716 (286 MB),
+// 381 / 362 on 10,550 (346 MB), 1645 / 1501 on 47,783; steps of Burgers 253 / 256 on 15,324 blocks (251 MB), 351 / 332 on 21,120
+// (346 MB); evaluations on new buffers, then alone / with a pass over the result: DERIVS 46.1 / 35.1 on 7,141 blocks (146 MB),
+// 79.6 / 77.0 on 7,813; wave 65.6 / 63.2 and 104.8 / 102.1 on 9,780 (160 MB); Burgers 59.8 / 55.8 and 96.6 / 93.4 on 19,580 (160 MB).
 template <int KIND, int EPI>
 bool streams(int64_t nb)
 {

@@ -23,8 +23,16 @@ struct DeviceTree {
 
 constexpr int32_t kUnitSingle = 1 << 30;   // flag on a unit: one block without a partner
 
-// from which size of a step's four vectors (an evaluation's input and output) kernels write, and where that pays read,
-// non-temporally
+// From which size of a step's four vectors (an evaluation's input and output) kernels write, and where that pays read,
+// non-temporally.  Sizes at which the two ways take the same time, measured on trees around two centres (MB; virtual blocks,
+// which share the 256 MB memory-side cache, not counted):
+//   steps                     wave 286, Burgers 220 to 265, 24 fields 335 to 360
+//   with the centred rule     wave 312, Burgers 259, 24 fields 400
+//   evaluations by themselves: below 100, 24 fields below 130 (non-temporal / plain there 0.78 to 0.99, at 290 MB 0.77 to 0.96)
+//   evaluations, the result read by the next launch: DERIVS 115 to 160, wave 75 to 90, Burgers below 60, 24 fields up to 145
+// The line for steps lies in the middle of these: on its wrong side a step loses at most 4 % (Burgers, 301 MB) and 2 % (24
+// fields with the centred rule, 355 MB).  The line for evaluations lies where none of these loses, also when the result
+// is read next; below it up to 25 % (DERIVS, new buffers each call, result not read) is left.
 constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 180ll << 20;
 
 // workgroup i runs on XCD i mod kXcds; the kernels deal chunks of kChunk consecutive blocks to the XCDs in turn

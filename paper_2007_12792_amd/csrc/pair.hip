@@ -316,9 +316,10 @@ hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& a, 
     if (!a.virt && t.n_virt > 0) return hipErrorInvalidValue;
     const int64_t span = pr::PAIR_CHUNK * NXCD;
     const dim3 grid((unsigned)((t.n_units + span - 1) / span * span));
-    // Written non-temporally from the size at which the vectors do not stay in the memory-side cache, without / with: steps
-    // 481 / 494 us on 708 blocks (278 MB), 505 / 519 on 792 (311 MB), 784 / 755 on 1,135 (446 MB), 51.9 / 50.8 ms on 102,075;
-    // evaluations 102 / 101 on 708 blocks (139 MB), 151 / 148 on 1,093 (215 MB), 225 / 197 on 1,709.
+    // Written non-temporally from the sizes that kernels.hpp explains, without / with: steps 479 / 490 us on 729 blocks (287 MB),
+    // 515 / 518 on 820 (322 MB), 544 / 548 on 883 (347 MB; on another tree 538 / 528 on 876), 559 / 549 on 932 (367 MB), 779 / 756
+    // on 1,086 (427 MB), 51.9 / 50.8 ms on 102,075; with the centred rule 638 / 652 on 904 (356 MB), 862 / 859 on 1,037 (408 MB);
+    // evaluations 100 / 96 on 666 blocks (131 MB), 158 / 154 on 1,044 (205 MB), 178 / 170 on 1,478 (291 MB).
     const bool stream = t.nb * BLK * (int64_t)sizeof(double) * 24 * (ep == kOutZipped ? 2 : 4) > (ep == kOutZipped ? kStreamEvalBytes : kStreamStepBytes);
     switch (ep) {
     case kOutZipped: launch_pairs<kOutZipped>(stream, grid, t, a, s); break;
