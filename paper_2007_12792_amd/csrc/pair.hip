@@ -118,7 +118,8 @@ __device__ __forceinline__ int64_t pair_of_workgroup(int64_t wg)
 // read by several workgroups, stays in the caches; with NTS the results are written so too.  Both need wavefronts whose
 // accesses are whole lines: with lanes over (i, k), where two wavefronts shared every line, they cost 5 and 2 %.
 // (Step, us, before -> now: 102,075 blocks 52,650 -> 50,800; 2,143: 1376 -> 1294; 1,135: 798 -> 752; 792: 525 -> 503.
-// Evaluation: 21,064 blocks 2226 -> 2174; 1,709: 221 -> 202.  Lanes over (i, j) alone: 52,760; with plain stores: 51,880.)
+// Evaluation, each on other buffers than the call before: 21,064 blocks 2245 -> 2190; 4,187: 507 -> 495; 1,709: 220 -> 211 (on
+// the same ones 217 -> 195).  A step with lanes over (i, j) alone: 52,760; with plain stores: 51,880.)
 template <int EPI, bool NTS, bool WIDE>
 __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 {
