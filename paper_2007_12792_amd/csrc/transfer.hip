@@ -11,18 +11,6 @@ namespace {
 
 constexpr int NPT = 8, BLK = 512, NTHREADS = 512;
 
-// spread the low 20 bits of v to every third bit
-__device__ __forceinline__ uint64_t spread3(uint32_t v)
-{
-    uint64_t x = v & 0xfffffu;
-    x = (x | (x << 32)) & 0x001f00000000ffffull;
-    x = (x | (x << 16)) & 0x001f0000ff0000ffull;
-    x = (x | (x << 8)) & 0x100f00f00f00f00full;
-    x = (x | (x << 4)) & 0x10c30c30c30c30c3ull;
-    x = (x | (x << 2)) & 0x1249249249249249ull;
-    return x;
-}
-
 __global__ __launch_bounds__(NTHREADS) void k_transfer(DeviceTransfer t, int nvar, const double* __restrict__ in,
                                                        double* __restrict__ out)
 {
@@ -58,8 +46,8 @@ __global__ __launch_bounds__(NTHREADS) void k_transfer(DeviceTransfer t, int nva
         const ot_leaf T = t.to[b];
         const uint32_t l = T.level;
         const uint32_t px = NPT * T.ix + i, py = NPT * T.iy + j, pz = NPT * T.iz + k;
-        const uint64_t key = l <= 17 ? (spread3(px << (17 - l)) | (spread3(py << (17 - l)) << 1) | (spread3(pz << (17 - l)) << 2))
-                                     : (spread3(px >> (l - 17)) | (spread3(py >> (l - 17)) << 1) | (spread3(pz >> (l - 17)) << 2));
+        const uint64_t key = l <= 17 ? morton_key20(px << (17 - l), py << (17 - l), pz << (17 - l))
+                                     : morton_key20(px >> (l - 17), py >> (l - 17), pz >> (l - 17));
         int64_t lo = first, hi = first + row[2];               // last leaf of [lo, hi) whose key is <= key
         while (hi - lo > 1) {
             const int64_t mid = (lo + hi) >> 1;

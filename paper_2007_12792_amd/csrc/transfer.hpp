@@ -20,8 +20,20 @@ struct HostTransfer {
     int64_t counts[3] = {0, 0, 0};     // target leaves per kind
 };
 
-// Morton key (x least significant) of depth-20 octant coordinates
-uint64_t morton_key20(uint32_t x, uint32_t y, uint32_t z);
+// Morton key (x least significant) of depth-20 octant coordinates, for the plan and for the kernel's search in it
+__host__ __device__ inline uint64_t spread3(uint32_t v)   // the low 20 bits to every third bit
+{
+    uint64_t r = v & 0xfffffu;
+    r = (r | (r << 32)) & 0x001f00000000ffffull;
+    r = (r | (r << 16)) & 0x001f0000ff0000ffull;
+    r = (r | (r << 8)) & 0x100f00f00f00f00full;
+    r = (r | (r << 4)) & 0x10c30c30c30c30c3ull;
+    return (r | (r << 2)) & 0x1249249249249249ull;
+}
+__host__ __device__ inline uint64_t morton_key20(uint32_t x, uint32_t y, uint32_t z)
+{
+    return spread3(x) | (spread3(y) << 1) | (spread3(z) << 2);
+}
 
 // Fills everything from the two leaf lists; OT_E_UNSUPPORTED when a target leaf is two or more
 // levels finer than the source leaf that contains it.

@@ -4,20 +4,6 @@
 #include "transfer.hpp"
 
 namespace octfd {
-
-uint64_t morton_key20(uint32_t x, uint32_t y, uint32_t z)
-{
-    auto spread = [](uint32_t v) {                       // the low 20 bits to every third bit
-        uint64_t r = v & 0xfffffu;
-        r = (r | (r << 32)) & 0x001f00000000ffffull;
-        r = (r | (r << 16)) & 0x001f0000ff0000ffull;
-        r = (r | (r << 8)) & 0x100f00f00f00f00full;
-        r = (r | (r << 4)) & 0x10c30c30c30c30c3ull;
-        return (r | (r << 2)) & 0x1249249249249249ull;
-    };
-    return spread(x) | (spread(y) << 1) | (spread(z) << 2);
-}
-
 namespace {
 
 // is leaf a inside (or equal to) the octant of leaf b
