@@ -351,17 +351,19 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual(DeviceTree tr, int nvar, c
 // some block touches the octant, that block's parent P is a same-level neighbour of L, and the seven neighbours of L on
 // the octant's side are 26-neighbours of P too (per axis they step back towards P where L is off P, and one to either
 // side where it is not); P is subdivided, so the 2:1 balance leaves none of them coarser than L.
-// Then the same three passes as in k_virtual, with nine nodes per line.  A lane gathers the nine nodes of its x lines
-// (81 of them: the first 17 lanes take a second one) into registers, so that the staging array is first written by the x
-// pass: where a line lies is worked out once per virtual block, as two sources (the part inside L's x range and the part
-// beyond it), and shared by all variables of the wavefront.  As in k_virtual, a wavefront owns one variable of one virtual
-// block at a time, with fewer than eight variables a workgroup takes several virtual blocks, and nothing needs a
-// workgroup barrier.
-// (47,783 blocks, 18,256 virtual blocks, two variables: 85 us per call; with one virtual block per workgroup, six of its
-// eight wavefronts idle, and one launch per level it was 154 us.)
+// Then the same three passes as in k_virtual, with nine nodes per line; a wavefront owns one variable of one virtual block at
+// a time.  What differs is how the nodes get to the x pass:
+//   k_virtual_centred       five variables or more: the eight wavefronts of a workgroup share one virtual block.  Its 729 sources
+//       are worked out once by all of them, and a wavefront requests them in the order of the storage, a few lines per load,
+//       through its staging array.
+//   k_virtual_centred_few   up to four: as in k_virtual a workgroup takes several virtual blocks, and 729 sources for so few
+//       variables would cost more than the loads.  A lane gathers the nine nodes of its x lines (81 of them: the first 17 lanes
+//       take a second one) into registers; where a line lies is worked out as two sources, the part inside L's x range and the
+//       part beyond it.  Nothing needs a workgroup barrier.
+// (us per call of k_virtual_centred / _few on 21,064 blocks, 11,056 virtual blocks: 1 variable 64 / 24, 2: 80 / 52, 3: 96 / 80, 4:
+// 113 / 106, 5: 133 / 136, 6: 150 / 159, 8: 181 / 211; 24 variables 452, with the nodes gathered by lines 584; 102,075 blocks, 24
+// variables: 1321, by lines 1699.  One launch per level, one virtual block per workgroup: 81, 98, 118, 130, 153, 166, 195, 490; 1388.)
 constexpr int CN = 9;                                // coarse nodes per axis
-constexpr int CPS = CN * NPT;                        // plane stride of a wavefront's staging array (lines of 8 after the x pass): 72 = 8 (mod 32)
-constexpr int CSTAGE = CN * CPS;
 
 // the eight fine values of a line with nine nodes v (node n is coarse node 4 o - 2 + n): even f passes node c0 through,
 // odd f takes nodes c0 - 2 .. c0 + 3 with the centred weights, acc = w0 v, then five fma (as centred_line)
@@ -376,6 +378,111 @@ __device__ __forceinline__ void fine_line_centred(const double (&v)[CN], double 
         r[2 * n + 1] = acc;
     }
 }
+
+// y and z passes of a wavefront's staging array A, in which the x pass has left lines of eight fine values, rows RSTR and
+// planes PSTR apart; writes the rows and planes in `need` to the virtual block at `out` (the lane's value of its plane 0)
+template <int RSTR, int PSTR>
+__device__ __forceinline__ void centred_yz(double* A, double* out, int need, int lane)
+{
+    double c[CN], r[8];
+    // y pass: lines (cz, tx), 72 of them; in place
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int line = lane + 64 * h;
+        if (line < CN * 8) {
+            double* col = A + (line >> 3) * PSTR + (line & 7);
+#pragma unroll
+            for (int m = 0; m < CN; ++m) c[m] = col[m * RSTR];
+            fine_line_centred(c, r);
+#pragma unroll
+            for (int m = 0; m < 8; ++m) col[m * RSTR] = r[m];
+        }
+    }
+    __builtin_amdgcn_wave_barrier();
+    // z pass: lines (ty, tx) = (hi, lo)
+    const int hi = lane >> 3, lo = lane & 7;
+#pragma unroll
+    for (int m = 0; m < CN; ++m) c[m] = A[m * PSTR + hi * RSTR + lo];
+    fine_line_centred(c, r);
+#pragma unroll
+    for (int m = 0; m < 8; ++m)
+        if (((need >> hi) & 1) && ((need >> (8 + m)) & 1)) out[m * (NPT * NPT)] = r[m];
+    __builtin_amdgcn_wave_barrier();                 // the next variable overwrites the array
+}
+
+constexpr int kFewVariables = 4;                     // up to here k_virtual_centred_few
+constexpr int CRS = CN, CPS = CN * CN + 7;           // row and plane stride of the staging array of nodes: 88 = 24 (mod 32)
+__global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int nvar, const double* __restrict__ zipped,
+                                                              double* __restrict__ virt)
+{
+    __shared__ double staging[8][CN * CPS];
+    __shared__ uint32_t plan[CN * CN * CN];          // byte offsets of the 729 sources
+    __shared__ int32_t gt[27 * 5];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int64_t q = block_of_workgroup(blockIdx.x), nb = tr.nb;
+    if (q >= tr.n_virt) return;                      // uniform over the workgroup
+    const int64_t leaf = tr.vblk[2 * q];
+    const int oct = tr.vblk[2 * q + 1];
+    const int need = tr.vneed[q];                    // y rows and z planes that any block reads
+    if (tid < 27 * 5) gt[tid] = tr.ghost_v[leaf * (27 * 5) + tid];
+    __syncthreads();
+    for (int p = tid; p < CN * CN * CN; p += NTHREADS) {
+        const int nz = p / (CN * CN), r = p - nz * CN * CN, ny = r / CN, nx = r - ny * CN;
+        // position in L's padded block: coarse node 4 o - 2 + n, shifted by the three ghost layers
+        const int ii = 4 * (oct & 1) + 1 + nx, jj = 4 * ((oct >> 1) & 1) + 1 + ny, kk = 4 * (oct >> 2) + 1 + nz;
+        const int rx = ii < PAD ? 0 : (ii < PAD + NPT ? 1 : 2);
+        const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2);
+        const int rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
+        const int lx = ii - PAD + (1 - rx) * NPT, ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
+        plan[p] = ghost_source(&gt[(rz * 9 + ry * 3 + rx) * 5], rx, ry, rz, lx, ly, lz);   // the centre entry is L itself
+    }
+    __syncthreads();
+    double* A = staging[wave];
+    const int64_t in_stride = nb * BLK, out_stride = tr.n_virt * BLK;
+    double* out = virt + q * BLK + lane;
+    // this lane's share of the gather: elements lane, lane + 64, ... of the 729 (the lanes past it repeat the last one)
+    constexpr int NG = (CN * CN * CN + 63) / 64;     // 12
+    uint32_t off[NG];
+    int dst[NG];
+#pragma unroll
+    for (int m = 0; m < NG; ++m) {
+        const int p = min(lane + 64 * m, CN * CN * CN - 1);
+        off[m] = plan[p];
+        dst[m] = p + 7 * (p / (CN * CN));
+    }
+    double nxt[NG];
+    auto gather = [&](int v) {
+        const double* base = zipped + v * in_stride;
+#pragma unroll
+        for (int m = 0; m < NG; ++m) nxt[m] = ldg(base, off[m]);
+    };
+    if (wave < nvar) gather(wave);
+#pragma unroll 1
+    for (int v = wave; v < nvar; v += 8) {
+#pragma unroll
+        for (int m = 0; m < NG; ++m) A[dst[m]] = nxt[m];
+        if (v + 8 < nvar) gather(v + 8);
+        __builtin_amdgcn_wave_barrier();
+        // x pass: lines (cz, cy), 81 of them; in place (a lane writes the first eight positions of the row it has read)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int line = lane + 64 * h;
+            if (line < CN * CN) {
+                double* row = A + line * CRS + 7 * (line / CN);
+                double c[CN], r[8];
+#pragma unroll
+                for (int m = 0; m < CN; ++m) c[m] = row[m];
+                fine_line_centred(c, r);
+#pragma unroll
+                for (int m = 0; m < 8; ++m) row[m] = r[m];
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        centred_yz<CRS, CPS>(A, out + v * out_stride, need, lane);
+    }
+}
+
+constexpr int FPS = CN * NPT;                        // plane stride of the staging array behind the x pass, rows of 8: 72 = 8 (mod 32)
 
 // Where the nine nodes of an x line come from, as byte offsets into one variable's zipped array: nodes 0..3, 4..7 of the
 // octant of L's size that holds the line (`lo`, `hi`: of nodes 0 and 4; they are two leaves where that octant is
@@ -411,14 +518,13 @@ __device__ __forceinline__ void load_line(double (&v)[CN], const double* base, c
     }
 }
 
-__global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int nvar, const double* __restrict__ zipped,
-                                                              double* __restrict__ virt)
+__global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr, int nvar, const double* __restrict__ zipped,
+                                                                  double* __restrict__ virt)
 {
-    __shared__ double staging[8][CSTAGE];
+    __shared__ double staging[8][CN * FPS];
     __shared__ int32_t rows[8][27 * 5];              // L's table row, a copy for each wavefront
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int nv = nvar < 8 ? nvar : 8, per = 8 / nv;
-    const int sub = wave / nv, v0 = wave - sub * nv;
+    const int per = 8 / nvar, sub = wave / nvar, v = wave - sub * nvar;      // virtual blocks per workgroup, which one, variable
     const int64_t q = block_of_workgroup(blockIdx.x) * per + sub, nb = tr.nb;
     if (sub >= per || q >= tr.n_virt) return;        // uniform over the wavefront; the kernel has no workgroup barrier
     const int64_t leaf = tr.vblk[2 * q];
@@ -436,58 +542,28 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int
     const LineSource s0 = line_source(row, ox, 4 * oy + 1 + line0 % CN, 4 * oz + 1 + line0 / CN);
     const LineSource s1 = line_source(row, ox, 4 * oy + 1 + line1 % CN, 4 * oz + 1 + line1 / CN);
     double* A = staging[wave];
-    const int hi = lane >> 3, lo = lane & 7;
     const int64_t in_stride = nb * BLK, out_stride = tr.n_virt * BLK;
     double* out = virt + q * BLK + lane;
-    double n0[CN], n1[CN];
-    auto gather = [&](int v) {
-        const double* base = zipped + v * in_stride;
-        if (ox) {                                    // uniform
-            load_line<1>(n0, base, s0);
-            if (second) load_line<1>(n1, base, s1);
-        } else {
-            load_line<0>(n0, base, s0);
-            if (second) load_line<0>(n1, base, s1);
-        }
-    };
-    gather(v0);
-#pragma unroll 1
-    for (int v = v0; v < nvar; v += nv) {
-        double c[CN], r[8];
-        // x pass: lines (cz, cy), from registers
-        fine_line_centred(n0, r);
-#pragma unroll
-        for (int m = 0; m < 8; ++m) A[line0 * NPT + m] = r[m];
-        if (second) {
-            fine_line_centred(n1, r);
-#pragma unroll
-            for (int m = 0; m < 8; ++m) A[line1 * NPT + m] = r[m];
-        }
-        if (v + nv < nvar) gather(v + nv);
-        __builtin_amdgcn_wave_barrier();
-        // y pass: lines (cz, tx), 72 of them; in place
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int line = lane + 64 * h;
-            if (line < CN * 8) {
-                double* col = A + (line >> 3) * CPS + (line & 7);
-#pragma unroll
-                for (int m = 0; m < CN; ++m) c[m] = col[m * NPT];
-                fine_line_centred(c, r);
-#pragma unroll
-                for (int m = 0; m < 8; ++m) col[m * NPT] = r[m];
-            }
-        }
-        __builtin_amdgcn_wave_barrier();
-        // z pass: lines (ty, tx) = (hi, lo)
-#pragma unroll
-        for (int m = 0; m < CN; ++m) c[m] = A[m * CPS + lane];
-        fine_line_centred(c, r);
-#pragma unroll
-        for (int m = 0; m < 8; ++m)
-            if (((need >> hi) & 1) && ((need >> (8 + m)) & 1)) out[v * out_stride + m * (NPT * NPT)] = r[m];
-        __builtin_amdgcn_wave_barrier();                         // the next variable's x pass overwrites the array
+    const double* base = zipped + v * in_stride;
+    double n0[CN], n1[CN], r[8];
+    if (ox) {                                        // uniform
+        load_line<1>(n0, base, s0);
+        if (second) load_line<1>(n1, base, s1);
+    } else {
+        load_line<0>(n0, base, s0);
+        if (second) load_line<0>(n1, base, s1);
     }
+    // x pass: lines (cz, cy), from registers
+    fine_line_centred(n0, r);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) A[line0 * NPT + m] = r[m];
+    if (second) {
+        fine_line_centred(n1, r);
+#pragma unroll
+        for (int m = 0; m < 8; ++m) A[line1 * NPT + m] = r[m];
+    }
+    __builtin_amdgcn_wave_barrier();
+    centred_yz<NPT, FPS>(A, out + v * out_stride, need, lane);
 }
 
 __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double* __restrict__ padded, double* __restrict__ zipped)
@@ -574,8 +650,12 @@ hipError_t launch_virtual(const DeviceTree& t, int nvar, const double* zipped, d
 hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* zipped, double* virt, hipStream_t s)
 {
     if (t.n_virt <= 0 || nvar <= 0) return hipSuccess;
-    const int per = 8 / (nvar < 8 ? nvar : 8);       // virtual blocks per workgroup, as in the kernel
-    hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+    if (nvar > kFewVariables) {
+        hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks(t.n_virt)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+    } else {
+        const int per = 8 / nvar;                    // virtual blocks per workgroup, as in the kernel
+        hipLaunchKernelGGL(k_virtual_centred_few, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+    }
     return hipGetLastError();
 }
 

@@ -82,14 +82,14 @@ def test_two_block_kernel_fits_one_compute_unit(usage, name):
 
 
 def test_every_kernel_is_looked_at(usage):
-    names = ["k_rhs", "k_rhs_stream", "k_rhs_pair", "k_pair_stream", "k_pair_wide", "k_unzip", "k_virtual", "k_virtual_centred", "k_zip"]
+    names = ["k_rhs", "k_rhs_stream", "k_rhs_pair", "k_pair_stream", "k_pair_wide", "k_unzip", "k_virtual", "k_virtual_centred", "k_virtual_centred_few", "k_zip"]
     other = [n for n in usage if not any(re.search(r"\d%s[IE]" % k, n) for k in names)]
     assert not other, other
 
 
 def test_fill_kernels_fit_three_workgroups_per_compute_unit(usage):
     names = [n for n in usage if "k_unzip" in n or "k_virtual" in n]
-    assert len(names) == 3
+    assert len(names) == 4
     for n in names:
         assert usage[n]["LDS Size [bytes/block]"] <= 160 * 1024 // 3, n
         assert usage[n]["VGPRs Spill"] == 0, n
