@@ -482,6 +482,17 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int
     }
 }
 
+// Virtual blocks per workgroup of k_virtual_centred_few: as its wavefronts have variables for, halved as long as the 256
+// compute units can hold all workgroups at once, three each by their LDS (us, step with the centred rule, always 8 or 4 / as here:
+// Burgers 44.5 / 36.8 on 568 blocks, 200 virtual ones, 49.5 / 44.2 on 855, 760 virtual, 54.5 / 52.2 on 1,310, 1,248 virtual; wave
+// system 54.0 / 46.5, 64.1 / 60.8, 85.7 / 81.8; with half as many workgroups 45.1 and 62.7 on 855 blocks, with more than
+// are resident 77.9 instead of 68.5 on 2,220, 1,776 virtual).
+inline int centred_per_workgroup(int64_t n_virt, int nvar)
+{
+    int per = 8 / nvar;
+    while (per > 1 && n_virt <= 3 * 256 * (int64_t)(per / 2)) per /= 2;
+    return per;
+}
 constexpr int FPS = CN * NPT;                        // plane stride of the staging array behind the x pass, rows of 8: 72 = 8 (mod 32)
 
 // Where the nine nodes of an x line come from, as byte offsets into one variable's zipped array: nodes 0..3, 4..7 of the
@@ -518,13 +529,13 @@ __device__ __forceinline__ void load_line(double (&v)[CN], const double* base, c
     }
 }
 
-__global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr, int nvar, const double* __restrict__ zipped,
+__global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr, int nvar, int per, const double* __restrict__ zipped,
                                                                   double* __restrict__ virt)
 {
     __shared__ double staging[8][CN * FPS];
     __shared__ int32_t rows[8][27 * 5];              // L's table row, a copy for each wavefront
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int per = 8 / nvar, sub = wave / nvar, v = wave - sub * nvar;      // virtual blocks per workgroup, which one, variable
+    const int sub = wave / nvar, v = wave - sub * nvar;         // which of the workgroup's `per` virtual blocks, variable
     const int64_t q = block_of_workgroup(blockIdx.x) * per + sub, nb = tr.nb;
     if (sub >= per || q >= tr.n_virt) return;        // uniform over the wavefront; the kernel has no workgroup barrier
     const int64_t leaf = tr.vblk[2 * q];
@@ -653,8 +664,8 @@ hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* z
     if (nvar > kFewVariables) {
         hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks(t.n_virt)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
     } else {
-        const int per = 8 / nvar;                    // virtual blocks per workgroup, as in the kernel
-        hipLaunchKernelGGL(k_virtual_centred_few, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+        const int per = centred_per_workgroup(t.n_virt, nvar);
+        hipLaunchKernelGGL(k_virtual_centred_few, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, per, zipped, virt);
     }
     return hipGetLastError();
 }

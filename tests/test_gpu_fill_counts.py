@@ -1,4 +1,4 @@
-"""The fills of the virtual blocks with every number of variables at which they share a workgroup differently (1..7: a
+"""The fills of the virtual blocks with every number of variables at which they share a workgroup differently (few: a
 wavefront takes one variable of one of several virtual blocks; 8: one each; more: several), against the oracle; and the
 properties of balanced trees that let the centred fill run in one launch and leave no workgroup of a fill partly filled."""
 import numpy as np
@@ -47,6 +47,22 @@ def test_unzip_with_any_number_of_variables(orc, dev, nvar, centred):
     (tg.unzip_centred if centred else tg.unzip)(torch.from_numpy(u).to(dev), got)
     torch.cuda.synchronize()
     assert_close(got.cpu().numpy(), to.unzip_centred(u) if centred else to.unzip(u), "%d variables" % nvar)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nvar", [1, 2, 3, 4])
+@pytest.mark.parametrize("radii,virtual", [([60000, 40000, 0], 304), ([170000, 105000, 60000], 1488), ([110000, 60000, 40000], 2064), ([200000, 130000, 80000], 3888)])
+def test_centred_fill_with_every_number_of_virtual_blocks_per_workgroup(orc, dev, nvar, radii, virtual):
+    """One variable: 1, 2, 4 and 8 virtual blocks per workgroup (halved while 768 workgroups hold them all); two: 1, 2, 4 and 4."""
+    pts = np.array([[500000, 520000, 540000]] if virtual < 2000 else [[300000, 520000, 540000], [800000, 100000, 200000]], np.uint32)
+    p = dict(lmin=3, lmax=5 if virtual == 304 else 6, pts_q20=pts, radius_q20=np.array(radii, np.uint32))
+    to, tg = orc.Tree.build(**p), octfd.Tree.build(**p)
+    assert virtual_blocks(tg) == virtual
+    u = np.random.default_rng(nvar).standard_normal((nvar, to.n, 8, 8, 8))
+    got = dev_empty((nvar, tg.n, 14, 14, 14), dev)
+    tg.unzip_centred(torch.from_numpy(u).to(dev), got)
+    torch.cuda.synchronize()
+    assert_close(got.cpu().numpy(), to.unzip_centred(u), "%d variables, %d virtual blocks" % (nvar, virtual))
 
 
 @pytest.mark.parametrize("seed", range(6))
