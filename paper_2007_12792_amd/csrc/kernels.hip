@@ -190,9 +190,12 @@ __global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs
 // read again here and would otherwise push the ghost rows out of the L2.
 // A workgroup takes every `stride`-th variable of a block.  Normally that is all of them, chunks of 16 consecutive blocks
 // dealt to the XCDs in turn; on small trees the variables are split so that the chip is full (unzip_stride).
-// (21,064 blocks, 24 variables: 4.24 -> 3.68 ms; 47,783 blocks, two variables: 807 -> 664 us; 792 blocks, 24 variables:
-// 160 -> 142 us.  Before, a thread copied six points 512 apart from memory to memory, eight workgroups per block.  Chunks of
-// 8 / 64 / 128 blocks: 3.71 / 3.71 / 3.79 ms; plain stores +8 %; two buffers in LDS with one barrier per variable +1 to 7 %.)
+// (21,064 blocks, 24 variables: 4.24 -> 3.68 ms; 47,783 blocks, two variables: 807 -> 664 us.  Before, a thread copied six
+// points 512 apart from memory to memory, eight workgroups per block, one variable of eight each.  Chunks of
+// 8 / 64 / 128 blocks: 3.71 / 3.71 / 3.79 ms; plain stores +8 %; two buffers in LDS with one barrier per variable +1 to 7 %.
+// Where the output stays in the memory-side cache, the call by itself is slower than that with four variables or more: 24
+// on 512 blocks 52 -> 61 us, 8 on 1,513 blocks 69 -> 78, 4 on 3,004 76 -> 79.  The launch that reads the output gains more:
+// unzip, rhs_eval and zip of the 24-field system 241 -> 225 us on 512 blocks, 420 -> 404 on 820, 757 -> 715 on 1,513.)
 // Workgroups per block: 1,024 run at a time, and four times as many keep the last wave short; but at least two variables each,
 // for which the sources are worked out once (792 blocks, 24 variables, 1 / 2 / 6 / 12 per block: 167 / 161 / 154 / 157 us; 834
 // blocks, two variables, 1 / 2 per block: 12.4 / 14.2 us).
