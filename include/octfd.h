@@ -207,7 +207,8 @@ int rk_step_static(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *p
  * composition.  It differs from rk_step only in how the virtual blocks (see rhs_eval_zipped) are
  * filled before each stage: with the centred stencils, each from the part of its source leaf's
  * padded block that it needs (gathered from the zipped vector).  Same stage kernels, same workspace (rk_centred_workspace_bytes
- * equals rk_workspace_bytes), and within a few per cent of rk_step's time. */
+ * equals rk_workspace_bytes).  It takes 2 to 11 % longer than rk_step for the 24-field system, 11 to 28 % for
+ * the others, depending on the tree. */
 int unzip_centred(const ot_tree *tree, int nvar, const double *zipped_dev, double *padded_dev, void *hip_stream);
 int rk_centred_workspace_bytes(const ot_tree *tree, ot_rhs_kind kind, size_t *bytes);
 int rk_step_centred(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *params, double dt,
