@@ -1,4 +1,5 @@
-// gfx950 kernel of the 24-field right-hand side on zipped input: TWO sibling blocks per workgroup.
+// gfx950 kernel of the 24-field right-hand side on zipped input: TWO sibling blocks per workgroup, a thread per point.  Nearly every
+// call runs the kernel with two points per thread instead (brick.hip, bricks_apply()).
 //
 // Two leaves that are x-neighbours inside one parent follow each other in storage.  One workgroup of
 // 1,024 threads (16 wavefronts, one whole compute unit) owns such a pair as a single 16 x 8 x 8 brick with a
@@ -331,6 +332,7 @@ hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& a, 
     const int64_t bytes = t.nb * BLK * (int64_t)sizeof(double) * 24 * (ep == kOutZipped ? 2 : 4);
     const bool stream = bytes > (ep == kOutZipped ? kStreamEvalBytes : kStreamStepBytes);
     const bool past = bytes > kOperandStepBytes;
+    if (bricks_apply(t, a)) return launch_rhs_bricks(t, ep, a, past, stream, s);
     switch (ep) {
     case kOutZipped: launch_pairs<kOutZipped>(past, stream, grid, t, a, s); break;
     case kRkFirst: launch_pairs<kRkFirst>(past, stream, grid, t, a, s); break;
