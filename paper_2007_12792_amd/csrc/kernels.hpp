@@ -31,9 +31,13 @@ constexpr int32_t kUnitSingle = 1 << 30;   // flag on a unit: one block without 
 //   evaluations by themselves: below 100, 24 fields below 130 (non-temporal / plain there 0.78 to 0.99, at 290 MB 0.77 to 0.96)
 //   evaluations, the result read by the next launch: DERIVS 115 to 160, wave 75 to 90, Burgers below 60, 24 fields up to 145
 // The line for steps lies in the middle of these: on its wrong side a step loses at most 4 % (Burgers, 301 MB) and 2 % (24
-// fields with the centred rule, 355 MB).  The line for evaluations lies where none of these loses, also when the result
-// is read next; below it up to 25 % (DERIVS, new buffers each call, result not read) is left.
-constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 180ll << 20;
+// fields with the centred rule, 355 MB).  The line for evaluations lies at the top of the last range.  New buffers each call,
+// plain / non-temporal, us, by themselves and with a reduction over the result behind each:
+//   DERIVS     59 MB 20.4 / 17.3, 31.1 / 31.1    144 MB 47.5 / 34.0, 64.5 / 66.9    158 MB 51.0 / 36.5, 69.4 / 71.6    189 MB 58.4 / 42.5, 79.6 / 82.0
+//   wave      151 MB 64.6 / 60.1, 74.6 / 76.2    177 MB 74.2 / 69.6, 85.3 / 87.4    Burgers 139 MB 55.0 / 50.5, 65.5 / 66.0
+//   24 fields 110 MB 82.6 / 79.4, 93.3 / 95.7    154 MB 95.1 / 90.9, 106.5 / 108.0    171 MB 98.7 / 95.8, 113.6 / 114.5
+// so above it a caller who reduces the result at once pays up to 3 %, and any other gains 3 to 28 %.
+constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 160000000;
 
 // workgroup i runs on XCD i mod kXcds; the kernels deal chunks of kChunk consecutive blocks to the XCDs in turn
 constexpr int kSchedChunk = 16;
