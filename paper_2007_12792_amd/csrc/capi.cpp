@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <cstring>
 #include <new>
 
 #include "kernels.hpp"
@@ -88,26 +89,42 @@ int ensure_device(const ot_tree* t)
     if (ndev <= 0) return OT_E_NODEVICE;
     int dev = 0;
     if ((e = hipGetDevice(&dev)) != hipSuccess) return hip_fail(e);
-    // one allocation for all tables, each part 256-byte aligned
+    // one allocation for all tables, each part 256-byte aligned; behind what is copied from the host, in one go, the ghost table, which
+    // the device makes from it
     const HostTree& h = t->host;
-    constexpr int kParts = 5;
-    auto ibytes = [](const auto& v) { return v.size() * sizeof(int32_t); };
-    const void* part[kParts] = {h.leaves.data(), h.ghost_v.data(), h.vblk.data(), h.units.data(), h.vneed.data()};
-    const size_t bytes[kParts] = {h.leaves.size() * sizeof(ot_leaf), ibytes(h.ghost_v), ibytes(h.vblk), ibytes(h.units), ibytes(h.vneed)};
+    constexpr int kParts = 9;
+    auto ibytes = [](const auto& v) { return v.size() * sizeof(v[0]); };
+    const void* part[kParts] = {h.leaves.data(), h.vblk.data(), h.units.data(), h.vneed.data(), h.node.data(), h.nbr.data(), h.parent.data(),
+                                h.first_virt.data(), h.virt_mask.data()};
+    const size_t bytes[kParts] = {ibytes(h.leaves), ibytes(h.vblk), ibytes(h.units), ibytes(h.vneed), ibytes(h.node), ibytes(h.nbr), ibytes(h.parent),
+                                  ibytes(h.first_virt), ibytes(h.virt_mask)};
     size_t off[kParts + 1] = {0};
     for (int i = 0; i < kParts; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
+    const size_t table = h.leaves.size() * kDirs * kEntry * sizeof(int32_t);
+    char* staging = new (std::nothrow) char[off[kParts]];
+    if (!staging) return OT_E_NOMEM;
+    for (int i = 0; i < kParts; ++i)
+        if (bytes[i]) std::memcpy(staging + off[i], part[i], bytes[i]);
     char* base = nullptr;
-    if ((e = hipMalloc(reinterpret_cast<void**>(&base), off[kParts])) != hipSuccess) return hip_fail(e);
-    for (int i = 0; i < kParts && e == hipSuccess; ++i)
-        if (bytes[i]) e = hipMemcpy(base + off[i], part[i], bytes[i], hipMemcpyHostToDevice);
+    e = hipMalloc(reinterpret_cast<void**>(&base), off[kParts] + table);
+    if (e != hipSuccess) {
+        delete[] staging;
+        return hip_fail(e);
+    }
+    e = hipMemcpy(base, staging, off[kParts], hipMemcpyHostToDevice);
+    delete[] staging;
+    auto ints = [&](int i) { return reinterpret_cast<const int32_t*>(base + off[i]); };
+    int32_t* ghost_v = reinterpret_cast<int32_t*>(base + off[kParts]);
+    const TableSource src{ints(4), ints(5), ints(6), ints(7), reinterpret_cast<const uint8_t*>(base + off[8])};
+    if (e == hipSuccess) e = launch_ghost_table(src, static_cast<int64_t>(h.leaves.size()), ghost_v, nullptr);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);              // the calls that read it may be on any stream
     if (e != hipSuccess) {
         (void)hipFree(base);
         return hip_fail(e);
     }
-    auto ints = [&](int i) { return reinterpret_cast<const int32_t*>(base + off[i]); };
     t->d_base = base;
     t->dev = DeviceTree{reinterpret_cast<const ot_leaf*>(base + off[0]), static_cast<int64_t>(h.leaves.size()),
-                        ints(1), ints(2), h.n_virt, ints(3), static_cast<int64_t>(h.units.size()), ints(4)};
+                        ghost_v, ints(1), h.n_virt, ints(2), static_cast<int64_t>(h.units.size()), ints(3)};
     t->device = dev;
     return resolve_static_workspace(dev);
 }
@@ -126,12 +143,20 @@ int ensure_device(ot_transfer* p)
     const size_t nt = h.table.size() * sizeof(int32_t), nf = h.from.size() * sizeof(ot_leaf);
     const size_t nk = h.from_keys.size() * sizeof(uint64_t), no = h.to.size() * sizeof(ot_leaf);
     const size_t of = up(nt), ok = of + up(nf), oo = ok + up(nk);
+    char* staging = new (std::nothrow) char[oo + no];
+    if (!staging) return OT_E_NOMEM;
+    std::memcpy(staging, h.table.data(), nt);
+    std::memcpy(staging + of, h.from.data(), nf);
+    std::memcpy(staging + ok, h.from_keys.data(), nk);
+    std::memcpy(staging + oo, h.to.data(), no);
     char* base = nullptr;
-    if ((e = hipMalloc(reinterpret_cast<void**>(&base), oo + no)) != hipSuccess) return hip_fail(e);
-    e = hipMemcpy(base, h.table.data(), nt, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + of, h.from.data(), nf, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + ok, h.from_keys.data(), nk, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(base + oo, h.to.data(), no, hipMemcpyHostToDevice);
+    e = hipMalloc(reinterpret_cast<void**>(&base), oo + no);
+    if (e != hipSuccess) {
+        delete[] staging;
+        return hip_fail(e);
+    }
+    e = hipMemcpy(base, staging, oo + no, hipMemcpyHostToDevice);
+    delete[] staging;
     if (e != hipSuccess) {
         (void)hipFree(base);
         return hip_fail(e);
@@ -182,7 +207,7 @@ int octree_build(const ot_build_params* params, ot_tree** out)
     ot_tree* t = new (std::nothrow) ot_tree;
     if (!t) return OT_E_NOMEM;
     int rc;
-    try { rc = build_tree(*params, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
+    try { rc = plan_tree(*params, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
     if (rc != OT_OK) { delete t; return rc; }
     *out = t;
     return OT_OK;
@@ -196,7 +221,7 @@ int octree_from_leaves(const ot_leaf* leaves, size_t n, uint32_t pad, ot_tree** 
     ot_tree* t = new (std::nothrow) ot_tree;
     if (!t) return OT_E_NOMEM;
     int rc;
-    try { rc = tree_from_leaves(leaves, n, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
+    try { rc = plan_tree_from_leaves(leaves, n, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
     if (rc != OT_OK) { delete t; return rc; }
     *out = t;
     return OT_OK;
@@ -218,8 +243,8 @@ int octree_get_leaves(const ot_tree* tree, ot_leaf* out, size_t cap)
 
 int octree_get_ghost_table(const ot_tree* tree, int32_t* out, size_t cap)
 {
-    if (!tree || !out || cap < tree->host.ghost.size()) return OT_E_BADARG;
-    for (size_t i = 0; i < tree->host.ghost.size(); ++i) out[i] = tree->host.ghost[i];
+    if (!tree || !out || cap < tree->host.leaves.size() * kDirs * kEntry) return OT_E_BADARG;
+    write_ghost_table(tree->host, false, out);
     return OT_OK;
 }
 

@@ -5,6 +5,7 @@
 #include <cstdint>
 
 #include "octfd.h"
+#include "table_rows.hpp"
 
 namespace octfd {
 
@@ -63,6 +64,8 @@ struct RhsArgs {
     double sigma;       // Kreiss-Oliger strength
 };
 
+// the ghost table of nb blocks on the device, coarser neighbours as virtual blocks
+hipError_t launch_ghost_table(const TableSource& t, int64_t nb, int32_t* ghost_v, hipStream_t s);
 // padded [nvar][nb][2744] from zipped and its virtual blocks (filled by one of the two calls below: which one decides
 // the ghost rule)
 hipError_t launch_unzip(const DeviceTree& t, int nvar, const double* zipped, const double* virt, double* padded, hipStream_t s);

@@ -7,8 +7,9 @@
 // every node that has children exist as nodes.  (A leaf with a neighbour two levels coarser has a parent with a neighbour
 // octant inside that leaf; the other way round, follow the children on the side of the missing octant down to a leaf.)  So
 // only the nodes with children, an eighth of all, are looked at, and the neighbours of a child are children of its
-// parent's neighbours, found without a descent from the root.  (Tree of 27,756 blocks with its tables, these in huge
-// pages: 23 -> 4.8 ms; 26 descents from the root per leaf for the balance and 27 for its table row took most of it.)
+// parent's neighbours, found without a descent from the root.  The rows of the ghost table follow from those neighbours and are
+// made where they are needed (table_rows.hpp).  (Tree of 27,756 blocks: 4.8 -> 1.0 ms; with 26 descents
+// from the root per leaf for the balance and 27 for its row of the table 23.)
 #include "octree_host.hpp"
 
 #include "kernels.hpp"
@@ -25,12 +26,14 @@ struct Node {
     int32_t first_child;  // >= 0 internal, kLeaf, or kUnset (from_leaves: nothing placed here yet)
     uint32_t level, ix, iy, iz;
     int32_t leaf_id;
+    int32_t parent, row;  // row: of a node with children, its place in Octree::inner
 };
 
 struct Octree {
     std::vector<Node> nodes;
+    std::vector<int32_t> inner;   // the nodes with children, parents first
 
-    Octree() { nodes.push_back(Node{kLeaf, 0, 0, 0, 0, -1}); }
+    Octree() { nodes.push_back(Node{kLeaf, 0, 0, 0, 0, -1, -1, -1}); }
 
     // turn node n into an internal node with eight children in state `child_state`
     int32_t split(int32_t n, int32_t child_state = kLeaf)
@@ -39,7 +42,9 @@ struct Octree {
         const int32_t first = static_cast<int32_t>(nodes.size());
         for (uint32_t c = 0; c < 8; ++c)
             nodes.push_back(Node{child_state, p.level + 1, 2 * p.ix + (c & 1), 2 * p.iy + ((c >> 1) & 1),
-                                 2 * p.iz + ((c >> 2) & 1), -1});
+                                 2 * p.iz + ((c >> 2) & 1), -1, n, -1});
+        nodes[n].row = static_cast<int32_t>(inner.size());
+        inner.push_back(n);
         nodes[n].first_child = first;
         return first;
     }
@@ -48,15 +53,6 @@ struct Octree {
     {
         const uint32_t sh = l - node_level - 1;
         return (((z >> sh) & 1) << 2) | (((y >> sh) & 1) << 1) | ((x >> sh) & 1);
-    }
-
-    // deepest existing node on the path from the root towards octant (l; x, y, z), depth <= l
-    int32_t descend(uint32_t l, uint32_t x, uint32_t y, uint32_t z) const
-    {
-        int32_t n = 0;
-        while (nodes[n].first_child >= 0 && nodes[n].level < l)
-            n = nodes[n].first_child + static_cast<int32_t>(child_slot(l, x, y, z, nodes[n].level));
-        return n;
     }
 };
 
@@ -86,23 +82,39 @@ bool near_seed(const Node& o, const ot_build_params& p)
     return false;
 }
 
-// Splits leaves until every node with children has its 26 neighbour octants, finest level first: what a node at level l
-// asks for is split at coarser levels only.  inner[l]: the nodes of level l that have children.
-void balance(Octree& t, std::vector<int32_t> (&inner)[21])
+// child_step() as a table
+struct ChildSteps {
+    ChildStep at[8][kDirs];
+    ChildSteps()
+    {
+        for (int c = 0; c < 8; ++c)
+            for (int dir = 0; dir < kDirs; ++dir) at[c][dir] = child_step(c, dir);
+    }
+};
+
+// Neighbours of every node with children (27, itself in the middle; the root's are the root), in the order of Octree::inner.  A
+// missing one lies in a leaf: that leaf is split (and joins the end of the list) or, with may_split = false, the tree is not
+// balanced.  A node's parent comes before it, so the parent's neighbours are known and have children by then.
+int link_neighbours(Octree& t, bool may_split, std::vector<int32_t>& nbr)
 {
-    for (int l = 20; l >= 1; --l) {
-        const uint32_t mask = (1u << l) - 1;
-        for (size_t q = 0; q < inner[l].size(); ++q) {
-            const Node o = t.nodes[inner[l][q]];
-            for (int dir = 0; dir < kDirs; ++dir) {
-                const uint32_t x = (o.ix + (dir % 3 - 1)) & mask, y = (o.iy + ((dir / 3) % 3 - 1)) & mask, z = (o.iz + (dir / 9 - 1)) & mask;
-                for (int32_t m = t.descend(o.level, x, y, z); t.nodes[m].level < o.level; m = t.descend(o.level, x, y, z)) {
-                    t.split(m);
-                    inner[t.nodes[m].level].push_back(m);
-                }
+    static const ChildSteps steps;
+    nbr.assign(kDirs, 0);
+    for (size_t r = 1; r < t.inner.size(); ++r) {                    // inner[0] is the root
+        const int32_t n = t.inner[r], parent = t.nodes[n].parent;
+        const int c = n - t.nodes[parent].first_child;
+        const size_t from = static_cast<size_t>(t.nodes[parent].row) * kDirs;
+        for (int dir = 0; dir < kDirs; ++dir) {
+            const ChildStep s = steps.at[c][dir];
+            const int32_t above = nbr[from + s.parent_dir];
+            int32_t first = t.nodes[above].first_child;
+            if (first < 0) {
+                if (!may_split) return OT_E_UNBALANCED;
+                first = t.split(above);
             }
+            nbr.push_back(first + s.slot);
         }
     }
+    return OT_OK;
 }
 
 void emit_leaves(Octree& t, int32_t n, std::vector<ot_leaf>& out)
@@ -117,142 +129,93 @@ void emit_leaves(Octree& t, int32_t n, std::vector<ot_leaf>& out)
     for (int c = 0; c < 8; ++c) emit_leaves(t, first + c, out);
 }
 
-// For child c = (cz<<2)|(cy<<1)|cx of a node and direction dir: which neighbour of the node holds the child's neighbour
-// octant, and as which of its children.
-struct ChildStep { int8_t parent_dir, slot; };
-struct ChildSteps {
-    ChildStep at[8][kDirs];
-    ChildSteps()
-    {
-        for (int c = 0; c < 8; ++c)
-            for (int dir = 0; dir < kDirs; ++dir) {
-                const int x = (c & 1) + dir % 3 - 1, y = ((c >> 1) & 1) + (dir / 3) % 3 - 1, z = (c >> 2) + dir / 9 - 1;   // -1 .. 2
-                auto up = [](int p) { return p < 0 ? 0 : (p < 2 ? 1 : 2); };
-                at[c][dir] = {static_cast<int8_t>(up(z) * 9 + up(y) * 3 + up(x)), static_cast<int8_t>(((z & 1) << 2) | ((y & 1) << 1) | (x & 1))};
-            }
-    }
-};
-
-// The children of an octant that touch the block on its side -dir: along an axis with d = -1 they are the upper
-// children, with d = +1 the lower ones; axes with d = 0 are free and enumerated x, then y, then z (ascending Morton order).
-struct TouchingChildren {
-    int8_t count[kDirs], slot[kDirs][8];
-    TouchingChildren()
-    {
-        for (int dir = 0; dir < kDirs; ++dir) {
-            const int d[3] = {dir % 3 - 1, (dir / 3) % 3 - 1, dir / 9 - 1};
-            int n = 0;
-            for (int c = 0; c < 8; ++c) {
-                bool touches = true;
-                for (int ax = 0; ax < 3; ++ax)
-                    if (d[ax] && ((c >> ax) & 1) != (d[ax] < 0 ? 1 : 0)) touches = false;
-                if (touches) slot[dir][n++] = static_cast<int8_t>(c);
-            }
-            count[dir] = static_cast<int8_t>(n);
-        }
-    }
-};
-
-// The ghost table and what is derived from it: virtual blocks, and which parts of them are read.  The leaves have
-// their ids.  Returns OT_OK or OT_E_UNBALANCED.
-int make_tables(const Octree& t, HostTree& out)
+// What the ghost table is made from, virtual blocks, and which parts of them are read.  The leaves have their ids, `out.nbr` the
+// neighbours.
+void make_tables(const Octree& t, HostTree& out)
 {
     static const ChildSteps steps;
-    static const TouchingChildren touching;
     const size_t nb = out.leaves.size();
-    // neighbours of every node with children (the node itself in the middle), in the order of the nodes: parents come first
-    std::vector<int32_t> rank(t.nodes.size(), -1), nbr;
-    int32_t n_inner = 0;
-    for (size_t n = 0; n < t.nodes.size(); ++n)
-        if (t.nodes[n].first_child >= 0) rank[n] = n_inner++;
-    nbr.assign(static_cast<size_t>(n_inner) * kDirs, 0);             // the root's neighbours are the root
-    std::vector<int32_t> parent_of_leaf(nb, 0);                      // 8 * node + child
-    for (size_t n = 0; n < t.nodes.size(); ++n) {
-        if (t.nodes[n].first_child < 0) continue;
-        const int32_t* at = &nbr[static_cast<size_t>(rank[n]) * kDirs];
+    out.node.resize(t.nodes.size());
+    for (size_t n = 0; n < t.nodes.size(); ++n) out.node[n] = t.nodes[n].first_child >= 0 ? t.nodes[n].first_child : ~t.nodes[n].leaf_id;
+    // A neighbour octant under a leaf is that leaf's child octant: noted in `virt_mask` (per leaf, which of its child octants some
+    // block needs) and `coarser`.  Only the children of a node that has a leaf among its neighbours have any.
+    struct Coarser { int32_t leaf; int8_t octant, dir; };
+    std::vector<Coarser> coarser;
+    out.parent.assign(nb, 0);
+    out.virt_mask.assign(nb, 0);
+    for (size_t r = 0; r < t.inner.size(); ++r) {
+        const int32_t first = t.nodes[t.inner[r]].first_child;
+        const int32_t* at = &out.nbr[r * kDirs];
+        uint32_t leaves = 0;
+        for (int dir = 0; dir < kDirs; ++dir) leaves |= static_cast<uint32_t>(out.node[at[dir]] < 0) << dir;
         for (int c = 0; c < 8; ++c) {
-            const int32_t ch = t.nodes[n].first_child + c;
-            if (t.nodes[ch].first_child < 0) {
-                parent_of_leaf[t.nodes[ch].leaf_id] = static_cast<int32_t>(8 * rank[n] + c);
-                continue;
-            }
-            int32_t* to = &nbr[static_cast<size_t>(rank[ch]) * kDirs];
+            if (out.node[first + c] >= 0) continue;
+            out.parent[~out.node[first + c]] = static_cast<int32_t>(8 * r + c);
+            if (!leaves) continue;
             for (int dir = 0; dir < kDirs; ++dir) {
                 const ChildStep s = steps.at[c][dir];
-                const int32_t first = t.nodes[at[s.parent_dir]].first_child;
-                if (first < 0) return OT_E_UNBALANCED;
-                to[dir] = first + s.slot;
+                if (!((leaves >> s.parent_dir) & 1)) continue;
+                const int32_t leaf = ~out.node[at[s.parent_dir]];
+                out.virt_mask[leaf] |= static_cast<uint8_t>(1 << s.slot);
+                coarser.push_back({leaf, s.slot, static_cast<int8_t>(dir)});
             }
         }
-    }
-    // rows of the ghost table.  A neighbour octant under a leaf is that leaf's child octant: noted in `mask` (per leaf, which
-    // of its child octants some block needs) and `coarser` (index of the entry, octant).
-    std::vector<uint8_t> mask(nb, 0);
-    struct Coarser { size_t entry; int32_t octant, dir; };
-    std::vector<Coarser> coarser;
-    out.ghost.clear();
-    out.ghost.reserve(nb * kDirs * kEntry);
-    for (size_t b = 0; b < nb; ++b) {
-        const int c = parent_of_leaf[b] & 7;
-        const int32_t* at = &nbr[static_cast<size_t>(parent_of_leaf[b] >> 3) * kDirs];
-        int32_t row[kDirs * kEntry];
-        for (int dir = 0; dir < kDirs; ++dir) {
-            const ChildStep s = steps.at[c][dir];
-            const Node& above = t.nodes[at[s.parent_dir]];
-            int32_t* e = row + dir * kEntry;
-            e[1] = e[2] = e[3] = e[4] = -1;
-            if (above.first_child < 0) {
-                e[0] = kCoarser;
-                e[1] = above.leaf_id;
-                mask[above.leaf_id] |= static_cast<uint8_t>(1 << s.slot);
-                coarser.push_back({(b * kDirs + dir) * kEntry, s.slot, dir});
-                continue;
-            }
-            const Node& nd = t.nodes[above.first_child + s.slot];
-            if (nd.first_child < 0) {
-                e[0] = kSame;
-                e[1] = nd.leaf_id;
-                continue;
-            }
-            e[0] = kFiner;
-            for (int q = 0; q < touching.count[dir]; ++q) {
-                const Node& ch = t.nodes[nd.first_child + touching.slot[dir][q]];
-                if (ch.first_child >= 0) return OT_E_UNBALANCED;
-                e[1 + q] = ch.leaf_id;
-            }
-        }
-        out.ghost.insert(out.ghost.end(), row, row + kDirs * kEntry);
     }
     // virtual blocks, numbered by source leaf, then octant
-    std::vector<int32_t> first(nb, 0);
+    out.first_virt.resize(nb);
     out.vblk.clear();
     int32_t n = 0;
     for (size_t s = 0; s < nb; ++s) {
-        first[s] = n;
+        out.first_virt[s] = n;
         for (int c = 0; c < 8; ++c)
-            if ((mask[s] >> c) & 1) {
+            if ((out.virt_mask[s] >> c) & 1) {
                 out.vblk.push_back(static_cast<int32_t>(s));
                 out.vblk.push_back(c);
                 ++n;
             }
     }
     out.n_virt = n;
-    out.ghost_v = out.ghost;
     out.vneed.assign(n, 0);
     // a block reads, of its neighbour in direction d, the three layers next to itself along every axis with d != 0
     // and all eight along the others
     auto layers = [](int d) { return d > 0 ? 0x07 : (d < 0 ? 0xE0 : 0xFF); };
     for (const Coarser& e : coarser) {
-        int32_t* v = &out.ghost_v[e.entry];
-        const int32_t src = v[1];
-        v[0] = kVirtual;
-        v[1] = first[src] + __builtin_popcount(static_cast<unsigned>(mask[src]) & ((1u << e.octant) - 1));
-        out.vneed[v[1]] |= layers((e.dir / 3) % 3 - 1) | layers(e.dir / 9 - 1) << 8;
+        const int32_t v = out.first_virt[e.leaf] + __builtin_popcount(static_cast<unsigned>(out.virt_mask[e.leaf]) & ((1u << e.octant) - 1));
+        out.vneed[v] |= layers((e.dir / 3) % 3 - 1) | layers(e.dir / 9 - 1) << 8;
     }
+}
+
+// the tree's leaves are final but for the balance
+int finish(Octree& t, bool may_split, HostTree& out)
+{
+    if (const int rc = link_neighbours(t, may_split, out.nbr)) return rc;
+    out.leaves.clear();
+    emit_leaves(t, 0, out.leaves);
+    make_tables(t, out);
+    make_units(out);
     return OT_OK;
 }
 
+void expand(HostTree& t)
+{
+    t.ghost.resize(t.leaves.size() * kDirs * kEntry);
+    t.ghost_v.resize(t.ghost.size());
+    write_ghost_table(t, false, t.ghost.data());
+    write_ghost_table(t, true, t.ghost_v.data());
+}
+
 }  // namespace
+
+void write_ghost_table(const HostTree& t, bool virt, int32_t* out)
+{
+    const TableSource src = t.source();
+    int32_t e[kEntry];
+    for (size_t b = 0; b < t.leaves.size(); ++b)
+        for (int dir = 0; dir < kDirs; ++dir) {
+            table_entry(src, static_cast<int64_t>(b), dir, virt, e);
+            for (int m = 0; m < kEntry; ++m) *out++ = e[m];
+        }
+}
 
 void make_units(HostTree& t)
 {
@@ -273,7 +236,7 @@ void make_units(HostTree& t)
     }
 }
 
-int build_tree(const ot_build_params& p, HostTree& out)
+int plan_tree(const ot_build_params& p, HostTree& out)
 {
     if (p.lmin < 3 || p.lmax < p.lmin || p.lmax > 19) return OT_E_BADARG;
     if (p.points_per_dim != 8 || p.pad != 3 || p.periodic != 1) return OT_E_UNSUPPORTED;
@@ -288,7 +251,6 @@ int build_tree(const ot_build_params& p, HostTree& out)
 
     Octree t;
     std::deque<int32_t> work{0};
-    std::vector<int32_t> inner[21];
     // uniform refinement to lmin, then seed-driven refinement; each node is visited once
     while (!work.empty()) {
         const int32_t n = work.front();
@@ -296,19 +258,13 @@ int build_tree(const ot_build_params& p, HostTree& out)
         const Node o = t.nodes[n];
         const bool grow = o.level < p.lmin || (o.level < p.lmax && near_seed(o, p));
         if (!grow) continue;
-        inner[o.level].push_back(n);
         const int32_t first = t.split(n);
         for (int c = 0; c < 8; ++c) work.push_back(first + c);
     }
-    balance(t, inner);
-    out.leaves.clear();
-    emit_leaves(t, 0, out.leaves);
-    const int rc = make_tables(t, out);
-    if (rc == OT_OK) make_units(out);
-    return rc;
+    return finish(t, true, out);
 }
 
-int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
+int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
 {
     if (!leaves || n == 0) return OT_E_BADARG;
     Octree t;
@@ -328,10 +284,20 @@ int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
     }
     for (const Node& nd : t.nodes)
         if (nd.first_child == kUnset) return OT_E_INCOMPLETE;                // a gap
-    out.leaves.clear();
-    emit_leaves(t, 0, out.leaves);
-    const int rc = make_tables(t, out);
-    if (rc == OT_OK) make_units(out);
+    return finish(t, false, out);
+}
+
+int build_tree(const ot_build_params& p, HostTree& out)
+{
+    const int rc = plan_tree(p, out);
+    if (rc == OT_OK) expand(out);
+    return rc;
+}
+
+int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
+{
+    const int rc = plan_tree_from_leaves(leaves, n, out);
+    if (rc == OT_OK) expand(out);
     return rc;
 }
 

@@ -2,49 +2,19 @@
 // traversal and the ghost-source table.  No device code here.
 #pragma once
 #include <cstdint>
-#include <cstdlib>
-#include <new>
 #include <vector>
 
-#include <sys/mman.h>
-
 #include "octfd.h"
+#include "table_rows.hpp"
 
 namespace octfd {
 
-constexpr int kDirs = 27;          // directions (dz+1)*9 + (dy+1)*3 + (dx+1)
-constexpr int kEntry = 5;          // {kind, id0..id3}
-enum GhostKind : int32_t { kSame = 0, kFiner = 1, kCoarser = 2, kVirtual = 3 };
-
-// Allocator of the two big tables (540 bytes per block each): whole huge pages where the system gives them on request.
-// A fresh table is written once, and with pages of 4 KB the page faults took longer than everything else in building a
-// tree (26 of 27 ms for 27,756 blocks on a virtual machine; 12 of 18 with huge pages).
-template <class T>
-struct HugePageAllocator {
-    using value_type = T;
-    static constexpr size_t kPage = size_t(2) << 20;
-    HugePageAllocator() = default;
-    template <class U> HugePageAllocator(const HugePageAllocator<U>&) {}
-    T* allocate(size_t n)
-    {
-        if (n > (~size_t(0) - kPage) / sizeof(T)) throw std::bad_alloc();
-        size_t bytes = n * sizeof(T);
-        const bool huge = bytes >= kPage;
-        if (huge) bytes = (bytes + kPage - 1) / kPage * kPage;
-        void* p = huge ? std::aligned_alloc(kPage, bytes) : std::malloc(bytes ? bytes : 1);
-        if (!p) throw std::bad_alloc();
-        if (huge) (void)madvise(p, bytes, MADV_HUGEPAGE);            // a hint: without it the pages are small ones
-        return static_cast<T*>(p);
-    }
-    void deallocate(T* p, size_t) { std::free(p); }
-    template <class U> bool operator==(const HugePageAllocator<U>&) const { return true; }
-    template <class U> bool operator!=(const HugePageAllocator<U>&) const { return false; }
-};
-using BigTable = std::vector<int32_t, HugePageAllocator<int32_t>>;
-
 struct HostTree {
     std::vector<ot_leaf> leaves;   // Morton order
-    BigTable ghost;                // [nb][27][5]
+    // What the rows of the ghost table are made from (TableSource)
+    std::vector<int32_t> node, nbr, parent, first_virt;
+    std::vector<uint8_t> virt_mask;
+    TableSource source() const { return {node.data(), nbr.data(), parent.data(), first_virt.data(), virt_mask.data()}; }
     // "Virtual blocks".  Where the same-level neighbour octant of a block does not exist because its parent L is
     // a leaf, the ghost values in that direction are interpolated inside L, and what they are depends only on L's
     // data and on the fine position inside L, not on which block asks.  Such an octant can therefore be filled
@@ -52,23 +22,28 @@ struct HostTree {
     // exactly like a neighbour of their own level.
     //   vblk    [n_virt][2]        per virtual block {source leaf id, child octant (ox | oy<<1 | oz<<2)}, ordered by
     //                              source leaf (Morton order), then octant
-    //   ghost_v [nb][27][5]        the ghost table with every coarser entry replaced by {kVirtual, virtual block}
     //   n_virt                     number of virtual blocks
     //   vneed   [n_virt]           which y rows (bits 0..7) and z planes (bits 8..15) of a virtual block any block reads: the
     //                              union, per axis, over the blocks that have it as a neighbour.  The fill writes only
     //                              those (whole x rows of them); the rest of a virtual block is never read.
-    BigTable ghost_v;
     std::vector<int32_t> vblk, vneed;
     int64_t n_virt = 0;
     // Work units of the two-block kernel of the 24-field system, in Morton order: the first block of every two
     // leaves that are the lower and upper x child of one parent (they follow each other in storage), and, flagged
     // with kUnitSingle, every other block (a leaf whose x sibling is subdivided).  Every block belongs to exactly one unit.
     std::vector<int32_t> units;
+    // The ghost table in full, [nb][27][5], and the same with every coarser entry replaced by {kVirtual, virtual block}: what the device
+    // makes for itself.  Filled by build_tree() and tree_from_leaves() only.
+    std::vector<int32_t> ghost, ghost_v;
 };
 
-// Each returns an OT_* status.
+// Each returns an OT_* status.  plan_...: everything but the ghost table in full.
+int plan_tree(const ot_build_params& p, HostTree& out);
+int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
 int build_tree(const ot_build_params& p, HostTree& out);
 int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
+// the ghost table, `virt`: with virtual blocks, to out[nb][27][5]
+void write_ghost_table(const HostTree& t, bool virt, int32_t* out);
 void make_units(HostTree& t);
 
 }  // namespace octfd
