@@ -355,17 +355,15 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual(DeviceTree tr, int nvar, c
 // the octant's side are 26-neighbours of P too (per axis they step back towards P where L is off P, and one to either
 // side where it is not); P is subdivided, so the 2:1 balance leaves none of them coarser than L.
 // Then the same three passes as in k_virtual, with nine nodes per line; a wavefront owns one variable of one virtual block at
-// a time.  What differs is how the nodes get to the x pass:
-//   k_virtual_centred       five variables or more: the eight wavefronts of a workgroup share one virtual block.  Its 729 sources
-//       are worked out once by all of them, and a wavefront requests them in the order of the storage, a few lines per load,
-//       through its staging array.
-//   k_virtual_centred_few   up to four: as in k_virtual a workgroup takes several virtual blocks, and 729 sources for so few
-//       variables would cost more than the loads.  A lane gathers the nine nodes of its x lines (81 of them: the first 17 lanes
-//       take a second one) into registers; where a line lies is worked out as two sources, the part inside L's x range and the
-//       part beyond it.  Nothing needs a workgroup barrier.
-// (us per call of k_virtual_centred / _few on 21,064 blocks, 11,056 virtual blocks: 1 variable 64 / 24, 2: 80 / 52, 3: 96 / 80, 4:
-// 113 / 106, 5: 133 / 136, 6: 150 / 159, 8: 181 / 211; 24 variables 452, with the nodes gathered by lines 584; 102,075 blocks, 24
-// variables: 1321, by lines 1699.  One launch per level, one virtual block per workgroup: 81, 98, 118, 130, 153, 166, 195, 490; 1388.)
+// a time and requests its nodes in the order of the storage, a few lines per load, through its staging array (a lane that gathers whole
+// x lines touches 64 lines of the cache per load, which bound that form: the L1 takes one per cycle).  What differs is who works out
+// the 729 sources:
+//   k_virtual_centred       nine variables or more: the eight wavefronts of a workgroup share one virtual block, and its sources.
+//   k_virtual_centred_few   up to eight: each wavefront by itself, from a table made at compile time and L's row of the ghost table, so
+//       that a workgroup can take several virtual blocks and nothing needs a workgroup barrier.
+// (us, unzip_centred on 21,064 blocks, of which the fill of 11,056 virtual blocks, with the sources worked out together / by each wavefront:
+// 5 variables 898 / 877, 6: 1075 / 1056, 8: 1425 / 1405; up to four, with gathered lines / as here: 1: 136 / 134, 2: 279 / 268, 4: 711 / 688.
+// Steps of the wave system 1652 -> 1585 on 47,783 blocks, 60.7 -> 56.5 on 834; of Burgers 789 -> 750, 44.0 -> 40.1.)
 constexpr int CN = 9;                                // coarse nodes per axis
 
 // the eight fine values of a line with nine nodes v (node n is coarse node 4 o - 2 + n): even f passes node c0 through,
@@ -379,6 +377,26 @@ __device__ __forceinline__ void fine_line_centred(const double (&v)[CN], double 
 #pragma unroll
         for (int m = 1; m < 6; ++m) acc = fma(c_lag[12 + m], v[n + m], acc);
         r[2 * n + 1] = acc;
+    }
+}
+
+constexpr int CRS = CN, CPS = CN * CN + 7;           // row and plane stride of the staging array of nodes: 88 = 24 (mod 32)
+// x pass over a wavefront's staging array of nodes: lines (cz, cy), 81 of them; in place (a lane writes the first eight positions of the
+// row it has read)
+__device__ __forceinline__ void centred_x(double* A, int lane)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int line = lane + 64 * h;
+        if (line < CN * CN) {
+            double* row = A + line * CRS + 7 * (line / CN);
+            double c[CN], r[8];
+#pragma unroll
+            for (int m = 0; m < CN; ++m) c[m] = row[m];
+            fine_line_centred(c, r);
+#pragma unroll
+            for (int m = 0; m < 8; ++m) row[m] = r[m];
+        }
     }
 }
 
@@ -413,8 +431,7 @@ __device__ __forceinline__ void centred_yz(double* A, double* out, int need, int
     __builtin_amdgcn_wave_barrier();                 // the next variable overwrites the array
 }
 
-constexpr int kFewVariables = 4;                     // up to here k_virtual_centred_few
-constexpr int CRS = CN, CPS = CN * CN + 7;           // row and plane stride of the staging array of nodes: 88 = 24 (mod 32)
+constexpr int kFewVariables = 8;                     // up to here k_virtual_centred_few
 __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int nvar, const double* __restrict__ zipped,
                                                               double* __restrict__ virt)
 {
@@ -466,77 +483,56 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int
         for (int m = 0; m < NG; ++m) A[dst[m]] = nxt[m];
         if (v + 8 < nvar) gather(v + 8);
         __builtin_amdgcn_wave_barrier();
-        // x pass: lines (cz, cy), 81 of them; in place (a lane writes the first eight positions of the row it has read)
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int line = lane + 64 * h;
-            if (line < CN * CN) {
-                double* row = A + line * CRS + 7 * (line / CN);
-                double c[CN], r[8];
-#pragma unroll
-                for (int m = 0; m < CN; ++m) c[m] = row[m];
-                fine_line_centred(c, r);
-#pragma unroll
-                for (int m = 0; m < 8; ++m) row[m] = r[m];
-            }
-        }
+        centred_x(A, lane);
         __builtin_amdgcn_wave_barrier();
         centred_yz<CRS, CPS>(A, out + v * out_stride, need, lane);
     }
 }
 
 // Virtual blocks per workgroup of k_virtual_centred_few: as its wavefronts have variables for, halved as long as the 256
-// compute units can hold all workgroups at once, three each by their LDS (us, step with the centred rule, always 8 or 4 / as here:
-// Burgers 44.5 / 36.8 on 568 blocks, 200 virtual ones, 49.5 / 44.2 on 855, 760 virtual, 54.5 / 52.2 on 1,310, 1,248 virtual; wave
-// system 54.0 / 46.5, 64.1 / 60.8, 85.7 / 81.8; with half as many workgroups 45.1 and 62.7 on 855 blocks, with more than
-// are resident 77.9 instead of 68.5 on 2,220, 1,776 virtual).
+// compute units can hold all workgroups at once, three each by their LDS (us, step with the centred rule, always 8 or 4 / as here / with half
+// as many workgroups / with twice as many: Burgers 39.2 / 33.2 / 33.6 / 33.8 on 554 blocks, 42.2 / 37.6 / 37.1 / 37.5 on 708, 48.0 / 46.0 /
+// 47.0 / 52.1 on 1,170; wave system 48.4 / 42.8 / 42.9 / 42.9, 53.2 / 50.2 / 49.2 / 50.5, 73.2 / 69.4 / 73.2 / 75.0).
 inline int centred_per_workgroup(int64_t n_virt, int nvar)
 {
     int per = 8 / nvar;
     while (per > 1 && n_virt <= 3 * 256 * (int64_t)(per / 2)) per /= 2;
     return per;
 }
-constexpr int FPS = CN * NPT;                        // plane stride of the staging array behind the x pass, rows of 8: 72 = 8 (mod 32)
-
-// Where the nine nodes of an x line come from, as byte offsets into one variable's zipped array: nodes 0..3, 4..7 of the
-// octant of L's size that holds the line (`lo`, `hi`: of nodes 0 and 4; they are two leaves where that octant is
-// subdivided) and the nodes beyond it on the side of the child octant (`out`: of the first one); distance of two nodes in bytes.
-struct LineSource { uint32_t lo, hi, out; int in_step, out_step; };
-
-__device__ __forceinline__ LineSource line_source(const int32_t* row, int ox, int jj, int kk)
+// Sources of the 729 nodes for each child octant of L, worked out at compile time but for the table row of L: which of the eight
+// directions on the octant's side (bit per axis on which the node is beyond L), which finer neighbour there, the node's index in a
+// neighbour of the same level and in a finer one.
+constexpr int CNODES = CN * CN * CN, CITEMS = (CNODES + 63) / 64;              // 729; 12 per lane
+struct CentredItems { uint32_t at[8][CITEMS * 64]; };
+constexpr CentredItems make_centred_items()
 {
-    const int ry = jj < PAD ? 0 : (jj < PAD + NPT ? 1 : 2), rz = kk < PAD ? 0 : (kk < PAD + NPT ? 1 : 2);
-    const int ly = jj - PAD + (1 - ry) * NPT, lz = kk - PAD + (1 - rz) * NPT;
-    const int rx = ox ? 2 : 0;
-    const int32_t* e = &row[(rz * 9 + ry * 3 + 1) * 5];          // the centre entry is L itself
-    const int32_t* g = &row[(rz * 9 + ry * 3 + rx) * 5];
-    LineSource s;
-    s.lo = ghost_source(e, 1, ry, rz, 0, ly, lz);
-    s.hi = ghost_source(e, 1, ry, rz, 4, ly, lz);
-    s.out = ghost_source(g, rx, ry, rz, ox ? 0 : 6, ly, lz);
-    s.in_step = e[0] == K_SAME ? 8 : 16;
-    s.out_step = g[0] == K_SAME ? 8 : 16;
-    return s;
+    CentredItems t{};
+    for (int oct = 0; oct < 8; ++oct)
+        for (int n = 0; n < CITEMS * 64; ++n) {
+            const int p = n < CNODES ? n : CNODES - 1;                         // the lanes past them repeat the last one
+            const int node[3] = {p % CN, p / CN % CN, p / (CN * CN)};
+            int out = 0, q = 0, sh = 0, same = 0, fine = 0;
+            for (int a = 0; a < 3; ++a) {
+                const int f = 4 * ((oct >> a) & 1) - 2 + node[a];              // in L: 0..7
+                const int l = f < 0 ? f + NPT : (f < NPT ? f : f - NPT);       // in the octant of L's size that holds it
+                const int half = f < 0 ? 1 : (f < NPT ? l >> 2 : 0);           // the half of it in which a finer neighbour holds it
+                if (f < 0 || f >= NPT) out |= 1 << a;
+                else { q |= half << sh; ++sh; }
+                same |= l << (3 * a);
+                fine |= (2 * l - NPT * half) << (3 * a);
+            }
+            if (out == 0) q = 0;                                               // L itself
+            t.at[oct][n] = (uint32_t)(out * 4 + q) | (uint32_t)same << 5 | (uint32_t)fine << 14;
+        }
+    return t;
 }
-// the nine nodes of a line of a child octant in the lower (O = 0: nodes -2..6) or upper (O = 1: nodes 2..10) half of L's x range
-template <int O>
-__device__ __forceinline__ void load_line(double (&v)[CN], const double* base, const LineSource& s)
-{
-#pragma unroll
-    for (int m = 0; m < CN; ++m) {
-        const int n = 4 * O - 2 + m;                 // node
-        v[m] = n < 0 ? ldg(base, s.out + (n + 2) * s.out_step)
-               : n < 4 ? ldg(base, s.lo + n * s.in_step)
-               : n < 8 ? ldg(base, s.hi + (n - 4) * s.in_step)
-                       : ldg(base, s.out + (n - 8) * s.out_step);
-    }
-}
+__device__ const CentredItems kCentredItems = make_centred_items();
 
 __global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr, int nvar, int per, const double* __restrict__ zipped,
                                                                   double* __restrict__ virt)
 {
-    __shared__ double staging[8][CN * FPS];
-    __shared__ int32_t rows[8][27 * 5];              // L's table row, a copy for each wavefront
+    __shared__ double staging[8][CN * CPS];
+    __shared__ uint32_t rows[8][8 * 4];              // L's neighbours in the eight directions, four each (kFinerLeaf: of which the node needs one)
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int sub = wave / nvar, v = wave - sub * nvar;         // which of the workgroup's `per` virtual blocks, variable
     const int64_t q = block_of_workgroup(blockIdx.x) * per + sub, nb = tr.nb;
@@ -544,40 +540,35 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr,
     const int64_t leaf = tr.vblk[2 * q];
     const int oct = tr.vblk[2 * q + 1];
     const int need = tr.vneed[q];                    // y rows and z planes that any block reads
-    const int ox = oct & 1, oy = (oct >> 1) & 1, oz = oct >> 2;
-    int32_t* row = rows[wave];
+    uint32_t item[CITEMS];
 #pragma unroll
-    for (int m = 0; m < 3; ++m)
-        if (lane + 64 * m < 27 * 5) row[lane + 64 * m] = tr.ghost_v[leaf * (27 * 5) + lane + 64 * m];
+    for (int m = 0; m < CITEMS; ++m) item[m] = kCentredItems.at[oct][lane + 64 * m];
+    uint32_t* row = rows[wave];
+    constexpr uint32_t kFinerLeaf = 1u << 31;
+    if (lane < 8 * 4) {
+        const int out = lane >> 2;
+        const int dx = out & 1 ? 2 * (oct & 1) - 1 : 0, dy = out & 2 ? (oct & 2) - 1 : 0, dz = out & 4 ? (oct >> 1 & 2) - 1 : 0;
+        const int32_t* e = &tr.ghost_v[leaf * (27 * 5) + (13 + 9 * dz + 3 * dy + dx) * 5];               // the centre entry is L itself
+        const int32_t kind = e[0], first = e[1], own = e[1 + (lane & 3)];
+        row[lane] = kind == K_SAME ? (uint32_t)first : (uint32_t)own | kFinerLeaf;
+    }
     __builtin_amdgcn_wave_barrier();
-    // this lane's x lines: (cz, cy) = (line / 9, line % 9), in L's padded block shifted by the three ghost layers
-    const int line0 = lane, line1 = min(lane + 64, CN * CN - 1);
-    const bool second = lane + 64 < CN * CN;
-    const LineSource s0 = line_source(row, ox, 4 * oy + 1 + line0 % CN, 4 * oz + 1 + line0 / CN);
-    const LineSource s1 = line_source(row, ox, 4 * oy + 1 + line1 % CN, 4 * oz + 1 + line1 / CN);
+    const double* base = zipped + v * nb * BLK;
+    uint32_t id[CITEMS];
+    double node[CITEMS];
+#pragma unroll
+    for (int m = 0; m < CITEMS; ++m) id[m] = row[item[m] & 31];
+#pragma unroll
+    for (int m = 0; m < CITEMS; ++m) node[m] = ldg(base, (id[m] * BLK + (id[m] & kFinerLeaf ? item[m] >> 14 : item[m] >> 5) % BLK) * 8u);
     double* A = staging[wave];
-    const int64_t in_stride = nb * BLK, out_stride = tr.n_virt * BLK;
-    double* out = virt + q * BLK + lane;
-    const double* base = zipped + v * in_stride;
-    double n0[CN], n1[CN], r[8];
-    if (ox) {                                        // uniform
-        load_line<1>(n0, base, s0);
-        if (second) load_line<1>(n1, base, s1);
-    } else {
-        load_line<0>(n0, base, s0);
-        if (second) load_line<0>(n1, base, s1);
-    }
-    // x pass: lines (cz, cy), from registers
-    fine_line_centred(n0, r);
 #pragma unroll
-    for (int m = 0; m < 8; ++m) A[line0 * NPT + m] = r[m];
-    if (second) {
-        fine_line_centred(n1, r);
-#pragma unroll
-        for (int m = 0; m < 8; ++m) A[line1 * NPT + m] = r[m];
+    for (int m = 0; m < CITEMS; ++m) {
+        const int p = min(lane + 64 * m, CNODES - 1);
+        A[p + 7 * (p / (CN * CN))] = node[m];
     }
     __builtin_amdgcn_wave_barrier();
-    centred_yz<NPT, FPS>(A, out + v * out_stride, need, lane);
+    centred_x(A, lane);
+    centred_yz<CRS, CPS>(A, virt + v * tr.n_virt * BLK + q * BLK + lane, need, lane);
 }
 
 __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double* __restrict__ padded, double* __restrict__ zipped)
