@@ -1,4 +1,4 @@
-// gfx950 kernel of the 24-field right-hand side on zipped input: two sibling blocks (a 16 x 8 x 8 brick, see pair.hip) per
+// gfx950 kernel of the 24-field right-hand side, on zipped or padded input: two sibling blocks (a 16 x 8 x 8 brick, see pair.hip) per
 // workgroup of 512 threads, TWO x neighbours per thread, one workgroup on every compute unit for the whole launch.
 //
 // What bounded the kernel with a thread per point: LDS reads of 8 bytes (42 % of the time), vector instructions (36 %), and that the
@@ -42,6 +42,7 @@ constexpr int YPS = NPT * RS + 18;       // 210
 constexpr int WY = NPT * YPS;            // D1_y u on [8 k][8 j][22 ii]
 constexpr int BUF = TILE > WZ + WY ? TILE : WZ + WY;   // the D1 arrays, or the second tile
 
+constexpr bool gz_inside(int g) { return g >= PAD && g < PAD + NPT; }
 constexpr int gyz(int g) { return g < PAD ? g : g + NPT; }        // 0,1,2,11,12,13
 constexpr int at(int kk, int jj, int ii) { return kk * PS + jj * RS + ii + X0; }
 
@@ -82,6 +83,17 @@ constexpr Point3 ghost_item(int task, int lane)
 // kFixed: it has no meaning (behind the ghost columns of a block without a partner) and takes the block's first values.
 struct Item { uint32_t where, dst; };
 constexpr uint32_t kFixed = 1u << 31;
+// On padded input: the index of the pair's first value in the unit's two padded blocks, which follow each other; without a meaning, that of
+// the block's first own value.
+constexpr uint32_t padded_index(int kk, int jj, int ii) { return (uint32_t)((kk * NP + jj) * NP + ii); }
+constexpr uint32_t padded_source(bool single, Point3 p)
+{
+    const bool upper = p.ii >= PAD + NPT;
+    if (!(single && upper)) return (upper ? PBLK : 0) + padded_index(p.kk, p.jj, p.ii - (upper ? NPT : 0));
+    // the upper half of a block without a partner: its ghosts beyond the x face, as far as stencils along the axes and xz, xy edges read them
+    const bool meant = p.ii < 2 * PAD + NPT && (gz_inside(p.kk) || gz_inside(p.jj));
+    return meant ? padded_index(p.kk, p.jj, p.ii) : padded_index(PAD, PAD, PAD);
+}
 constexpr Item make_item(bool single, int task, int lane)
 {
     const Point3 p = ghost_item(task, lane);
@@ -114,6 +126,24 @@ constexpr Items make_items()
     return t;
 }
 __device__ const Items kItems = make_items();
+struct PaddedItems { uint32_t at[2][27 * 64]; };
+constexpr PaddedItems make_padded_items()
+{
+    PaddedItems t{};
+    for (int s = 0; s < 2; ++s)
+        for (int n = 0; n < 27 * 64; ++n) t.at[s][n] = padded_source(s != 0, ghost_item(n / 64, n % 64));
+    return t;
+}
+__device__ const PaddedItems kPaddedItems = make_padded_items();
+constexpr bool padded_items_inside()
+{
+    const PaddedItems t = make_padded_items();
+    for (int s = 0; s < 2; ++s)
+        for (int n = 0; n < 27 * 64; ++n)
+            if (t.at[s][n] + 2 > (s ? 1u : 2u) * PBLK) return false;
+    return true;
+}
+static_assert(padded_items_inside(), "every pair lies in the unit's padded blocks");
 
 __device__ __forceinline__ Pair fma2(Pair a, Pair b, Pair c) { return Pair{fma(a.x, b.x, c.x), fma(a.y, b.y, c.y)}; }
 __device__ __forceinline__ Pair fma2(double a, Pair b, Pair c) { return Pair{fma(a, b.x, c.x), fma(a, b.y, c.y)}; }
@@ -236,7 +266,8 @@ __device__ __forceinline__ int32_t scalar_int(const void* p) { return *(const __
 // What a wavefront's threads need to know of a unit
 struct Unit {
     int64_t b0;
-    uint32_t o8;             // byte offset of the thread's points in a variable's zipped array (phantom: of the same ones of the real block)
+    uint32_t o8;             // byte offset of the thread's points in a variable's zipped array (phantom: of the same ones of the real block);
+                             // padded input: this and the sources in the unit's padded blocks
     uint32_t own;            // source of the thread's own values in the tile
     uint32_t src[ITEMS];     // of its ghost items
     uint32_t phantom;        // uniform over the wavefront
@@ -244,9 +275,11 @@ struct Unit {
     uint32_t apart, real;
 };
 
+// EPI = kOutPadded: padded in, padded out
 template <int EPI, bool NTL, bool NTS>
 __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a)
 {
+    constexpr bool PADDED = EPI == kOutPadded;
     __shared__ __attribute__((aligned(16))) double tile[TILE];
     __shared__ __attribute__((aligned(16))) double wyz[BUF];
     __shared__ __attribute__((aligned(16))) double lapS[10 * 2 * br::NT];
@@ -268,7 +301,7 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
 
     // the table rows of a unit's two blocks are adjacent; a single block's row twice
     auto table_row = [&](int32_t unit) -> int32_t {
-        if (tid >= 2 * 27 * 5) return 0;
+        if (PADDED || tid >= 2 * 27 * 5) return 0;
         const int64_t b0 = unit & ~kUnitSingle;
         return tr.ghost_v[b0 * (27 * 5) + ((unit & kUnitSingle) && tid >= 27 * 5 ? tid - 27 * 5 : tid)];
     };
@@ -276,6 +309,18 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
         const bool single = unit & kUnitSingle;            // uniform
         n.b0 = unit & ~kUnitSingle;
         n.phantom = single && half;
+        if constexpr (PADDED) {
+            const uint32_t inner = padded_index(PAD, PAD, PAD), at = (uint32_t)((k * NP + j) * NP + i);
+            n.o8 = (inner + at + (half && !single ? PBLK : 0)) * 8u;
+            // a phantom's first columns are the real block's ghosts beyond the upper x face
+            n.own = n.phantom && i < PAD ? (inner + at + NPT) * 8u : n.o8;
+            n.apart = 0;
+            n.real = (2u << ITEMS) - 1;
+#pragma unroll
+            for (int m = 0; m < ITEMS; ++m)
+                if (m < ITEMS - 1 || w < LAST_ITEM_WAVES) n.src[m] = kPaddedItems.at[single][m * br::NT + tid] * 8u;
+            return;
+        }
         n.o8 = ((uint32_t)(n.b0 + (single ? 0 : half)) * BLK + (k * NPT + j) * NPT + i) * 8u;
         n.own = n.o8;
         n.apart = 0;
@@ -303,15 +348,17 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
                          xi - NPT >= PAD, ITEMS);
     };
 
+    // where the offsets of points start, variable v, unit at block b0
+    auto start = [&](int64_t b0, int v) -> int64_t { return PADDED ? ((int64_t)v * nb + b0) * PBLK : (int64_t)v * nb * BLK; };
     // No branch does anything but load to a register that another load may have written: the compiler would wait for the loads where
     // such branches join.
     struct Fetch { Pair own, g[ITEMS]; double own2, g2[ITEMS]; };          // second values 16 bytes apart come by themselves
     auto request = [&](Fetch& f, const Unit& n, int v, auto first, auto last) {      // items first .. last - 1, -1: own values
         constexpr int FIRST = decltype(first)::value, LAST = decltype(last)::value;
-        const double* base = a.in + (int64_t)v * nb * BLK;
+        const double* base = a.in + start(n.b0, v);
         const double* vbase = a.virt + (int64_t)v * n_virt * BLK;
         auto load = [&](Pair& to, double& to2, uint32_t s, int m) {
-            if (n.real >> m & 1) {                         // uniform
+            if (PADDED || (n.real >> m & 1)) {             // uniform
                 to = ldp<false>(base, s & ~7u);
             } else {
                 asm volatile("" : "+v"(s));          // or lane masks for every item would be kept
@@ -339,7 +386,7 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
     auto commit = [&](double* to, Fetch& f, const Unit& n, auto edges) -> Pair {
         constexpr bool EDGES = decltype(edges)::value;
         auto finish = [&](Pair& v, double v2, uint32_t s, int m) {
-            if (n.apart >> m & 1) {                  // uniform
+            if (!PADDED && (n.apart >> m & 1)) {     // uniform
                 asm volatile("" : "+v"(s));
                 v.y = (s & 3u) == kFinerBit ? v2 : v.y;
             }
@@ -361,12 +408,14 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
     int64_t round = 0, q = unit_of_round(0, blockIdx.x, tr.n_units);
     if (q < 0) return;                               // uniform
     int32_t unit = scalar_int(&tr.units[q]);
-    if (tid < 2 * 27 * 5) gt[tid] = table_row(unit);
-    __syncthreads();
+    if (!PADDED) {
+        if (tid < 2 * 27 * 5) gt[tid] = table_row(unit);
+        __syncthreads();
+    }
     Unit me;
     make_unit(me, unit);
 
-    auto centre = [&](const Unit& n, int v) -> Pair { return ldp<false>(a.in + (int64_t)v * nb * BLK, n.o8); };
+    auto centre = [&](const Unit& n, int v) -> Pair { return ldp<false>(a.in + start(n.b0, v), n.o8); };
     struct Epi { Pair acc, u; };
     auto epi_load = [&](Epi& e, int f) {
         if (EPI == kRkMiddle || EPI == kRkLast) {
@@ -389,7 +438,8 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
     auto put = [&](int f, const Result& r) {
         if (me.phantom) return;                      // uniform
         const int64_t o = (int64_t)f * nb * BLK;
-        if (EPI == kOutZipped) stp<NTS>(a.out + o, me.o8, r.a);
+        if (PADDED) stp<NTS>(a.out + start(me.b0, f), me.o8, r.a);
+        else if (EPI == kOutZipped) stp<NTS>(a.out + o, me.o8, r.a);
         else if (EPI == kRkLast) stp<NTS>(a.u + o, me.o8, r.a);
         else { stp<NTS>(a.acc + o, me.o8, r.a); stp<NTS>(a.out + o, me.o8, r.b); }
     };
@@ -493,7 +543,7 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
 #pragma unroll 1
     for (int t = 1; t < 10; ++t) pass_d2(t, Edges{});
     pass_d2(10, Faces{});
-    if (tid < 2 * 27 * 5) gt[tid] = row;             // of the next unit; read behind the barriers of the passes that follow
+    if (!PADDED && tid < 2 * 27 * 5) gt[tid] = row;  // of the next unit; read behind the barriers of the passes that follow
     // Passes over the variables without second derivatives: the tile and the D1 arrays, now idle, in turn.  They are shorter than
     // the way to memory and back, so the data of the variable after the next one is requested.
     auto pass_light = [&](double* T, double* next, int t, Pair unext, Fetch& coming, Fetch& after, Epi& now, Epi& then) {
@@ -551,6 +601,15 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
 template <int EPI, bool NTL, bool NTS>
 __global__ __launch_bounds__(br::NT) void k_brick(DeviceTree tr, RhsArgs a) { br::rhs_brick<EPI, NTL, NTS>(tr, a); }
 
+// Padded in, padded out.  What bounds it is memory traffic: every value of the input is read once, all but the corners, and only the 8^3
+// interior of an output block is written, 64 bytes of every 112, so that no line of it is whole.  Plain stores wait in the L2 for the
+// rest of a line and are then completed from memory all the same; non-temporal ones push nothing else out.  Rows start at any
+// multiple of 8 bytes, which is all that the accesses ask for, and the sources are the same for all units.
+// (us, one block per workgroup, a thread per point, Lap parked in the output -> as here with plain stores -> as here: 512 blocks 88 -> 68 -> 62,
+// 792 179 -> 146 -> 117, 5,230 1135 -> 1034 -> 839, 21,064 4510 -> 4198 -> 3436; the pipeline of unzip, this and zip 207 -> 191 -> 193,
+// 384 -> 341 -> 334, 2473 -> 2363 -> 2184, 9678 -> 9334 -> 8590.)
+__global__ __launch_bounds__(br::NT) void k_brick_padded(DeviceTree tr, RhsArgs a) { br::rhs_brick<kOutPadded, false, true>(tr, a); }
+
 template <int EPI>
 void launch_bricks(bool past, bool stream, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
@@ -574,6 +633,7 @@ bool bricks_apply(const DeviceTree& t, const RhsArgs& a)
 hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& a, bool past, bool stream, hipStream_t s)
 {
     switch (ep) {
+    case kOutPadded: hipLaunchKernelGGL(k_brick_padded, dim3(br::ROUND), dim3(br::NT), 0, s, t, a); break;
     case kOutZipped: launch_bricks<kOutZipped>(past, stream, t, a, s); break;
     case kRkFirst: launch_bricks<kRkFirst>(past, stream, t, a, s); break;
     case kRkMiddle: launch_bricks<kRkMiddle>(past, stream, t, a, s); break;

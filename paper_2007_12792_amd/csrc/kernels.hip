@@ -1,21 +1,13 @@
 // gfx950 kernels of liboctfd.
 //
 // A workgroup owns one block.  The kinds with one or two variables read it in slabs of two planes, one per wavefront
-// (slab.hpp); the 24-field system has one thread per point and a ghost-padded 14^3 tile of ONE variable in LDS through
-// which the variables are streamed (here from a padded array; on zipped input see pair.hip).  The fused kernels take ghost
-// values straight from zipped storage through the ghost-source table and never materialise the padded array; where each
-// value comes from is worked out once per block and reused for every variable.
-//
-// Mixed second derivatives D1_a(D1_b u) are not evaluated as 36-tap stencils: every thread
-// publishes its own D1_y u and D1_z u in LDS, the 3-deep ghost positions are filled in
-// cooperatively, and the outer operator then takes six taps from that array.
+// (slab.hpp); the 24-field system has kernels of its own (brick.hip, pair.hip).  The fused kernels take ghost
+// values straight from zipped storage through the ghost-source table and never materialise the padded array.
 //
 // Arithmetic follows one fixed IEEE sequence per formula (see octfd.h); the file is compiled with
 // -ffp-contract=off, so a fused multiply-add happens exactly where fma() is written.
-#include "fill.hpp"
 #include "slab.hpp"
 #include "stencils.hpp"
-#include "syn24.hpp"
 #include "tile.hpp"
 
 #include <algorithm>
@@ -26,148 +18,28 @@ namespace {
 
 // ---------------------------------------------------------------- right-hand-side kernel
 
-// The 24-field system on padded input: one block per workgroup of 512 threads, one thread per point, the variables
-// streamed through a double-buffered tile.  (On zipped input it runs k_rhs_pair instead.)
-struct Syn24Lds {
-    double tiles[2 * TILE];
-    double wyz[WZ + WY];                             // D1_z u and D1_y u of the variable in hand (mixed derivatives)
-    uint32_t plan_src[PLAN_EDGE * NTHREADS];
-};
-__device__ __forceinline__ void rhs_syn24_padded(const DeviceTree& tr, const RhsArgs& a, Syn24Lds& lds, int64_t b, int tid)
-{
-    const int64_t nb = tr.nb;
-    double* const tiles = lds.tiles;
-    double* const wyz = lds.wyz;
-    int i, j, k;
-    point_of(tid, i, j, k);
-    const int c = tidx(k + PAD, j + PAD, i + PAD);
-    // byte offset of this thread's point inside a padded block
-    const uint32_t p8 = (((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)) * 8u;
-    // 1/h = 2^(l+3) and 1/h^2, built from the level as bit patterns in scalar registers
-    const int lvl = tr.leaves[b].level;
-    const double ih = __longlong_as_double((long long)(1026 + lvl) << 52), ih2 = __longlong_as_double((long long)(1029 + 2 * lvl) << 52);
-    const double sigma = a.sigma;
-
-    FillPlan<PLAN_EDGE> fp;
-    fp.src = lds.plan_src;
-    make_plan_padded<PLAN_EDGE, NEDGE>(fp, tid);
-    double pv[PLAN_EDGE];
-
-    auto var_base = [&](int v) -> const double* { return a.in + ((int64_t)v * nb + b) * PBLK; };
-    auto centre = [&](int v) -> double { return ldg(var_base(v), p8); };   // this thread's own value of variable v
-
-    // SYN24.  The variables are streamed in descending cyclic order (see syn24_stream).  The
-    // first ten real passes (variables 9..0) evaluate the second-derivative combinations Lap_s;
-    // each thread parks them at its own point in variables 10+s of the output, from where
-    // the later passes (variables 23..10, which need Lap_{a mod 10}) read them back before those
-    // slots receive their final values.  Per-thread state thus shrinks to one gradient.
-    //
-    // The tile is double-buffered and global memory is requested ahead of its use: tile data
-    // of the next variable is loaded into registers at the top of a pass and stored to the
-    // other LDS buffer at its end (one barrier per pass, plus the one inside mixed_derivs); the
-    // pointwise operands of the next pass (u_{a+11}, Lap) likewise.
-    double* wz = wyz;
-    double* wy = wyz + WZ;
-    const double halpha = 0.5 * centre(0), bx = centre(1), by = centre(2), bz = centre(3);
-    const double Gxx = 1.0 - 0.125 * centre(4), Gxy = -(0.125 * centre(5)), Gxz = -(0.125 * centre(6));
-    const double Gyy = 1.0 - 0.125 * centre(7), Gyz = -(0.125 * centre(8)), Gzz = 1.0 - 0.125 * centre(9);
-    double nx = 0, ny = 0, nz = 0;
-    const int ownz = k * PS + (j + PAD) * RS + (i + PAD), owny = k * YPS + j * RS + (i + PAD);
-    struct Look { double unext, lap; };
-
-    auto out_base = [&](int v) -> double* { return a.out + ((int64_t)v * nb + b) * PBLK; };   // Lap_{v-10} is parked there (v = 10..19)
-    auto put = [&](int f, double rhs) { emit<kOutPadded>(a, nb, f, b, 0u, p8, rhs, EpiOperands{0.0, 0.0}); };
-
-    // top of pass t: request the tile data of pass t+1 and this pass's own pointwise operands.
-    // NEXT_USE says how much of the tile pass t+1 reads (edges only if it takes second derivatives).
-    auto issue = [&](int t, int f, Look& l, int& f1, auto next_use) {
-        constexpr int NEXT_USE = decltype(next_use)::value;
-        if (t + 1 < NSTREAM) {
-            f1 = syn24_stream(t + 1);
-            prefetch<PLAN_EDGE, NEXT_USE>(pv, fp, var_base(f1), tid);
-        }
-        l.unext = centre((f + 11) % 24);
-        if (t > 10) l.lap = ldg(out_base(10 + f % 10), p8);
-    };
-    using UseEdge = std::integral_constant<int, PLAN_EDGE>;
-    using UseFace = std::integral_constant<int, PLAN_FACE>;
-    // pass over a variable with second derivatives (9..0)
-    auto pass_d2 = [&](int t, auto next_use) {
-        constexpr int NEXT_USE = decltype(next_use)::value;
-        const double* T = tiles + (t & 1) * TILE;
-        const int f = syn24_stream(t);
-        int f1 = 0;
-        Look l{0.0, 0.0};
-        issue(t, f, l, f1, next_use);
-        const Syn24Part p = syn24_axes<true>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
-        const Mixed mx = mixed_derivs(T, wy, wz, tid, owny, ownz, ih);
-        double off = Gxy * mx.dxy;
-        off = fma(Gxz, mx.dxz, off);
-        off = fma(Gyz, mx.dyz, off);
-        const double lap = fma(2.0, off, p.diag);
-        stg(out_base(10 + f), p8, lap);
-        put(f, syn24_combine(p, f, lap, halpha, l.unext));
-        store_tile<PLAN_EDGE, NEXT_USE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
-        __syncthreads();
-    };
-    // pass over a variable without second derivatives (23..10)
-    auto pass_light = [&](int t) {
-        const double* T = tiles + (t & 1) * TILE;
-        const int f = syn24_stream(t);
-        int f1 = 0;
-        Look l{0.0, 0.0};
-        issue(t, f, l, f1, UseFace{});
-        const Syn24Part p = syn24_axes<false>(T, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
-        put(f, syn24_combine(p, f, l.lap, halpha, l.unext));
-        if (t + 1 < NSTREAM) {
-            store_tile<PLAN_EDGE, PLAN_FACE>(tiles + ((t + 1) & 1) * TILE, fp, pv, tid);
-            __syncthreads();
-        }
-    };
-
-    {   // pass 0: gradient of variable 10 only
-        const int f = syn24_stream(0), f1 = syn24_stream(1);
-        prefetch<PLAN_EDGE, PLAN_FACE>(pv, fp, var_base(f), tid);
-        store_tile<PLAN_EDGE, PLAN_FACE>(tiles, fp, pv, tid);
-        __syncthreads();
-        prefetch<PLAN_EDGE, PLAN_EDGE>(pv, fp, var_base(f1), tid);
-        nx = d1_at(tiles, c, 1, ih); ny = d1_at(tiles, c, RS, ih); nz = d1_at(tiles, c, PS, ih);
-        store_tile<PLAN_EDGE, PLAN_EDGE>(tiles + TILE, fp, pv, tid);
-        __syncthreads();
-    }
-#pragma unroll 1
-    for (int t = 1; t < 10; ++t) pass_d2(t, UseEdge{});
-    pass_d2(10, UseFace{});
-#pragma unroll 1
-    for (int t = 11; t < NSTREAM; ++t) pass_light(t);
-}
-
 // The right-hand side (and Runge-Kutta stage update) of whole blocks, one block per workgroup, all its variables.
 // Zipped input (ZIN): the block's surroundings are read through the ghost table in which coarser neighbours appear as
 // virtual blocks, which k_virtual or k_virtual_centred has filled before the launch, so every value is a copy or an
 // injection and no interpolation happens here; the two ghost rules differ only in which of the two kernels ran.
-constexpr int rhs_threads(int kind) { return kind == OT_RHS_SYN24 ? NTHREADS : slab_wavefronts(kind) * 64; }
+constexpr int rhs_threads(int kind) { return slab_wavefronts(kind) * 64; }
+constexpr int kWavesPerSimd = 8;                     // 64 VGPRs: four workgroups share a compute unit
 template <int KIND, bool ZIN, int EPI>
-__global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs(DeviceTree tr, RhsArgs a)
+__global__ __launch_bounds__(rhs_threads(KIND), kWavesPerSimd) void k_rhs(DeviceTree tr, RhsArgs a)
 {
     static_assert(ZIN != (EPI == kOutPadded), "padded in, padded out; everything else zipped");
     const int64_t b = block_of_workgroup(blockIdx.x);
     if (b >= tr.nb) return;                          // uniform over the workgroup
-    if constexpr (KIND == OT_RHS_SYN24) {
-        __shared__ Syn24Lds lds;
-        rhs_syn24_padded(tr, a, lds, b, threadIdx.x);
-    } else {
-        __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
-        __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
-        rhs_slab<KIND, ZIN, EPI, false>(tr, a, lds, lapS, b, threadIdx.x);
-    }
+    __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
+    __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
+    rhs_slab<KIND, ZIN, EPI, false>(tr, a, lds, lapS, b, threadIdx.x);
 }
 // The same on zipped input with non-temporal accesses to everything but the input (see streams()): what passes through once
 // does not push the input, whose ghost rows are read by several blocks, out of the L2 and the memory-side cache.
 constexpr int kStreamChunk = 64;   // blocks dealt to an XCD at a time: 1541 / 1521 / 1515 / 1509 / 1535 us for 8 / 16 / 32 / 64 / 128
                                    // (step of the wave system on 47,783 blocks)
 template <int KIND, int EPI>
-__global__ __launch_bounds__(rhs_threads(KIND), waves_per_simd(KIND)) void k_rhs_stream(DeviceTree tr, RhsArgs a)
+__global__ __launch_bounds__(rhs_threads(KIND), kWavesPerSimd) void k_rhs_stream(DeviceTree tr, RhsArgs a)
 {
     const int64_t b = block_of_workgroup<kStreamChunk>(blockIdx.x);
     if (b >= tr.nb) return;
@@ -599,8 +471,8 @@ bool streams(int64_t nb)
 template <int KIND, bool ZIN, int EPI>
 hipError_t launch_one(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
-    if constexpr (KIND == OT_RHS_SYN24 && ZIN) {
-        return launch_rhs_pairs(t, static_cast<Epilogue>(EPI), a, s);
+    if constexpr (KIND == OT_RHS_SYN24) {
+        return ZIN ? launch_rhs_pairs(t, static_cast<Epilogue>(EPI), a, s) : launch_rhs_bricks(t, kOutPadded, a, false, true, s);
     } else {
         if constexpr (ZIN) {
             if (streams<KIND, EPI>(t.nb)) {

@@ -79,7 +79,7 @@ hipError_t launch_zip(const DeviceTree& t, int nvar, const double* padded, doubl
 // epilogue kOutZipped or one of the Runge-Kutta stages
 hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& args, hipStream_t s);
 // the same with two points per thread (brick.hip), where it applies: operands of a stage read (past) and results written (stream)
-// non-temporally
+// non-temporally; also epilogue kOutPadded, on padded input, for all arguments
 bool bricks_apply(const DeviceTree& t, const RhsArgs& args);
 hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& args, bool past, bool stream, hipStream_t s);
 // in_zipped = false: args.in is padded; true: args.in is zipped and args.virt holds its virtual blocks

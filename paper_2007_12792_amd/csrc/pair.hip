@@ -8,12 +8,11 @@
 // so an x face costs the neighbour's whole 4 KB).  Ghost points per point fall from 3.94 to 3.0.
 //
 // With the compute unit's 160 KB of LDS to itself the workgroup also keeps the ten second-derivative
-// combinations Lap_s of its points in LDS (80 KB) instead of parking them in memory, which the one-block
-// kernel must do.  The tile is single-buffered: data of the next variable waits in registers until every
+// combinations Lap_s of its points in LDS (80 KB).  The tile is single-buffered: data of the next variable waits in registers until every
 // thread has finished with the tile.
 //
-// Everything a thread computes at its point is the same IEEE sequence as in the one-block kernel
-// (stencils.hpp, syn24.hpp); only where the operands sit in LDS differs.  Ghost values that would come from a
+// Mixed second derivatives D1_a(D1_b u) are not evaluated as 36-tap stencils: every thread publishes its own D1_y u and D1_z u in
+// LDS, the 3-deep ghost positions are filled in cooperatively, and the outer operator then takes six taps from that array.  Ghost values that would come from a
 // coarser leaf are read from virtual blocks (see HostTree), so no interpolation happens here.
 #include "kernels.hpp"
 #include "stencils.hpp"
@@ -71,7 +70,7 @@ __device__ __forceinline__ void ghost_point(int p, int& ii, int& jj, int& kk)
     }
 }
 
-// Mixed derivatives at the thread's point, as mixed_derivs() of the one-block kernel: every thread has stored
+// Mixed derivatives at the thread's point: every thread has stored
 // D1_y u and D1_z u of its own point; the 3-deep ghost positions are whole-wavefront tasks (wavefronts 0..5: one ghost
 // x column each, both operators; wavefronts 4..15: half a ghost y row each).  fill() ends before the barrier that
 // the caller places; taps() follows it.

@@ -59,39 +59,7 @@ __device__ __forceinline__ AxisOps axis_ops(const double* t, int c, int st, doub
 
 struct PointOps { double u0, dx, dy, dz, lap, ko; };   // all operators at a point
 
-struct Mixed { double dxy, dxz, dyz; };
-
-// Mixed derivatives of the variable in `tile` at this thread's point:
-//   dxy = D1_x(D1_y u), dxz = D1_x(D1_z u), dyz = D1_y(D1_z u).
-// wy [8][8][14] and wz [8][14][14] hold D1_y u and D1_z u; every thread has already stored the
-// values of its own point (indices owny, ownz).  The 3-deep ghost positions are whole-wavefront
-// tasks: wavefronts 0..5 each take one ghost x index (64 (j,k) columns, both operators),
-// wavefronts 2..7 each take one ghost y index.  Contains one barrier; the arrays may be reused
-// after the next barrier.
-__device__ __forceinline__ Mixed mixed_derivs(const double* tile, double* wy, double* wz, int tid, int owny, int ownz, double ih)
-{
-    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int la = tid & 7, lb = (tid >> 3) & 7;       // lane coordinates inside the task
-    if (w < 6) {                                        // ghost x index ii, lanes = (j, k)
-        const int ii = w < 3 ? w : w + NPT;
-        const int ct = tidx(lb + PAD, la + PAD, ii);
-        wy[lb * YPS + la * RS + ii] = d1_at(tile, ct, RS, ih);
-        wz[lb * PS + (la + PAD) * RS + ii] = d1_at(tile, ct, PS, ih);
-    }
-    if (w >= 2) {                                       // ghost y index jj, lanes = (i, k)
-        const int g = w - 2, jj = g < 3 ? g : g + NPT;
-        const int ct = tidx(lb + PAD, jj, la + PAD);
-        wz[lb * PS + jj * RS + (la + PAD)] = d1_at(tile, ct, PS, ih);
-    }
-    __syncthreads();
-    Mixed r;
-    r.dxy = d1_at(wy, owny, 1, ih);
-    __builtin_amdgcn_sched_barrier(0);
-    r.dxz = d1_at(wz, ownz, 1, ih);
-    __builtin_amdgcn_sched_barrier(0);
-    r.dyz = d1_at(wz, ownz, RS, ih);
-    return r;
-}
+struct Mixed { double dxy, dxz, dyz; };                // D1_x(D1_y u), D1_x(D1_z u), D1_y(D1_z u)
 
 // ---------------------------------------------------------------- output
 

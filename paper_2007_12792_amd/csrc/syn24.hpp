@@ -1,5 +1,5 @@
 // The 24-field synthetic system (see octfd.h, rhs_eval): what one pass over one variable computes at a thread's
-// point, and the order in which the variables are streamed.  Shared by the one-block and the two-block kernels.
+// point, and the order in which the variables are streamed.  Shared by the two-block kernels.
 #pragma once
 #include "stencils.hpp"
 
@@ -11,11 +11,11 @@ namespace {
 // holds the gradient of the successor variable on entry and this variable's own gradient on exit.
 //   t1 = beta . grad u,  t3q = grad u . grad u_next (before the factor 1/4),  ko = dissipation,
 //   diag = Gxx Dxx + Gyy Dyy + Gzz Dzz (WITH_D2 only).
-// WITH_D2 also publishes D1_y u and D1_z u of the own point for mixed_derivs().
+// WITH_D2 also publishes D1_y u and D1_z u of the own point for the mixed derivatives.
 struct Syn24Part { double t1, t3q, ko, diag; };
 
 // SY, SZ: row and plane stride of the tile (and of the D1_z array)
-template <bool WITH_D2, int SY = RS, int SZ = PS>
+template <bool WITH_D2, int SY, int SZ>
 __device__ __forceinline__ Syn24Part syn24_axes(const double* t, int c, double* wy, double* wz, int owny, int ownz,
                                                 double& nx, double& ny, double& nz, double bx, double by, double bz,
                                                 double Gxx, double Gyy, double Gzz, double sigma, double ih, double ih2)

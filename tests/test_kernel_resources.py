@@ -2,8 +2,8 @@
 
 The right-hand-side kernels of the kinds other than the 24-field system are compiled for 64 registers and 40 KB of LDS
 so that four workgroups share a compute unit; at that occupancy a kernel that spills even a few registers was measured
-a quarter slower.  The 24-field kernels need 128 registers and half the LDS of a compute unit.  A change that breaks one
-of these silently costs tens of per cent, so the build is checked here.
+a quarter slower.  The two-block kernel of the 24-field system needs 128 registers (the one with two points per thread:
+test_brick_resources.py).  A change that breaks one of these silently costs tens of per cent, so the build is checked here.
 """
 import os
 import re
@@ -57,19 +57,12 @@ def check(res, what, vgprs, lds):
 
 
 def test_small_kinds_fit_four_workgroups_per_compute_unit_without_spilling(usage):
-    plain = {k: v for k, v in instances(usage, "k_rhs").items() if k[0] != 3}      # kind, zipped input, epilogue
+    plain = instances(usage, "k_rhs")                                              # kind, zipped input, epilogue
     stream = instances(usage, "k_rhs_stream")                                      # kind, epilogue
     # on zipped input: DERIVS one epilogue, the others that and three stages; on padded input one each
     assert len(plain) == 9 + 3 and len(stream) == 9
     for key, res in list(plain.items()) + list(stream.items()):
         check(res, key, 64, 160 * 1024 // 4)
-
-
-def test_24_field_kernels_fit_two_workgroups_per_compute_unit(usage):
-    ks = {k: v for k, v in instances(usage, "k_rhs").items() if k[0] == 3}      # padded input only: zipped input runs k_rhs_pair
-    assert len(ks) == 1
-    for key, res in ks.items():
-        check(res, key, 128, 160 * 1024 // 2)                  # no interpolation code left in them
 
 
 @pytest.mark.parametrize("name", ["k_rhs_pair", "k_pair_stream", "k_pair_wide"])     # k_rhs_pair also: operands non-temporal
