@@ -48,6 +48,18 @@ __global__ __launch_bounds__(rhs_threads(KIND), kWavesPerSimd) void k_rhs_stream
     rhs_slab<KIND, true, EPI, true>(tr, a, lds, lapS, b, threadIdx.x);
 }
 
+// padded blocks in and out, written non-temporally (see kStreamPaddedBytes; an instance of its own, since a branch around the two kinds of
+// store is merged into one plain store)
+template <int KIND>
+__global__ __launch_bounds__(rhs_threads(KIND), kWavesPerSimd) void k_rhs_padded_stream(DeviceTree tr, RhsArgs a)
+{
+    const int64_t b = block_of_workgroup(blockIdx.x);
+    if (b >= tr.nb) return;
+    __shared__ double lds[slab_wavefronts(KIND) / sl::NSLAB * sl::LDS];
+    __shared__ double lapS[KIND == OT_RHS_WAVE ? BLK : 1];
+    rhs_slab<KIND, false, kOutPadded, true>(tr, a, lds, lapS, b, threadIdx.x);
+}
+
 // ---------------------------------------------------------------- unzip / zip kernels
 
 // unzip as a gather.  With the virtual blocks of the input filled (by k_virtual for the clamped ghost rule, by
@@ -468,6 +480,14 @@ bool streams(int64_t nb)
                              : 4 * ot_rhs_nvar_in(kind) * vector > kStreamStepBytes;
 }
 
+// On padded blocks only the result's 64 bytes of every 112 are written, which the L2 and the memory-side cache complete from memory
+// unless the line is there.  Non-temporal stores are worth it from where input and output leave that cache (us a call on changing
+// buffers, plain / non-temporal, and the pipeline of unzip, this and zip: Burgers on 1,919 blocks, 84 MB, 9.6 / 10.2, 34.6 / 34.8, on 3,396, 149
+// MB, 16.7 / 15.5, 62.7 / 63.8, on 5,230, 230 MB, 35.6 / 25.5, 95.4 / 92.6; wave 168 MB 19.6 / 17.9, 71.4 / 71.9, 298 MB 48.9 / 39.3, 122.5 /
+// 118.1, on 47,783 698 / 576, 1613 / 1498; DERIVS 211 MB 19.9 / 27.3, 68.5 / 72.2, 373 MB 63.0 / 45.1, 123.7 / 117.8, on 47,783 879 / 720,
+// 1662 / 1511).
+constexpr int64_t kStreamPaddedBytes = 256ll << 20;
+
 template <int KIND, bool ZIN, int EPI>
 hipError_t launch_one(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
@@ -477,6 +497,13 @@ hipError_t launch_one(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
         if constexpr (ZIN) {
             if (streams<KIND, EPI>(t.nb)) {
                 hipLaunchKernelGGL((k_rhs_stream<KIND, EPI>), dim3(grid_for_blocks<kStreamChunk>(t.nb)), dim3(rhs_threads(KIND)), 0, s, t, a);
+                return hipGetLastError();
+            }
+        }
+        if constexpr (!ZIN) {
+            constexpr ot_rhs_kind kind = static_cast<ot_rhs_kind>(KIND);
+            if ((ot_rhs_nvar_in(kind) + ot_rhs_nvar_out(kind)) * t.nb * PBLK * (int64_t)sizeof(double) > kStreamPaddedBytes) {
+                hipLaunchKernelGGL((k_rhs_padded_stream<KIND>), dim3(grid_for_blocks(t.nb)), dim3(rhs_threads(KIND)), 0, s, t, a);
                 return hipGetLastError();
             }
         }

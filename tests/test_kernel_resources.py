@@ -60,8 +60,9 @@ def test_small_kinds_fit_four_workgroups_per_compute_unit_without_spilling(usage
     plain = instances(usage, "k_rhs")                                              # kind, zipped input, epilogue
     stream = instances(usage, "k_rhs_stream")                                      # kind, epilogue
     # on zipped input: DERIVS one epilogue, the others that and three stages; on padded input one each
-    assert len(plain) == 9 + 3 and len(stream) == 9
-    for key, res in list(plain.items()) + list(stream.items()):
+    padded_stream = instances(usage, "k_rhs_padded_stream")                        # kind
+    assert len(plain) == 9 + 3 and len(stream) == 9 and len(padded_stream) == 3
+    for key, res in list(plain.items()) + list(stream.items()) + list(padded_stream.items()):
         check(res, key, 64, 160 * 1024 // 4)
 
 
@@ -75,7 +76,7 @@ def test_two_block_kernel_fits_one_compute_unit(usage, name):
 
 
 def test_every_kernel_is_looked_at(usage):
-    names = ["k_rhs", "k_rhs_stream", "k_rhs_pair", "k_pair_stream", "k_pair_wide", "k_unzip", "k_virtual", "k_virtual_centred", "k_virtual_centred_few", "k_zip"]
+    names = ["k_rhs", "k_rhs_stream", "k_rhs_padded_stream", "k_rhs_pair", "k_pair_stream", "k_pair_wide", "k_unzip", "k_virtual", "k_virtual_centred", "k_virtual_centred_few", "k_zip"]
     other = [n for n in usage if not any(re.search(r"\d%s[IE]" % k, n) for k in names)]
     assert not other, other
 
