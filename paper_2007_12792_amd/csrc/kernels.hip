@@ -455,6 +455,7 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr,
     centred_yz<CRS, CPS>(A, virt + v * tr.n_virt * BLK + q * BLK + lane, need, lane);
 }
 
+template <bool STREAM>
 __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double* __restrict__ padded, double* __restrict__ zipped)
 {
     const int tid = threadIdx.x;
@@ -462,6 +463,24 @@ __global__ __launch_bounds__(NTHREADS) void k_zip(int64_t nblocks, const double*
     if (q >= nblocks) return;
     const int i = tid & 7, j = (tid >> 3) & 7, k = tid >> 6;
     zipped[q * BLK + tid] = padded[q * PBLK + ((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)];
+}
+
+// The same in 16-byte words and past the caches, from kStreamZipBlocks on.  What bounds it is memory: of the lines that hold a padded block's
+// interior 43 % are ghosts.  (us a call on changing buffers, plain / non-temporal, then with a reduction over the result behind each, and the pipeline
+// of unzip, rhs_eval and this: DERIVS on 1,919 blocks, 7,676 of a variable, 16.9 / 15.8, 31.6 / 32.2, 68.4 / 60.5; wave 6,792: 14.3 / 13.9, 28.7 /
+// 29.9, 122 / 114, 10,460: 24.5 / 21.0, 39.1 / 39.3, 185 / 170; on 47,783 blocks wave 203 / 180, 277 / 252, 1607 / 1564, DERIVS 408 / 365, 550 / 504,
+// 1666 / 1573; 24 variables on 512 blocks 28.8 / 24.3, 43.5 / 43.7, 198 / 191, on 21,064 1075 / 972, 1423 / 1321, 8602 / 8508.  With 8-byte
+// words 2 to 8 % slower up to 9,213 blocks and the same beyond; 16-byte words without the rest 1 to 3 % slower on large trees.)
+constexpr int64_t kStreamZipBlocks = 8192;           // of all variables
+template <>
+__global__ __launch_bounds__(BLK / 2) void k_zip<true>(int64_t nblocks, const double* __restrict__ padded, double* __restrict__ zipped)
+{
+    const int tid = threadIdx.x;
+    const int64_t q = blockIdx.x;   // var*nb + block
+    if (q >= nblocks) return;
+    const int i = 2 * (tid & 3), j = (tid >> 2) & 7, k = tid >> 5;
+    const Pair v = __builtin_nontemporal_load(reinterpret_cast<const PairAt8*>(padded + q * PBLK + ((k + PAD) * NP + (j + PAD)) * NP + (i + PAD)));
+    __builtin_nontemporal_store(v, reinterpret_cast<PairAt8*>(zipped + q * BLK + 2 * tid));
 }
 
 // Non-temporal accesses cost where what a launch writes would have been in the memory-side cache for the next one: in a step,
@@ -567,7 +586,8 @@ hipError_t launch_zip(const DeviceTree& t, int nvar, const double* padded, doubl
 {
     const int64_t n = t.nb * nvar;
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zip, dim3((unsigned)n), dim3(NTHREADS), 0, s, n, padded, zipped);
+    if (n >= kStreamZipBlocks) hipLaunchKernelGGL(k_zip<true>, dim3((unsigned)n), dim3(BLK / 2), 0, s, n, padded, zipped);
+    else hipLaunchKernelGGL(k_zip<false>, dim3((unsigned)n), dim3(NTHREADS), 0, s, n, padded, zipped);
     return hipGetLastError();
 }
 
