@@ -173,7 +173,21 @@ __device__ __forceinline__ void fine_line(int o, const double (&v)[8], double (&
     else fine_half_line<0>(v, r);
 }
 
+// From this size of the input on the fills write non-temporally: the virtual blocks are read once or twice, among data many times the
+// memory-side cache.  (us, plain / non-temporal, step, step with the centred rule, evaluation, unzip: 24 fields on 3,396 blocks, 334 MB, 1711 / 1687,
+// 1894 / 1876, 345 / 333, 695 / 690, on 21,064 9566 / 9444, 10380 / 10270, 1899 / 1876, 4078 / 4040; wave system on 47,783, 391 MB, 1503 / 1491,
+// 1595 / 1593, 261 / 258, 728 / 724.  Below: 24 fields on 1,919, 188 MB, 978 / 980, 1083 / 1088, 188 / 180, 379 / 382; wave system on 21,064,
+// 173 MB, 684 / 681, 752 / 752, 102 / 106, 251 / 290; Burgers on 47,783, 196 MB, 694 / 693, 751 / 750, 111 / 105, 351 / 337, on 21,064 unzip 123 / 150.)
+constexpr int64_t kStreamFillBytes = 256ll << 20;
+inline bool fill_streams(const DeviceTree& t, int nvar) { return nvar * t.nb * BLK * (int64_t)sizeof(double) > kStreamFillBytes; }
+template <bool NT>
+__device__ __forceinline__ void put_virtual(double* p, double v)
+{
+    if (NT) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
 constexpr int VPS = 72;                              // plane stride of the staging array, 8 (mod 32): no bank conflicts in the y pass
+template <bool NT>
 __global__ __launch_bounds__(NTHREADS) void k_virtual(DeviceTree tr, int nvar, const double* __restrict__ zipped, double* __restrict__ virt)
 {
     __shared__ double staging[8][NPT * VPS];
@@ -225,7 +239,7 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual(DeviceTree tr, int nvar, c
         // only the rows and planes that are read are written (whole x rows: 64-byte pieces)
 #pragma unroll
         for (int m = 0; m < 8; ++m)
-            if (row_needed && ((need >> (8 + m)) & 1)) out[v * out_stride + m * (NPT * NPT)] = r[m];
+            if (row_needed && ((need >> (8 + m)) & 1)) put_virtual<NT>(&out[v * out_stride + m * (NPT * NPT)], r[m]);
         __builtin_amdgcn_wave_barrier();                         // the next variable's x pass overwrites the array
     }
 }
@@ -286,7 +300,7 @@ __device__ __forceinline__ void centred_x(double* A, int lane)
 
 // y and z passes of a wavefront's staging array A, in which the x pass has left lines of eight fine values, rows RSTR and
 // planes PSTR apart; writes the rows and planes in `need` to the virtual block at `out` (the lane's value of its plane 0)
-template <int RSTR, int PSTR>
+template <int RSTR, int PSTR, bool NT>
 __device__ __forceinline__ void centred_yz(double* A, double* out, int need, int lane)
 {
     double c[CN], r[8];
@@ -311,11 +325,12 @@ __device__ __forceinline__ void centred_yz(double* A, double* out, int need, int
     fine_line_centred(c, r);
 #pragma unroll
     for (int m = 0; m < 8; ++m)
-        if (((need >> hi) & 1) && ((need >> (8 + m)) & 1)) out[m * (NPT * NPT)] = r[m];
+        if (((need >> hi) & 1) && ((need >> (8 + m)) & 1)) put_virtual<NT>(&out[m * (NPT * NPT)], r[m]);
     __builtin_amdgcn_wave_barrier();                 // the next variable overwrites the array
 }
 
 constexpr int kFewVariables = 8;                     // up to here k_virtual_centred_few
+template <bool NT>
 __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int nvar, const double* __restrict__ zipped,
                                                               double* __restrict__ virt)
 {
@@ -369,7 +384,7 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred(DeviceTree tr, int
         __builtin_amdgcn_wave_barrier();
         centred_x(A, lane);
         __builtin_amdgcn_wave_barrier();
-        centred_yz<CRS, CPS>(A, out + v * out_stride, need, lane);
+        centred_yz<CRS, CPS, NT>(A, out + v * out_stride, need, lane);
     }
 }
 
@@ -412,6 +427,7 @@ constexpr CentredItems make_centred_items()
 }
 __device__ const CentredItems kCentredItems = make_centred_items();
 
+template <bool NT>
 __global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr, int nvar, int per, const double* __restrict__ zipped,
                                                                   double* __restrict__ virt)
 {
@@ -452,7 +468,7 @@ __global__ __launch_bounds__(NTHREADS) void k_virtual_centred_few(DeviceTree tr,
     }
     __builtin_amdgcn_wave_barrier();
     centred_x(A, lane);
-    centred_yz<CRS, CPS>(A, virt + v * tr.n_virt * BLK + q * BLK + lane, need, lane);
+    centred_yz<CRS, CPS, NT>(A, virt + v * tr.n_virt * BLK + q * BLK + lane, need, lane);
 }
 
 template <bool STREAM>
@@ -566,7 +582,7 @@ hipError_t launch_virtual(const DeviceTree& t, int nvar, const double* zipped, d
 {
     if (t.n_virt <= 0 || nvar <= 0) return hipSuccess;
     const int per = 8 / (nvar < 8 ? nvar : 8);       // virtual blocks per workgroup, as in the kernel
-    hipLaunchKernelGGL(k_virtual, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+    hipLaunchKernelGGL(fill_streams(t, nvar) ? k_virtual<true> : k_virtual<false>, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
     return hipGetLastError();
 }
 
@@ -574,10 +590,10 @@ hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* z
 {
     if (t.n_virt <= 0 || nvar <= 0) return hipSuccess;
     if (nvar > kFewVariables) {
-        hipLaunchKernelGGL(k_virtual_centred, dim3(grid_for_blocks(t.n_virt)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
+        hipLaunchKernelGGL(fill_streams(t, nvar) ? k_virtual_centred<true> : k_virtual_centred<false>, dim3(grid_for_blocks(t.n_virt)), dim3(NTHREADS), 0, s, t, nvar, zipped, virt);
     } else {
         const int per = centred_per_workgroup(t.n_virt, nvar);
-        hipLaunchKernelGGL(k_virtual_centred_few, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, per, zipped, virt);
+        hipLaunchKernelGGL(fill_streams(t, nvar) ? k_virtual_centred_few<true> : k_virtual_centred_few<false>, dim3(grid_for_blocks((t.n_virt + per - 1) / per)), dim3(NTHREADS), 0, s, t, nvar, per, zipped, virt);
     }
     return hipGetLastError();
 }

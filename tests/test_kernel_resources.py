@@ -83,7 +83,7 @@ def test_every_kernel_is_looked_at(usage):
 
 def test_fill_kernels_fit_three_workgroups_per_compute_unit(usage):
     names = [n for n in usage if "k_unzip" in n or "k_virtual" in n]
-    assert len(names) == 4
+    assert len(names) == 1 + 2 * 3                              # the fills also non-temporally
     for n in names:
         assert usage[n]["LDS Size [bytes/block]"] <= 160 * 1024 // 3, n
         assert usage[n]["VGPRs Spill"] == 0, n
