@@ -251,10 +251,10 @@ def main():
     hbm_ms = bytes_per_launch / (HBM_PEAK_GBS * 1e9) * 1e3
     valu_ms = None if not rec or not rec.get("fp64_flop_per_launch") else rec["fp64_flop_per_launch"] / (FP64_VECTOR_PEAK_TFLOPS * 1e12) * 1e3
     roofline_ms = max(hbm_ms, valu_ms or 0.0)
-    # the library takes a kernel with non-temporal accesses from 300 MiB of step vectors, 180 MiB of an evaluation's input and output
+    # the library takes a kernel with non-temporal accesses from 300 MiB of step vectors, 160 MB of an evaluation's input and output
     vectors = octfd.nvar_in(kind) + V if single_rhs else 4 * V
-    streams = vectors * nb * 4096 > (180 if single_rhs else 300) << 20
-    stage_kernel = {(True, True): "k_pair_stream", (True, False): "k_rhs_pair", (False, True): "k_rhs_stream", (False, False): "k_rhs"}[cfg["kind"] == "SYN24", streams]
+    streams = vectors * nb * 4096 > (160000000 if single_rhs else 300 << 20)
+    stage_kernel = {(True, True): "k_brick", (True, False): "k_brick", (False, True): "k_rhs_stream", (False, False): "k_rhs"}[cfg["kind"] == "SYN24", streams]
     out = {
         "metric": "block-point RHS updates/sec (fp64, per var) + achieved HBM GB/s, 1 GPU",
         "value": value, "unit": "updates/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
