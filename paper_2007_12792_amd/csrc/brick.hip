@@ -1,5 +1,5 @@
 // gfx950 kernel of the 24-field right-hand side, on zipped or padded input: two sibling blocks (a 16 x 8 x 8 brick, see pair.hip) per
-// workgroup of 512 threads, TWO x neighbours per thread, one workgroup on every compute unit for the whole launch.
+// workgroup of 512 threads, TWO x neighbours per thread, one workgroup at a time on every compute unit (rounds.hpp).
 //
 // What bounded the kernel with a thread per point: LDS reads of 8 bytes (42 % of the time), vector instructions (36 %), and that the
 // two hardly overlap, all wavefronts of the compute unit being in the same phase of a pass.  Two points per thread halve the first:
@@ -21,6 +21,7 @@
 // 9,510.  With three chains of gradients instead of Lap in LDS, u_{a+11} never read again and one barrier per pass 10,750: 27 passes
 // instead of 25, and no registers left to request data two passes ahead.)
 #include "kernels.hpp"
+#include "rounds.hpp"
 #include "stencils.hpp"
 #include "syn24.hpp"
 #include "tile.hpp"
@@ -249,17 +250,6 @@ __device__ __forceinline__ double scalar(double v)
 typedef const __attribute__((address_space(1))) double* Global;
 typedef const __attribute__((address_space(1))) PairAt8* GlobalPair;
 
-// Every compute unit runs one workgroup, which takes a unit of every `round` of 256: round r is units 256 r .. 256 r + 255, of which each
-// XCD (workgroup i runs on XCD i mod 8) takes a run, so that the blocks it works on at a time are close neighbours.  -1: none left.
-constexpr int ROUND = 256;
-__device__ __forceinline__ int64_t unit_of_round(int64_t round, int wg, int64_t n_units)
-{
-    const int64_t left = n_units - round * ROUND;
-    if (left <= 0) return -1;
-    const int run = left < ROUND ? (int)((left + NXCD - 1) / NXCD) : ROUND / NXCD;      // the last round is spread over all XCDs
-    const int x = wg % NXCD, n = wg / NXCD;
-    return n < run && x * run + n < left ? round * ROUND + x * run + n : -1;
-}
 // read through the constant address space: a scalar load
 __device__ __forceinline__ int32_t scalar_int(const void* p) { return *(const __attribute__((address_space(4))) int32_t*)(uintptr_t)p; }
 
@@ -405,7 +395,9 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
     using Faces = std::false_type;
     auto fence = []() { __builtin_amdgcn_sched_barrier(0); };
 
-    int64_t round = 0, q = unit_of_round(0, blockIdx.x, tr.n_units);
+    const int wg = blockIdx.x % kRound;
+    const Rounds mine = rounds_of_part(blockIdx.x / kRound, gridDim.x / kRound, rounds_of(tr.n_units));
+    int64_t round = mine.first, q = round < mine.last ? unit_of_round(round, wg, tr.n_units) : -1;
     if (q < 0) return;                               // uniform
     int32_t unit = scalar_int(&tr.units[q]);
     if (!PADDED) {
@@ -459,7 +451,7 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
     const int lvl = scalar_int(&tr.leaves[me.b0].level);
     const double ih = __longlong_as_double((long long)(1026 + lvl) << 52), ih2 = __longlong_as_double((long long)(1029 + 2 * lvl) << 52);
     const double scale1 = scalar(C60 * ih), scale2 = scalar((2.0 * C180) * ih2), scale_ko = scalar(a.sigma * over64(ih));
-    q = unit_of_round(++round, blockIdx.x, tr.n_units);
+    q = ++round < mine.last ? unit_of_round(round, wg, tr.n_units) : -1;
     const bool more = q >= 0;                        // uniform
     if (more) unit = scalar_int(&tr.units[q]);
     const int32_t row = more ? table_row(unit) : 0;
@@ -610,10 +602,12 @@ __global__ __launch_bounds__(br::NT) void k_brick(DeviceTree tr, RhsArgs a) { br
 // 384 -> 341 -> 334, 2473 -> 2363 -> 2184, 9678 -> 9334 -> 8590.)
 __global__ __launch_bounds__(br::NT) void k_brick_padded(DeviceTree tr, RhsArgs a) { br::rhs_brick<kOutPadded, false, true>(tr, a); }
 
+inline dim3 grid_for_units(int64_t n_units) { return dim3(kRound * (unsigned)parts_of(rounds_of(n_units))); }
+
 template <int EPI>
 void launch_bricks(bool past, bool stream, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
-    const dim3 grid(br::ROUND), block(br::NT);
+    const dim3 grid = grid_for_units(t.n_units), block(br::NT);
     constexpr bool kOperands = EPI == kRkMiddle || EPI == kRkLast;
     if (stream) hipLaunchKernelGGL((k_brick<EPI, kOperands, true>), grid, block, 0, s, t, a);
     else if (kOperands && past) hipLaunchKernelGGL((k_brick<EPI, kOperands, false>), grid, block, 0, s, t, a);
@@ -633,7 +627,7 @@ bool bricks_apply(const DeviceTree& t, const RhsArgs& a)
 hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& a, bool past, bool stream, hipStream_t s)
 {
     switch (ep) {
-    case kOutPadded: hipLaunchKernelGGL(k_brick_padded, dim3(br::ROUND), dim3(br::NT), 0, s, t, a); break;
+    case kOutPadded: hipLaunchKernelGGL(k_brick_padded, grid_for_units(t.n_units), dim3(br::NT), 0, s, t, a); break;
     case kOutZipped: launch_bricks<kOutZipped>(past, stream, t, a, s); break;
     case kRkFirst: launch_bricks<kRkFirst>(past, stream, t, a, s); break;
     case kRkMiddle: launch_bricks<kRkMiddle>(past, stream, t, a, s); break;
