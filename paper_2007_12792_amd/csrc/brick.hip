@@ -604,34 +604,37 @@ __global__ __launch_bounds__(br::NT) void k_brick_padded(DeviceTree tr, RhsArgs 
 
 inline dim3 grid_for_units(int64_t n_units) { return dim3(kRound * (unsigned)parts_of(rounds_of(n_units))); }
 
+// Operands of a stage are read non-temporally from the size at which a step's four vectors fill the 256 MB memory-side cache, us without / with: 196 / 203 on 512
+// blocks (201 MB), 357 / 366 on 575 (226 MB), 388 / 400 on 631 (248 MB), 421 / 418 on 694 (272 MB), 464 / 448 on 778 (305 MB); with
+// the centred rule 374 / 383, 419 / 429, 448 / 445, 505 / 486 on the last four.
+constexpr int64_t kOperandStepBytes = 256ll << 20;
+
 template <int EPI>
-void launch_bricks(bool past, bool stream, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
+void launch_bricks(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
     const dim3 grid = grid_for_units(t.n_units), block(br::NT);
     constexpr bool kOperands = EPI == kRkMiddle || EPI == kRkLast;
+    // Written non-temporally from the sizes that kernels.hpp explains, us without / with (operands past the caches on both sides): steps 448 / 453 on
+    // 764 blocks (300 MB), 457 / 453 on 792, 462 / 463 on 834 (327 MB), 483 / 467 on 890 (349 MB), 521 / 508 on 981, 723 / 684 on 1,198;
+    // with the centred rule 485 / 492, 494 / 496, 499 / 509, 527 / 521, 576 / 577, 785 / 754.
+    const int64_t bytes = t.nb * BLK * (int64_t)sizeof(double) * 24 * (EPI == kOutZipped ? 2 : 4);
+    const bool stream = bytes > (EPI == kOutZipped ? kStreamEvalBytes : kStreamStepBytes);
     if (stream) hipLaunchKernelGGL((k_brick<EPI, kOperands, true>), grid, block, 0, s, t, a);
-    else if (kOperands && past) hipLaunchKernelGGL((k_brick<EPI, kOperands, false>), grid, block, 0, s, t, a);
+    else if (kOperands && bytes > kOperandStepBytes) hipLaunchKernelGGL((k_brick<EPI, kOperands, false>), grid, block, 0, s, t, a);
     else hipLaunchKernelGGL((k_brick<EPI, false, false>), grid, block, 0, s, t, a);
 }
 
 }  // namespace
 
-// Which units fit: sources here reach 2^20 virtual blocks.  Arrays that are aligned to 8 bytes only stay with the kernel whose
-// accesses are of 8 bytes.
-bool bricks_apply(const DeviceTree& t, const RhsArgs& a)
+hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& a, hipStream_t s)
 {
-    auto odd = [](const void* p) { return reinterpret_cast<uintptr_t>(p) % 16 != 0; };
-    return t.n_virt <= kBlockLimit && !odd(a.in) && !odd(a.out) && !odd(a.acc) && !odd(a.u) && !odd(a.virt);
-}
-
-hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& a, bool past, bool stream, hipStream_t s)
-{
+    if (ep != kOutPadded && t.n_virt > kBlockLimit) return hipErrorInvalidValue;     // sources here are of 32 bits
     switch (ep) {
     case kOutPadded: hipLaunchKernelGGL(k_brick_padded, grid_for_units(t.n_units), dim3(br::NT), 0, s, t, a); break;
-    case kOutZipped: launch_bricks<kOutZipped>(past, stream, t, a, s); break;
-    case kRkFirst: launch_bricks<kRkFirst>(past, stream, t, a, s); break;
-    case kRkMiddle: launch_bricks<kRkMiddle>(past, stream, t, a, s); break;
-    case kRkLast: launch_bricks<kRkLast>(past, stream, t, a, s); break;
+    case kOutZipped: launch_bricks<kOutZipped>(t, a, s); break;
+    case kRkFirst: launch_bricks<kRkFirst>(t, a, s); break;
+    case kRkMiddle: launch_bricks<kRkMiddle>(t, a, s); break;
+    case kRkLast: launch_bricks<kRkLast>(t, a, s); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

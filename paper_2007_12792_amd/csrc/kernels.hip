@@ -527,7 +527,9 @@ template <int KIND, bool ZIN, int EPI>
 hipError_t launch_one(const DeviceTree& t, const RhsArgs& a, hipStream_t s)
 {
     if constexpr (KIND == OT_RHS_SYN24) {
-        return ZIN ? launch_rhs_pairs(t, static_cast<Epilogue>(EPI), a, s) : launch_rhs_bricks(t, kOutPadded, a, false, true, s);
+        // bricks reach 2^20 virtual blocks, whatever the alignment of the arrays (us, a thread per point / bricks, evaluation and step on 792 blocks
+        // 108 / 93, 512 / 457, on 21,057 2141 / 1838, 10,780 / 9332; arrays aligned to 8 bytes only 107 / 94, 523 / 461, 2178 / 1867, 10,907 / 9434)
+        return ZIN && t.n_virt > kBlockLimit ? launch_rhs_pairs(t, static_cast<Epilogue>(EPI), a, s) : launch_rhs_bricks(t, static_cast<Epilogue>(EPI), a, s);
     } else {
         if constexpr (ZIN) {
             if (streams<KIND, EPI>(t.nb)) {

@@ -75,13 +75,11 @@ hipError_t launch_virtual(const DeviceTree& t, int nvar, const double* zipped, d
 // ... or in unzip_centred
 hipError_t launch_virtual_centred(const DeviceTree& t, int nvar, const double* zipped, double* virt, hipStream_t s);
 hipError_t launch_zip(const DeviceTree& t, int nvar, const double* padded, double* zipped, hipStream_t s);
-// the 24-field right-hand side over the units of the tree (pair.hip): zipped input with its virtual blocks,
-// epilogue kOutZipped or one of the Runge-Kutta stages
+// the 24-field right-hand side over the units of the tree, two points per thread (brick.hip): zipped input of trees with at most 2^20 virtual
+// blocks, epilogue kOutZipped or one of the Runge-Kutta stages, or padded input of any tree, epilogue kOutPadded
+hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& args, hipStream_t s);
+// a thread per point (pair.hip): zipped input of any tree
 hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& args, hipStream_t s);
-// the same with two points per thread (brick.hip), where it applies: operands of a stage read (past) and results written (stream)
-// non-temporally; also epilogue kOutPadded, on padded input, for all arguments
-bool bricks_apply(const DeviceTree& t, const RhsArgs& args);
-hipError_t launch_rhs_bricks(const DeviceTree& t, Epilogue ep, const RhsArgs& args, bool past, bool stream, hipStream_t s);
 // in_zipped = false: args.in is padded; true: args.in is zipped and args.virt holds its virtual blocks
 hipError_t launch_rhs(const DeviceTree& t, ot_rhs_kind kind, bool in_zipped, Epilogue ep, const RhsArgs& args, hipStream_t s);
 

@@ -1,5 +1,6 @@
-// gfx950 kernel of the 24-field right-hand side on zipped input: TWO sibling blocks per workgroup, a thread per point.  Nearly every
-// call runs the kernel with two points per thread instead (brick.hip, bricks_apply()).
+// gfx950 kernel of the 24-field right-hand side on zipped input of trees with more virtual blocks than a 32-bit byte offset reaches (2^20 of
+// a variable; see source.hpp): TWO sibling blocks per workgroup, a thread per point.  All other trees run the kernel with two points
+// per thread (brick.hip).
 //
 // Two leaves that are x-neighbours inside one parent follow each other in storage.  One workgroup of
 // 1,024 threads (16 wavefronts, one whole compute unit) owns such a pair as a single 16 x 8 x 8 brick with a
@@ -114,13 +115,12 @@ __device__ __forceinline__ int64_t pair_of_workgroup(int64_t wg)
 // face (taken through the block's own table row), the rest is filled with any valid value, and the threads of the
 // second half go through all the motions (they must meet the barriers) but write nothing to memory.
 //
-// The Runge-Kutta operands pass through once per stage; with NTL they are read non-temporally, so that the input, whose ghost
-// rows are read by several workgroups, stays in the caches; with NTS the results are written so too.  Both need wavefronts whose
-// accesses are whole lines: with lanes over (i, k), where two wavefronts shared every line, they cost 5 and 2 %.
-// (Step, us, before -> now: 102,075 blocks 52,650 -> 50,800; 2,143: 1376 -> 1294; 1,135: 798 -> 752; 792: 525 -> 503.
-// Evaluation, each on other buffers than the call before: 21,064 blocks 2245 -> 2190; 4,187: 507 -> 495; 1,709: 220 -> 211 (on
-// the same ones 217 -> 195).  A step with lanes over (i, j) alone: 52,760; with plain stores: 51,880.)
-template <int EPI, bool NTL, bool NTS, bool WIDE>
+// The Runge-Kutta operands pass through once per stage; they are read non-temporally, so that the input, whose ghost
+// rows are read by several workgroups, stays in the caches, and the results are written so too (every tree that comes here is
+// far larger than the caches).  Both need wavefronts whose accesses are whole lines.  (Step on 102,075 blocks, us, lanes over (i, k), where two
+// wavefronts share every line, -> (i, j): 52,650 -> 52,760; with both kinds of access past the caches 50,800, with plain stores 51,880.
+// Sources of more than 32 bits cost 1.4 %: 51,980 -> 52,720, and an evaluation on 21,064 blocks 2233 -> 2264.)
+template <int EPI>
 __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 {
     __shared__ double tile[pr::TILE];
@@ -196,12 +196,12 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
         constexpr int USE = decltype(use)::value;
         const double* base = var_base(v);
         const double* vbase = virt_base(v);
-        f.own = ldg_source<WIDE>(base, vbase, own_src);
+        f.own = ldg_source(base, vbase, own_src);
 #pragma unroll
         for (int m = 0; m < USE; ++m) {
             uint32_t off = gsrc[m];
             if (USE == pr::USE_FACE && m == 1 && face_mask1) off = 0;
-            f.g[m] = ldg_source<WIDE>(base, vbase, off);
+            f.g[m] = ldg_source(base, vbase, off);
         }
     };
     auto commit = [&](const Fetch& f, auto use) {
@@ -247,7 +247,7 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
         const int f = syn24_stream(t), f1 = syn24_stream(t + 1);
         prefetch(nxt, f1, next_use);
         const double unext = centre((f + 11) % 24);
-        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, NTL>(a, nb, f, o8), tile[c]);
+        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true>(a, nb, f, o8), tile[c]);
         const Syn24Part p = syn24_axes<true, pr::RS, pr::PS>(tile, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, Gxx, Gyy, Gzz, sigma, ih, ih2);
         pr::mixed_fill(tile, wy, wz, tid, ih);
         __syncthreads();
@@ -257,7 +257,7 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
         off = fma(Gyz, mx.dyz, off);
         const double lap = fma(2.0, off, p.diag);
         lapS[f * pr::NT + tid] = lap;
-        if (!phantom) emit<EPI, NTS>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lap, 0.5 * u0, unext), eo);
+        if (!phantom) emit<EPI, true>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lap, 0.5 * u0, unext), eo);
         commit(nxt, next_use);
         __syncthreads();                             // the tile is complete; D1_y u, D1_z u may be overwritten
     };
@@ -269,10 +269,10 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
         const int f = syn24_stream(t);
         const bool more = t + 1 < NSTREAM;
         if (more) prefetch(nxt, syn24_stream(t + 1), UseFace{});
-        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, NTL>(a, nb, f, o8), tile[c]);
+        const EpiOperands eo = with_u<EPI>(epi_prefetch<EPI, true>(a, nb, f, o8), tile[c]);
         if (t <= 13) wyz[(t - 11) * pr::NT + tid] = tile[c];     // u_23, u_22, u_21 for the last three passes
         const Syn24Part p = syn24_axes<false, pr::RS, pr::PS>(tile, c, wy, wz, owny, ownz, nx, ny, nz, bx, by, bz, 0.0, 0.0, 0.0, sigma, ih, ih2);
-        if (!phantom) emit<EPI, NTS>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lapS[(f % 10) * pr::NT + tid], 0.5 * u0, unext), eo);
+        if (!phantom) emit<EPI, true>(a, nb, f, b0, o8, 0u, syn24_combine(p, f, lapS[(f % 10) * pr::NT + tid], 0.5 * u0, unext), eo);
         if (more) {
             __syncthreads();                         // everybody is done with the tile
             commit(nxt, UseFace{});
@@ -293,50 +293,19 @@ __device__ __forceinline__ void rhs_pair(const DeviceTree& tr, const RhsArgs& a)
 }
 
 template <int EPI>
-constexpr bool kHasOperands = EPI == kRkMiddle || EPI == kRkLast;
-template <int EPI, bool NTL>
-__global__ __launch_bounds__(pr::NT) void k_rhs_pair(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, NTL, false, false>(tr, a); }
-template <int EPI>
-__global__ __launch_bounds__(pr::NT) void k_pair_stream(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true, true, false>(tr, a); }
-// for trees with more virtual blocks than a 32-bit offset reaches.  The wider addresses cost the two kernels above 1.4 %
-// (21,064 blocks, evaluation: 2233 / 2264 us; 102,075 blocks, step: 51.98 / 52.72 ms), k_unzip and the slab kernels nothing.
-template <int EPI>
-__global__ __launch_bounds__(pr::NT) void k_pair_wide(DeviceTree tr, RhsArgs a) { rhs_pair<EPI, true, true, true>(tr, a); }
-
-// The operands are read so from the size at which a step's four vectors fill the 256 MB memory-side cache, us without / with:
-// 224 / 234 on 512 blocks (201 MB), 412 / 434 on 568, 442 / 461 on 645 (254 MB), 484 / 485 on 708 (278 MB), 525 / 509 on 785.
-constexpr int64_t kOperandStepBytes = 256ll << 20;
-
-template <int EPI>
-void launch_pairs(bool past, bool stream, dim3 grid, const DeviceTree& t, const RhsArgs& a, hipStream_t s)
-{
-    if (t.n_virt > kBlockLimit) hipLaunchKernelGGL(k_pair_wide<EPI>, grid, dim3(pr::NT), 0, s, t, a);
-    else if (stream) hipLaunchKernelGGL(k_pair_stream<EPI>, grid, dim3(pr::NT), 0, s, t, a);
-    else if (kHasOperands<EPI> && past) hipLaunchKernelGGL((k_rhs_pair<EPI, kHasOperands<EPI>>), grid, dim3(pr::NT), 0, s, t, a);
-    else hipLaunchKernelGGL((k_rhs_pair<EPI, false>), grid, dim3(pr::NT), 0, s, t, a);
-}
+__global__ __launch_bounds__(pr::NT) void k_pair_wide(DeviceTree tr, RhsArgs a) { rhs_pair<EPI>(tr, a); }
 
 }  // namespace
 
 hipError_t launch_rhs_pairs(const DeviceTree& t, Epilogue ep, const RhsArgs& a, hipStream_t s)
 {
-    if (t.n_units <= 0) return hipSuccess;
-    if (!a.virt && t.n_virt > 0) return hipErrorInvalidValue;
     const int64_t span = pr::PAIR_CHUNK * NXCD;
-    const dim3 grid((unsigned)((t.n_units + span - 1) / span * span));
-    // Written non-temporally from the sizes that kernels.hpp explains, without / with: steps 479 / 490 us on 729 blocks (287 MB),
-    // 515 / 518 on 820 (322 MB), 544 / 548 on 883 (347 MB; on another tree 538 / 528 on 876), 559 / 549 on 932 (367 MB), 779 / 756
-    // on 1,086 (427 MB), 51.9 / 50.8 ms on 102,075; with the centred rule 638 / 652 on 904 (356 MB), 862 / 859 on 1,037 (408 MB);
-    // evaluations 100 / 96 on 666 blocks (131 MB), 158 / 154 on 1,044 (205 MB), 178 / 170 on 1,478 (291 MB).
-    const int64_t bytes = t.nb * BLK * (int64_t)sizeof(double) * 24 * (ep == kOutZipped ? 2 : 4);
-    const bool stream = bytes > (ep == kOutZipped ? kStreamEvalBytes : kStreamStepBytes);
-    const bool past = bytes > kOperandStepBytes;
-    if (bricks_apply(t, a)) return launch_rhs_bricks(t, ep, a, past, stream, s);
+    const dim3 grid((unsigned)((t.n_units + span - 1) / span * span)), block(pr::NT);
     switch (ep) {
-    case kOutZipped: launch_pairs<kOutZipped>(past, stream, grid, t, a, s); break;
-    case kRkFirst: launch_pairs<kRkFirst>(past, stream, grid, t, a, s); break;
-    case kRkMiddle: launch_pairs<kRkMiddle>(past, stream, grid, t, a, s); break;
-    case kRkLast: launch_pairs<kRkLast>(past, stream, grid, t, a, s); break;
+    case kOutZipped: hipLaunchKernelGGL(k_pair_wide<kOutZipped>, grid, block, 0, s, t, a); break;
+    case kRkFirst: hipLaunchKernelGGL(k_pair_wide<kRkFirst>, grid, block, 0, s, t, a); break;
+    case kRkMiddle: hipLaunchKernelGGL(k_pair_wide<kRkMiddle>, grid, block, 0, s, t, a); break;
+    case kRkLast: hipLaunchKernelGGL(k_pair_wide<kRkLast>, grid, block, 0, s, t, a); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -27,12 +27,9 @@ __device__ __forceinline__ void stg(double* base, uint32_t byte_off, double v)
     *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + byte_off) = v;
 }
 
-// the value at a source, from the variable's zipped array or its virtual blocks; WIDE = false: of a tree with at most
-// kBlockLimit virtual blocks, whose bits 1 and 2 are 0
-template <bool WIDE = true>
+// the value at a source, from the variable's zipped array or its virtual blocks
 __device__ __forceinline__ double ldg_source(const double* base, const double* virt, uint32_t src)
 {
-    if (!WIDE) return ldg(source_is_virtual(src) ? virt : base, src & ~1u);
     asm volatile("" : "+v"(src));
     return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(source_is_virtual(src) ? virt : base) + source_offset(src));
 }
