@@ -21,9 +21,11 @@ __global__ __launch_bounds__(256) void k_ghost_table(TableSource t, int64_t entr
 
 hipError_t launch_ghost_table(const TableSource& t, int64_t nb, int32_t* ghost_v, hipStream_t s)
 {
-    const int64_t entries = nb * kDirs;
-    hipLaunchKernelGGL(k_ghost_table, dim3(static_cast<unsigned>((entries + 255) / 256)), dim3(256), 0, s, t, entries, ghost_v);
-    return hipGetLastError();
+    int64_t entries = nb * kDirs;
+    // the launch's own status: hipGetLastError() may return one that an earlier call of the program has left, and the caller is uploading a tree
+    TableSource source = t;
+    void* args[] = {&source, &entries, &ghost_v};
+    return hipLaunchKernel(reinterpret_cast<const void*>(k_ghost_table), dim3(static_cast<unsigned>((entries + 255) / 256)), dim3(256), args, 0, s);
 }
 
 }  // namespace octfd
