@@ -244,7 +244,7 @@ int octree_get_leaves(const ot_tree* tree, ot_leaf* out, size_t cap)
 int octree_get_ghost_table(const ot_tree* tree, int32_t* out, size_t cap)
 {
     if (!tree || !out || cap < tree->host.leaves.size() * kDirs * kEntry) return OT_E_BADARG;
-    write_ghost_table(tree->host, false, out);
+    write_ghost_table(tree->host, out);
     return OT_OK;
 }
 

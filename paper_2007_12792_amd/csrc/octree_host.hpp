@@ -42,8 +42,8 @@ int plan_tree(const ot_build_params& p, HostTree& out);
 int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
 int build_tree(const ot_build_params& p, HostTree& out);
 int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
-// the ghost table, `virt`: with virtual blocks, to out[nb][27][5]
-void write_ghost_table(const HostTree& t, bool virt, int32_t* out);
+// the ghost table, to out[nb][27][5]
+void write_ghost_table(const HostTree& t, int32_t* out);
 void make_units(HostTree& t);
 
 }  // namespace octfd

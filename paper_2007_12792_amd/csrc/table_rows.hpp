@@ -30,6 +30,17 @@ __host__ __device__ constexpr ChildStep child_step(int c, int dir)
     return {static_cast<int8_t>(pz * 9 + py * 3 + px), static_cast<int8_t>(((z & 1) << 2) | ((y & 1) << 1) | (x & 1))};
 }
 
+// Whether child c of the neighbour octant in direction dir touches the block, on the octant's side -dir: along an axis with d = -1 the
+// upper children do, with d = +1 the lower ones; axes with d = 0 are free.
+__host__ __device__ constexpr bool touches(int c, int dir)
+{
+    const int d[3] = {dir % 3 - 1, (dir / 3) % 3 - 1, dir / 9 - 1};
+    int forced = 0, fixed = 0;
+    for (int a = 0; a < 3; ++a)
+        if (d[a]) { fixed |= 1 << a; forced |= (d[a] < 0 ? 1 : 0) << a; }
+    return (c & fixed) == forced;
+}
+
 // entry `dir` of block b; `virt`: a coarser neighbour as the virtual block that stands for it
 __host__ __device__ inline void table_entry(const TableSource& t, int64_t b, int dir, bool virt, int32_t (&e)[kEntry])
 {
@@ -50,16 +61,11 @@ __host__ __device__ inline void table_entry(const TableSource& t, int64_t b, int
         e[1] = ~nd;
         return;
     }
-    // the children that touch the block on the octant's side -dir: along an axis with d = -1 the upper ones, with d = +1 the lower
-    // ones; axes with d = 0 are free and enumerated x, then y, then z (ascending Morton order)
+    // the children that touch the block, x first, then y, then z (ascending Morton order)
     e[0] = kFiner;
-    const int d[3] = {dir % 3 - 1, (dir / 3) % 3 - 1, dir / 9 - 1};
-    int forced = 0, fixed = 0;
-    for (int a = 0; a < 3; ++a)
-        if (d[a]) { fixed |= 1 << a; forced |= (d[a] < 0 ? 1 : 0) << a; }
     int n = 1;
     for (int c = 0; c < 8; ++c)
-        if ((c & fixed) == forced && n < kEntry) e[n++] = ~t.node[nd + c];
+        if (touches(c, dir) && n < kEntry) e[n++] = ~t.node[nd + c];
 }
 
 }  // namespace octfd

@@ -1,9 +1,12 @@
 """The balance and the ghost table from neighbours of nodes with children, against the oracle's own walk: deep trees around the
 periodic corner and edges, and leaf lists that break the balance across a face, an edge or a corner only."""
+import time
+
 import numpy as np
 import pytest
 
 import paper_2007_12792_amd as octfd
+import synthdata as sd
 
 
 def children(leaf):
@@ -36,3 +39,18 @@ def test_unbalanced_leaf_lists_are_refused(child, inner):
     with pytest.raises(octfd.OctfdError) as e:
         octfd.Tree.from_leaves(three)
     assert e.value.status == octfd.OT_E_UNBALANCED
+
+
+def test_handing_out_the_table_is_little_more_than_a_copy():
+    """27,756 blocks: rows made one entry at a time take six copies of the table, as they are 1.4"""
+    t = octfd.Tree.build(3, 8, sd.seed_points("orbit", 1), np.array([int(0.1 * 0.83 ** k * sd.Q) for k in range(5)], np.uint32))
+    def fastest(go):
+        times = []
+        for _ in range(9):
+            start = time.perf_counter()
+            go()
+            times.append(time.perf_counter() - start)
+        return min(times)
+    table = t.ghost_table()
+    made, copied = fastest(t.ghost_table), fastest(table.copy)
+    assert made < 3.5 * copied, (t.n, made, copied)
