@@ -42,7 +42,7 @@ def test_unbalanced_leaf_lists_are_refused(child, inner):
 
 
 def test_handing_out_the_table_is_little_more_than_a_copy():
-    """27,756 blocks: rows made one entry at a time take six copies of the table, as they are 1.4"""
+    """27,791 blocks: rows made one entry at a time take six copies of the table, as they are 1.4"""
     t = octfd.Tree.build(3, 8, sd.seed_points("orbit", 1), np.array([int(0.1 * 0.83 ** k * sd.Q) for k in range(5)], np.uint32))
     def fastest(go):
         times = []
