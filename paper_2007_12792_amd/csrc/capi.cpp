@@ -207,7 +207,7 @@ int octree_build(const ot_build_params* params, ot_tree** out)
     ot_tree* t = new (std::nothrow) ot_tree;
     if (!t) return OT_E_NOMEM;
     int rc;
-    try { rc = plan_tree(*params, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
+    try { rc = build_tree(*params, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
     if (rc != OT_OK) { delete t; return rc; }
     *out = t;
     return OT_OK;
@@ -221,7 +221,7 @@ int octree_from_leaves(const ot_leaf* leaves, size_t n, uint32_t pad, ot_tree** 
     ot_tree* t = new (std::nothrow) ot_tree;
     if (!t) return OT_E_NOMEM;
     int rc;
-    try { rc = plan_tree_from_leaves(leaves, n, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
+    try { rc = tree_from_leaves(leaves, n, t->host); } catch (const std::bad_alloc&) { rc = OT_E_NOMEM; }
     if (rc != OT_OK) { delete t; return rc; }
     *out = t;
     return OT_OK;

@@ -213,18 +213,6 @@ int finish(Octree& t, bool may_split, HostTree& out)
     return OT_OK;
 }
 
-void expand(HostTree& t)
-{
-    t.ghost.resize(t.leaves.size() * kDirs * kEntry);
-    t.ghost_v.resize(t.ghost.size());
-    write_ghost_table(t, t.ghost.data());
-    int32_t e[kEntry], *v = t.ghost_v.data();
-    for (size_t n = 0; n < t.leaves.size() * kDirs; ++n) {
-        table_entry(t.source(), static_cast<int64_t>(n / kDirs), static_cast<int>(n % kDirs), true, e);
-        for (int m = 0; m < kEntry; ++m) *v++ = e[m];
-    }
-}
-
 }  // namespace
 
 constexpr uint64_t kAround = 0x0000077707770777ull;     // 3^3 of 4^3
@@ -285,7 +273,7 @@ void make_units(HostTree& t)
     }
 }
 
-int plan_tree(const ot_build_params& p, HostTree& out)
+int build_tree(const ot_build_params& p, HostTree& out)
 {
     if (p.lmin < 3 || p.lmax < p.lmin || p.lmax > 19) return OT_E_BADARG;
     if (p.points_per_dim != 8 || p.pad != 3 || p.periodic != 1) return OT_E_UNSUPPORTED;
@@ -313,7 +301,7 @@ int plan_tree(const ot_build_params& p, HostTree& out)
     return finish(t, true, out);
 }
 
-int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
+int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
 {
     if (!leaves || n == 0) return OT_E_BADARG;
     Octree t;
@@ -334,20 +322,6 @@ int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
     for (const Node& nd : t.nodes)
         if (nd.first_child == kUnset) return OT_E_INCOMPLETE;                // a gap
     return finish(t, false, out);
-}
-
-int build_tree(const ot_build_params& p, HostTree& out)
-{
-    const int rc = plan_tree(p, out);
-    if (rc == OT_OK) expand(out);
-    return rc;
-}
-
-int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
-{
-    const int rc = plan_tree_from_leaves(leaves, n, out);
-    if (rc == OT_OK) expand(out);
-    return rc;
 }
 
 }  // namespace octfd

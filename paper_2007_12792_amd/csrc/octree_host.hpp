@@ -32,14 +32,9 @@ struct HostTree {
     // leaves that are the lower and upper x child of one parent (they follow each other in storage), and, flagged
     // with kUnitSingle, every other block (a leaf whose x sibling is subdivided).  Every block belongs to exactly one unit.
     std::vector<int32_t> units;
-    // The ghost table in full, [nb][27][5], and the same with every coarser entry replaced by {kVirtual, virtual block}: what the device
-    // makes for itself.  Filled by build_tree() and tree_from_leaves() only.
-    std::vector<int32_t> ghost, ghost_v;
 };
 
-// Each returns an OT_* status.  plan_...: everything but the ghost table in full.
-int plan_tree(const ot_build_params& p, HostTree& out);
-int plan_tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
+// Each returns an OT_* status.  The ghost table itself is not kept: the device makes its own from source(), write_ghost_table() hands it out.
 int build_tree(const ot_build_params& p, HostTree& out);
 int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out);
 // the ghost table, to out[nb][27][5]

@@ -6,6 +6,7 @@
 
 #include "octree_host.hpp"
 #include "source.hpp"
+#include "tables.hpp"
 
 using namespace octfd;
 
@@ -27,10 +28,11 @@ int main()
     const long nb = static_cast<long>(t.leaves.size());
     std::printf("blocks %ld, virtual blocks %ld\n", nb, static_cast<long>(t.n_virt));
     if (t.n_virt <= kBlockLimit || nb >= kBlockLimit || t.n_virt > kVirtualLimit) { std::printf("FAILED: sizes\n"); return 1; }
+    const std::vector<int32_t> ghost_v = ghost_table_by_entry(t, true);
     long bad = 0, beyond = 0;
     for (long b = 0; b < nb; ++b)
         for (int dir = 0; dir < kDirs; ++dir) {
-            const int32_t* e = &t.ghost_v[(b * kDirs + dir) * kEntry];
+            const int32_t* e = &ghost_v[(b * kDirs + dir) * kEntry];
             const int r[3] = {dir % 3, (dir / 3) % 3, dir / 9};
             for (int corner = 0; corner < 8; ++corner) {
                 const int l[3] = {corner & 1 ? 7 : 0, corner & 2 ? 7 : 0, corner & 4 ? 7 : 0};

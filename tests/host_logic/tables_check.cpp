@@ -6,6 +6,7 @@
 
 #include "kernels.hpp"
 #include "octree_host.hpp"
+#include "tables.hpp"
 
 using namespace octfd;
 
@@ -14,16 +15,18 @@ static int fail(const char* what, long b) { std::printf("FAILED: %s (block %ld)\
 static int check(const HostTree& t)
 {
     const long nb = static_cast<long>(t.leaves.size());
+    const std::vector<int32_t> ghost = ghost_table(t), ghost_v = ghost_table_by_entry(t, true);
+    if (ghost != ghost_table_by_entry(t, false)) return fail("the table that is handed out", -1);
     // virtual blocks: every coarser entry of the ghost table has become a virtual block that is the right child
     // octant of the right source leaf; every virtual block is used
     const long nv = static_cast<long>(t.n_virt);
-    if (static_cast<long>(t.vblk.size()) != 2 * nv || t.ghost_v.size() != t.ghost.size())
+    if (static_cast<long>(t.vblk.size()) != 2 * nv || ghost_v.size() != ghost.size())
         return fail("sizes of the virtual-block tables", -1);
     std::vector<int> used(nv, 0);
     for (long b = 0; b < nb; ++b)
         for (int dir = 0; dir < kDirs; ++dir) {
-            const int32_t* e = &t.ghost[(b * kDirs + dir) * kEntry];
-            const int32_t* v = &t.ghost_v[(b * kDirs + dir) * kEntry];
+            const int32_t* e = &ghost[(b * kDirs + dir) * kEntry];
+            const int32_t* v = &ghost_v[(b * kDirs + dir) * kEntry];
             if (e[0] != kCoarser) {
                 for (int m = 0; m < kEntry; ++m)
                     if (e[m] != v[m]) return fail("an entry that is not coarser was changed", b);
@@ -48,7 +51,7 @@ static int check(const HostTree& t)
             for (int jj = 0; jj < 14; ++jj)
                 for (int ii = 0; ii < 14; ++ii) {
                     const int r[3] = {ii < 3 ? 0 : (ii < 11 ? 1 : 2), jj < 3 ? 0 : (jj < 11 ? 1 : 2), kk < 3 ? 0 : (kk < 11 ? 1 : 2)};
-                    const int32_t* v = &t.ghost_v[(b * kDirs + r[2] * 9 + r[1] * 3 + r[0]) * kEntry];
+                    const int32_t* v = &ghost_v[(b * kDirs + r[2] * 9 + r[1] * 3 + r[0]) * kEntry];
                     if (v[0] != kVirtual) continue;
                     // position inside the neighbour in that direction
                     const int ly = jj - 3 + (1 - r[1]) * 8, lz = kk - 3 + (1 - r[2]) * 8;
