@@ -83,29 +83,13 @@ bool near_seed(const Node& o, const ot_build_params& p)
     return false;
 }
 
-// child_step() as a table; and by where a child's neighbour lies among the 4^3 octants around and in the node
+// child_step() as a table
 struct ChildSteps {
-    ChildStep at[8][kDirs], around[64];
+    ChildStep at[8][kDirs];
     ChildSteps()
     {
         for (int c = 0; c < 8; ++c)
-            for (int dir = 0; dir < kDirs; ++dir) {
-                at[c][dir] = child_step(c, dir);
-                around[((c >> 2) + dir / 9) * 16 + ((c >> 1 & 1) + dir / 3 % 3) * 4 + (c & 1) + dir % 3] = at[c][dir];
-            }
-    }
-};
-
-// touches() as lists
-struct TouchingChildren {
-    int8_t count[kDirs], slot[kDirs][8];
-    TouchingChildren()
-    {
-        for (int dir = 0; dir < kDirs; ++dir) {
-            count[dir] = 0;
-            for (int c = 0; c < 8; ++c)
-                if (touches(c, dir) && count[dir] < kEntry - 1) slot[dir][count[dir]++] = static_cast<int8_t>(c);
-        }
+            for (int dir = 0; dir < kDirs; ++dir) at[c][dir] = child_step(c, dir);
     }
 };
 
@@ -215,45 +199,6 @@ int finish(Octree& t, bool may_split, HostTree& out)
 
 }  // namespace
 
-constexpr uint64_t kAround = 0x0000077707770777ull;     // 3^3 of 4^3
-
-// As table_entry() for every entry.  The neighbours of a node's children, themselves among them, are the 4^3 octants around and in it: looked up once
-// for all children, which follow each other in the traversal.  (Trees of 1,296, 27,791 and 102,075 blocks: 0.1, 3.0 and 11.3 ms; a copy of a table
-// made with the tree 0.05, 2.4 and 10.7, but then building the trees took 17 and 75 ms longer; table_entry() for each entry 0.65, 13.4 and 47.)
-void write_ghost_table(const HostTree& t, int32_t* out)
-{
-    static const ChildSteps steps;
-    static const TouchingChildren touching;
-    const int32_t* const nodes = t.node.data();
-    int32_t entry[64][kEntry], row = -1;             // per axis 0..3: a child's neighbour on that side, or itself
-    uint64_t finer = 0;
-    for (const int32_t parent : t.parent) {
-        if (parent >> 3 != row) {
-            row = parent >> 3;
-            const int32_t* at = &t.nbr[static_cast<size_t>(row) * kDirs];
-            int32_t above[kDirs];
-            for (int dir = 0; dir < kDirs; ++dir) above[dir] = nodes[at[dir]];
-            finer = 0;
-            for (int n = 0; n < 64; ++n) {
-                const ChildStep s = steps.around[n];
-                const int32_t a = above[s.parent_dir], nd = a < 0 ? a : nodes[a + s.slot];
-                int32_t* e = entry[n];
-                e[0] = a < 0 ? kCoarser : (nd < 0 ? kSame : kFiner);
-                e[1] = ~nd;
-                e[2] = e[3] = e[4] = -1;
-                finer |= static_cast<uint64_t>(nd >= 0) << n;
-            }
-        }
-        const int first = (parent >> 2 & 1) * 16 + (parent >> 1 & 1) * 4 + (parent & 1);
-        for (int n = 0; n < 9; ++n) std::memcpy(out + 3 * kEntry * n, entry[first + n / 3 * 16 + n % 3 * 4], sizeof entry[0] * 3);
-        for (uint64_t left = finer >> first & kAround; left; left &= left - 1) {
-            const int n = __builtin_ctzll(left), dir = n / 16 * 9 + n / 4 % 4 * 3 + n % 4;
-            for (int q = 0; q < touching.count[dir]; ++q) out[dir * kEntry + 1 + q] = ~nodes[~entry[first + n][1] + touching.slot[dir][q]];
-        }
-        out += kDirs * kEntry;
-    }
-}
-
 void make_units(HostTree& t)
 {
     const size_t nb = t.leaves.size();
@@ -322,6 +267,62 @@ int tree_from_leaves(const ot_leaf* leaves, size_t n, HostTree& out)
     for (const Node& nd : t.nodes)
         if (nd.first_child == kUnset) return OT_E_INCOMPLETE;                // a gap
     return finish(t, false, out);
+}
+
+namespace {
+constexpr uint64_t kAround = 0x0000077707770777ull;     // 3^3 of 4^3
+// child_step() by where a child's neighbour lies among the 4^3 octants around and in the node; touches() as lists
+struct RowTables {
+    ChildStep around[64];
+    int8_t count[kDirs], slot[kDirs][8];
+    RowTables()
+    {
+        for (int c = 0; c < 8; ++c)
+            for (int dir = 0; dir < kDirs; ++dir)
+                around[((c >> 2) + dir / 9) * 16 + ((c >> 1 & 1) + dir / 3 % 3) * 4 + (c & 1) + dir % 3] = child_step(c, dir);
+        for (int dir = 0; dir < kDirs; ++dir) {
+            count[dir] = 0;
+            for (int c = 0; c < 8; ++c)
+                if (touches(c, dir) && count[dir] < kEntry - 1) slot[dir][count[dir]++] = static_cast<int8_t>(c);
+        }
+    }
+};
+}  // namespace
+
+// As table_entry() for every entry.  The neighbours of a node's children, themselves among them, are the 4^3 octants around and in it: looked up once
+// for all children, which follow each other in the traversal.  (Trees of 1,296, 27,791 and 102,075 blocks: 0.1, 3.0 and 11.3 ms; a copy of a table
+// made with the tree 0.05, 2.4 and 10.7, but then building the trees took 17 and 75 ms longer; table_entry() for each entry 0.65, 13.4 and 47.)
+void write_ghost_table(const HostTree& t, int32_t* out)
+{
+    static const RowTables tables;
+    const int32_t* const nodes = t.node.data();
+    int32_t entry[64][kEntry], row = -1;             // per axis 0..3: a child's neighbour on that side, or itself
+    uint64_t finer = 0;
+    for (const int32_t parent : t.parent) {
+        if (parent >> 3 != row) {
+            row = parent >> 3;
+            const int32_t* at = &t.nbr[static_cast<size_t>(row) * kDirs];
+            int32_t above[kDirs];
+            for (int dir = 0; dir < kDirs; ++dir) above[dir] = nodes[at[dir]];
+            finer = 0;
+            for (int n = 0; n < 64; ++n) {
+                const ChildStep s = tables.around[n];
+                const int32_t a = above[s.parent_dir], nd = a < 0 ? a : nodes[a + s.slot];
+                int32_t* e = entry[n];
+                e[0] = a < 0 ? kCoarser : (nd < 0 ? kSame : kFiner);
+                e[1] = ~nd;
+                e[2] = e[3] = e[4] = -1;
+                finer |= static_cast<uint64_t>(nd >= 0) << n;
+            }
+        }
+        const int first = (parent >> 2 & 1) * 16 + (parent >> 1 & 1) * 4 + (parent & 1);
+        for (int n = 0; n < 9; ++n) std::memcpy(out + 3 * kEntry * n, entry[first + n / 3 * 16 + n % 3 * 4], sizeof entry[0] * 3);
+        for (uint64_t left = finer >> first & kAround; left; left &= left - 1) {
+            const int n = __builtin_ctzll(left), dir = n / 16 * 9 + n / 4 % 4 * 3 + n % 4;
+            for (int q = 0; q < tables.count[dir]; ++q) out[dir * kEntry + 1 + q] = ~nodes[~entry[first + n][1] + tables.slot[dir][q]];
+        }
+        out += kDirs * kEntry;
+    }
 }
 
 }  // namespace octfd
