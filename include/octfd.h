@@ -19,10 +19,10 @@
  *   - device entry points only enqueue work on `hip_stream` (a hipStream_t passed as void*, NULL =
  *     default stream).  They do not synchronise and do not allocate, with two exceptions.  (1) The
  *     device copies of a tree's index tables are a cache inside the opaque handle, which the first
- *     device call on the tree fills (one hipMalloc and synchronous copies; this fails inside a
- *     stream capture).  Call octree_upload beforehand where that matters.  The device that was
- *     current then must be the current one in every later call on the tree (else
- *     OT_E_UNSUPPORTED).  (2) rhs_eval_zipped, which has no workspace argument, keeps the virtual
+ *     device call on the tree fills (one hipMalloc, a copy and a kernel on the default stream, which
+ *     it waits for; this fails inside a stream capture).  Call octree_upload beforehand where that
+ *     matters.  The device that was current then must be the current one in every later call on the
+ *     tree (else OT_E_UNSUPPORTED).  (2) rhs_eval_zipped, which has no workspace argument, keeps the virtual
  *     blocks of its input (see there) in an array that belongs to the tree; its first call on a
  *     tree with level jumps allocates that array (a later call with more variables enlarges it).
  *     rk_step, rk_step_centred and rk_step_static never allocate once the tables are uploaded.
@@ -143,8 +143,9 @@ int unzip(const ot_tree *tree, int nvar, const double *zipped_dev, double *padde
  *   D1 = (fma(45,d1, fma(-9,d2, d3)) * (1/60)) / h;
  *   D2 = (fma(-490,u0, fma(270,s1, fma(-27,s2, 2*s3))) * (1/180)) / h^2;  Laplacian = (D2x+D2y)+D2z;
  *   KO = sigma * (((q_x+q_y)+q_z) / (64 h)),  q = fma(-20,u0, fma(15,s1, fma(-6,s2, s3))).
- * For SYN24 the call uses variables 10..19 of the output array as scratch while it runs (each is
- * overwritten with its final value before the call's work completes). */
+ * For SYN24 factors that are powers of two may be applied at another place of a sequence, which
+ * changes a result only where a value on the way underflows or comes within a factor of 2^16 of
+ * overflow. */
 int rhs_eval(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *params,
              const double *padded_dev, double *rhs_padded_dev, void *hip_stream);
 
@@ -207,7 +208,7 @@ int rk_step_static(const ot_tree *tree, ot_rhs_kind kind, const ot_rhs_params *p
  * composition.  It differs from rk_step only in how the virtual blocks (see rhs_eval_zipped) are
  * filled before each stage: with the centred stencils, each from the part of its source leaf's
  * padded block that it needs (gathered from the zipped vector).  Same stage kernels, same workspace (rk_centred_workspace_bytes
- * equals rk_workspace_bytes).  It takes 2 to 11 % longer than rk_step for the 24-field system, 11 to 28 % for
+ * equals rk_workspace_bytes).  It takes 4 to 13 % longer than rk_step for the 24-field system, 1 to 13 % for
  * the others, depending on the tree. */
 int unzip_centred(const ot_tree *tree, int nvar, const double *zipped_dev, double *padded_dev, void *hip_stream);
 int rk_centred_workspace_bytes(const ot_tree *tree, ot_rhs_kind kind, size_t *bytes);

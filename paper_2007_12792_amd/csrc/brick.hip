@@ -9,12 +9,13 @@
 //     that u_{a+11} is read again in ten passes of 24 only;
 //   - in the passes without second derivatives, two tiles in turn (the second where D1_y u, D1_z u lie otherwise), one barrier, and
 //     the data of the variable after the next one on its way: such a pass is shorter than the way to memory;
-//   - a workgroup goes from unit to unit, and the first data of the next is requested in the last passes of the one before;
+//   - a workgroup goes from unit to unit through its part of the launch, and the first data of the next is requested in the last passes of the
+//     one before;
 //   - loads are spread over a pass: issued at once they wait for each other at the L1 (64 bytes per cycle).
 // Every ghost item is a pair too (a 16-byte load where its neighbour is of the same level, two where it is finer), its place and
 // source worked out at compile time but for the table row.  Powers of two are moved out of the arithmetic where that changes
-// no rounding (short of underflow and of the last factor of eight before overflow): 104 instead of 116 fp64 instructions in a pass
-// without, 200 instead of 240 in one with second derivatives.
+// no rounding (short of underflow, and of overflow: within a factor of eight of it in products of fields, and where sigma itself, times up to
+// 2^16, passes it): 104 instead of 116 fp64 instructions in a pass without, 200 instead of 240 in one with second derivatives.
 // (us, thread per point -> here: step on 102,075 blocks 50,750 -> 43,500, on 21,064 10,920 -> 9,510, on 792 503 -> 442, on 526 399 -> 353;
 // evaluation on 21,064 blocks 2170 -> 1880, on 526 94 -> 82.  Of these: pairs and 16-byte words alone 10,150 for the step on 21,064
 // blocks, powers of two and compile-time items 10,120, pairs throughout and two passes ahead 9,680, from unit to unit 9,640, loads spread
@@ -593,10 +594,12 @@ __device__ __forceinline__ void rhs_brick(const DeviceTree& tr, const RhsArgs& a
 template <int EPI, bool NTL, bool NTS>
 __global__ __launch_bounds__(br::NT) void k_brick(DeviceTree tr, RhsArgs a) { br::rhs_brick<EPI, NTL, NTS>(tr, a); }
 
-// Padded in, padded out.  What bounds it is memory traffic: every value of the input is read once, all but the corners, and only the 8^3
-// interior of an output block is written, 64 bytes of every 112, so that no line of it is whole.  Plain stores wait in the L2 for the
-// rest of a line and are then completed from memory all the same; non-temporal ones push nothing else out.  Rows start at any
-// multiple of 8 bytes, which is all that the accesses ask for, and the sources are the same for all units.
+// Padded in, padded out.  What bounds it is memory traffic.  Of the ghosts of the input the faces of all variables are read and the edges of fields 0..9,
+// but no corners and none between the two blocks; of the own values those of fields 0..20 twice (0..9 also as pointwise factors, 10 as the first and
+// the last of the stream, 11..20 also as u_{a+11}), the second time mostly from the caches.  Only the 8^3 interior of an output block is
+// written, 64 bytes of every 112, so that no line of it is whole.  Plain stores wait in the L2 for the rest of a line and are then
+// completed from memory all the same; non-temporal ones push nothing else out.  Rows start at any multiple of 8 bytes, which is all that
+// the accesses ask for, and the sources are the same for all units.
 // (us, one block per workgroup, a thread per point, Lap parked in the output -> as here with plain stores -> as here: 512 blocks 88 -> 68 -> 62,
 // 792 179 -> 146 -> 117, 5,230 1135 -> 1034 -> 839, 21,064 4510 -> 4198 -> 3436; the pipeline of unzip, this and zip 207 -> 191 -> 193,
 // 384 -> 341 -> 334, 2473 -> 2363 -> 2184, 9678 -> 9334 -> 8590.)

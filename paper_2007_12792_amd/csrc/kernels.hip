@@ -177,7 +177,10 @@ __device__ __forceinline__ void fine_line(int o, const double (&v)[8], double (&
 // memory-side cache.  (us, plain / non-temporal, step, step with the centred rule, evaluation, unzip: 24 fields on 3,396 blocks, 334 MB, 1711 / 1687,
 // 1894 / 1876, 345 / 333, 695 / 690, on 21,064 9566 / 9444, 10380 / 10270, 1899 / 1876, 4078 / 4040; wave system on 47,783, 391 MB, 1503 / 1491,
 // 1595 / 1593, 261 / 258, 728 / 724.  Below: 24 fields on 1,919, 188 MB, 978 / 980, 1083 / 1088, 188 / 180, 379 / 382; wave system on 21,064,
-// 173 MB, 684 / 681, 752 / 752, 102 / 106, 251 / 290; Burgers on 47,783, 196 MB, 694 / 693, 751 / 750, 111 / 105, 351 / 337, on 21,064 unzip 123 / 150.)
+// 173 MB, 684 / 681, 752 / 752, 102 / 106, 251 / 290; Burgers on 47,783, 196 MB, 694 / 693, 751 / 750, 111 / 105, 351 / 337, on 21,064 unzip 123 / 150.  Just
+// above, on trees with 1.0, 0.45 and 0.36 virtual blocks per block: 24 fields 259 MB 1424 / 1409, 1600 / 1590, 290 / 284, 549 / 542, 289 MB 1493 / 1470, 1657 / 1642,
+// 293 / 291, 608 / 602; wave 259 MB 1010 / 1007, 1084 / 1085, 175 / 172, 482 / 480, 290 MB 1114 / 1110, 1189 / 1189, 192 / 192, 531 / 530; Burgers 259 MB 913 /
+// 912, 977 / 977, 150 / 149, 483 / 482, 289 MB 1015 / 1016, 1082 / 1084, 165 / 164, 538 / 534.)
 constexpr int64_t kStreamFillBytes = 256ll << 20;
 inline bool fill_streams(const DeviceTree& t, int nvar) { return nvar * t.nb * BLK * (int64_t)sizeof(double) > kStreamFillBytes; }
 template <bool NT>

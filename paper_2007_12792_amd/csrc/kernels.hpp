@@ -27,17 +27,19 @@ constexpr int32_t kUnitSingle = 1 << 30;   // flag on a unit: one block without 
 // From which size of a step's four vectors (an evaluation's input and output) kernels write, and where that pays read,
 // non-temporally.  Sizes at which the two ways take the same time, measured on trees around two centres (MB; virtual blocks,
 // which share the 256 MB memory-side cache, not counted):
-//   steps                     wave 286, Burgers 220 to 265, 24 fields 335 to 360
-//   with the centred rule     wave 312, Burgers 259, 24 fields 400
+//   steps                     wave 286, Burgers 220 to 265, 24 fields 305 to 330 (brick.hip)
+//   with the centred rule     wave 312, Burgers 259, 24 fields 340 to 390
 //   evaluations by themselves: below 100, 24 fields below 130 (non-temporal / plain there 0.78 to 0.99, at 290 MB 0.77 to 0.96)
 //   evaluations, the result read by the next launch: DERIVS 115 to 160, wave 75 to 90, Burgers below 60, 24 fields up to 145
 // The line for steps lies in the middle of these: on its wrong side a step loses at most 4 % (Burgers, 301 MB) and 2 % (24
-// fields with the centred rule, 355 MB).  The line for evaluations lies at the top of the last range.  New buffers each call,
+// fields with the centred rule, 327 MB).  The line for evaluations lies at the top of the last range.  New buffers each call,
 // plain / non-temporal, us, by themselves and with a reduction over the result behind each:
 //   DERIVS     59 MB 20.4 / 17.3, 31.1 / 31.1    144 MB 47.5 / 34.0, 64.5 / 66.9    158 MB 51.0 / 36.5, 69.4 / 71.6    189 MB 58.4 / 42.5, 79.6 / 82.0
 //   wave      151 MB 64.6 / 60.1, 74.6 / 76.2    177 MB 74.2 / 69.6, 85.3 / 87.4    Burgers 139 MB 55.0 / 50.5, 65.5 / 66.0
 //   24 fields 110 MB 82.6 / 79.4, 93.3 / 95.7    154 MB 95.1 / 90.9, 106.5 / 108.0    171 MB 98.7 / 95.8, 113.6 / 114.5
-// so above it a caller who reduces the result at once pays up to 3 %, and any other gains 3 to 28 %.
+// so above it a caller who reduces the result at once pays up to 3 %, and any other gains 3 to 28 %.  Another run of the same, on four sets of buffers in
+// turn, saw nothing of those 3 %: DERIVS 162 MB 49.6 / 38.2, 76.4 / 75.5, 175 MB 53.0 / 41.1, 80.9 / 80.5, 187 MB 55.9 / 42.8, 85.2 / 83.9; wave
+// 162 MB 63.4 / 61.2, 83.2 / 84.1, 187 MB 71.5 / 67.5, 92.9 / 92.4; Burgers 161 MB 58.1 / 54.0, 77.7 / 76.7; 24 fields 162 MB 97.2 / 94.7, 117.2 / 118.4.
 constexpr int64_t kStreamStepBytes = 300ll << 20, kStreamEvalBytes = 160000000;
 
 // workgroup i runs on XCD i mod kXcds; the kernels deal chunks of kChunk consecutive blocks to the XCDs in turn

@@ -11,7 +11,8 @@ constexpr int kDirs = 27;          // directions (dz+1)*9 + (dy+1)*3 + (dx+1)
 constexpr int kEntry = 5;          // {kind, id0..id3}
 enum GhostKind : int32_t { kSame = 0, kFiner = 1, kCoarser = 2, kVirtual = 3 };
 
-// What a row is made from: the tree's nodes and, of those with children, the neighbours; a thirtieth of the table's size.
+// What a row is made from: the tree's nodes and, of those with children, the neighbours; about 30 bytes per block, an
+// eighteenth of the table.
 struct TableSource {
     const int32_t* node;           // [n_nodes] first of eight children, or ~leaf id
     const int32_t* nbr;            // [n_inner][27] nodes: the neighbour octants of the nodes with children
